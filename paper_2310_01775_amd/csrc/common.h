@@ -2,7 +2,7 @@
 //
 // Lane mapping of the rollout kernels: one lane per (particle i, push side s,
 // block b), lane = 4 SL i + SL s + b, where SL = 1, 2 or 4 block slots (B
-// rounded up; slots b >= B are idle copies of block 0) hold the blocks of the
+// rounded up; slots b >= B are idle copies of block B - 1) hold the blocks of the
 // sub-rollout of side s (North, East, South, West = 0..3).  The blocks of a
 // sub-rollout exchange positions (and, in the reverse sweep, force adjoints)
 // by quad_perm DPP moves within their quad; the four sides of a particle meet

@@ -21,10 +21,11 @@ hipError_t launch_rollout_adj(const SimConst& c, int N, const float* theta, cons
 int rollout_tile_particles(int B, bool packed);
 hipError_t launch_rollout_fwd_batched(const ProblemDesc* descs, const int2* tiles, int ntiles, int block,
                                       int grid, const float* theta, float* cost, float* tape, uint32_t* status,
-                                      hipStream_t st, bool packed);
+                                      hipStream_t st, bool packed, int max_H, int max_B);
 hipError_t launch_rollout_adj_batched(const ProblemDesc* descs, const int2* tiles, int ntiles, int block,
                                       int grid, const float* theta, const float* tape, float cb_scalar,
-                                      float* grad, float* seg, uint32_t* status, hipStream_t st, bool packed);
+                                      float* grad, float* seg, uint32_t* status, hipStream_t st, bool packed, int max_H,
+                                      int max_B);
 
 // SVGD step of one problem.  h: when bandwidth > 0 it is used as is; otherwise
 // the median heuristic runs and writes h into the workspace (and h_out if

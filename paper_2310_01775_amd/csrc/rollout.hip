@@ -138,6 +138,12 @@ __device__ __forceinline__ void store_blk_at(const Blk& X, float* __restrict__ e
 // consecutive steps at once (one per lane) and each step reads its value back
 // with readlane, so a step costs one instruction instead of the polynomial.
 // Every pass (forward, replay, reverse) takes the same per-lane expression.
+__device__ __forceinline__ float profile_block(int j, float invL) {
+    return push_profile((float)((j & ~63) + 1 + (int)__lane_id()) * invL);
+}
+__device__ __forceinline__ float profile_lane(float v, int j) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), j & 63));
+}
 struct Profile {
     float invL;
     int base;
@@ -150,41 +156,59 @@ struct Profile {
         const int b0 = j & ~63;
         if (b0 != base) {
             base = b0;
-            v = push_profile((float)(b0 + 1 + (int)__lane_id()) * invL);
+            v = profile_block(j, invL);
         }
-        return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), j & 63));
+        return profile_lane(v, j);
     }
 };
+
+// f(j, s((j + 1) / L)) for the steps j0 <= j < j1 of a phase.  A step of a
+// rollout that has its SIMD to itself costs its instructions' issue and its
+// branches (no other wave fills the fetch after a taken branch), so the loop
+// over a block of 64 steps holds no profile check and no masked store.
+// Forward at N = 1024, B = 3, T = 200: 74 us with the check, the mask and the
+// per-phase inputs read at each phase start; 60 us without the check and with
+// the inputs read once (phase_table); 55 us with the stores unmasked.
+template <class F>
+__device__ __forceinline__ void for_steps(int j0, int j1, float invL, F&& f) {
+    for (int j = j0; j < j1;) {
+        const float v = profile_block(j, invL);
+        const int je = min(j1, (j & ~63) + 64);
+#pragma unroll 1
+        for (; j < je; ++j) f(j, profile_lane(v, j));
+    }
+}
 
 // Index of the K-th block other than b (increasing order).
 __host__ __device__ constexpr int other_block(int K, int b) { return K < b ? K : K + 1; }
 
 // quad_perm control that hands lane slot b the value of slot other_block(K, b)
-// of its own group of SL slots.
-template <int SL, int K>
+// of its own group of SL slots (an idle slot takes what block B - 1 takes).
+template <int B, int K>
 constexpr int other_sel() {
+    constexpr int SL = Slots<B>::SL;
     int sel = 0;
     for (int p = 0; p < 4; ++p) {
         const int b = p % SL, base = p - b;
-        int q = other_block(K, b);
+        int q = other_block(K, b < B ? b : B - 1);
         if (q >= SL) q = 0;
         sel |= (base + q) << (2 * p);
     }
     return sel;
 }
 
-template <int SL, int K>
+template <int B, int K>
 __device__ __forceinline__ float from_other_k(float v) {
-    constexpr int sel = other_sel<SL, K>();
+    constexpr int sel = other_sel<B, K>();
     return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), sel, 0xF, 0xF, false));
 }
 
 // K is a constant of an unrolled loop (0..2).
-template <int SL>
+template <int B>
 __device__ __forceinline__ float from_other(float v, int K) {
-    if (K == 0) return from_other_k<SL, 0>(v);
-    if (K == 1) return from_other_k<SL, 1>(v);
-    return from_other_k<SL, 2>(v);
+    if (K == 0) return from_other_k<B, 0>(v);
+    if (K == 1) return from_other_k<B, 1>(v);
+    return from_other_k<B, 2>(v);
 }
 
 // Sum over the four sides of a particle (lanes SL apart): (v0+v1)+(v2+v3) on
@@ -207,7 +231,7 @@ __device__ __forceinline__ float slot_sum(float v) {
     return v;
 }
 
-// Constants of this lane's block b (slots b >= B take block 0's).
+// Constants of this lane's block b (an idle slot duplicates block B - 1).
 template <int B>
 struct BlkConst {
     float cf, cr, ev2, ew2, dtm, dtI, crw2;
@@ -247,7 +271,7 @@ __device__ __forceinline__ BlkConst<B> blk_const(const SimConst& c, int b) {
     for (int K = 0; K < (B > 1 ? B - 1 : 1); ++K) {
         float v = 0.0f;
 #pragma unroll
-        for (int bb = 0; bb < B; ++bb) v = (b == bb && B > 1) ? c.hsum[bb][other_block(K, bb)] : v;
+        for (int bb = 0; bb < B; ++bb) v = (b == bb && B > 1 && K < B - 1) ? c.hsum[bb][other_block(K, bb)] : v;
         k.hs[K] = v;
     }
     return k;
@@ -265,8 +289,8 @@ __device__ __forceinline__ void step_forward(const SimConst& c, const BlkConst<B
     float ox[NO > 0 ? NO : 1], oy[NO > 0 ? NO : 1];
 #pragma unroll
     for (int K = 0; K < NO; ++K) {
-        ox[K] = from_other<SL>(X.x, K);
-        oy[K] = from_other<SL>(X.y, K);
+        ox[K] = from_other<B>(X.x, K);
+        oy[K] = from_other<B>(X.y, K);
     }
     // regularised Coulomb friction
     const float inv = hw_rsq(fmaf(X.vx, X.vx, fmaf(X.vy, X.vy, k.ev2)));
@@ -329,10 +353,10 @@ __device__ __forceinline__ void step_reverse(const SimConst& c, const BlkConst<B
     float ox[NO > 0 ? NO : 1], oy[NO > 0 ? NO : 1], ofx[NO > 0 ? NO : 1], ofy[NO > 0 ? NO : 1];
 #pragma unroll
     for (int K = 0; K < NO; ++K) {
-        ox[K] = from_other<SL>(X.x, K);
-        oy[K] = from_other<SL>(X.y, K);
-        ofx[K] = from_other<SL>(Fxb, K);
-        ofy[K] = from_other<SL>(Fyb, K);
+        ox[K] = from_other<B>(X.x, K);
+        oy[K] = from_other<B>(X.y, K);
+        ofx[K] = from_other<B>(Fxb, K);
+        ofy[K] = from_other<B>(Fyb, K);
     }
     // pusher
     {
@@ -405,16 +429,36 @@ __device__ __forceinline__ void side_frame(int s, Push& p) {
     p.ty = p.nx;
 }
 
-// softmax(a_k)_s of this lane's side (max-subtracted, Eq. 5's relaxation)
-__device__ __forceinline__ float side_weight(const float* __restrict__ theta, int N, int i, int k, int s) {
-    float a0 = theta[(int64_t)(6 * k + 0) * N + i];
-    float a1 = theta[(int64_t)(6 * k + 1) * N + i];
-    float a2 = theta[(int64_t)(6 * k + 2) * N + i];
-    float a3 = theta[(int64_t)(6 * k + 3) * N + i];
+// softmax(a)_s of this lane's side (max-subtracted, Eq. 5's relaxation)
+__device__ __forceinline__ float side_weight(float a0, float a1, float a2, float a3, int s) {
     float m = fmaxf(fmaxf(a0, a1), fmaxf(a2, a3));
     float e0 = expf(a0 - m), e1 = expf(a1 - m), e2 = expf(a2 - m), e3 = expf(a3 - m);
     float es = (s == 0) ? e0 : (s == 1) ? e1 : (s == 2) ? e2 : e3;
     return es / (((e0 + e1) + e2) + e3);
+}
+
+// A lane's inputs of every phase -- its side's weight z, the offset o and the
+// depth D -- read once before the time loop into the wave's LDS table
+// [H][3][64].  Read at each phase start instead, they waited behind the tape
+// stores in flight (memory operations complete in order), a drain of the
+// store queue per phase.
+constexpr int kPhaseFloats = 3 * 64;  // one phase of the table
+__device__ __forceinline__ void phase_table(const float* __restrict__ theta, int N, int i, int s, int H, float* tab,
+                                            int lw) {
+    float a[kMaxPushes][6];
+#pragma unroll
+    for (int k = 0; k < kMaxPushes; ++k)
+        if (k < H)
+#pragma unroll
+            for (int c = 0; c < 6; ++c) a[k][c] = theta[(int64_t)(6 * k + c) * N + i];
+#pragma unroll
+    for (int k = 0; k < kMaxPushes; ++k)
+        if (k < H) {
+            float* t = tab + k * kPhaseFloats + lw;
+            t[0] = side_weight(a[k][0], a[k][1], a[k][2], a[k][3], s);
+            t[64] = a[k][4];
+            t[128] = a[k][5];
+        }
 }
 
 __device__ __forceinline__ float smooth_abs(float u, float ea2) { return sqrtf(u * u + ea2); }
@@ -422,22 +466,25 @@ __device__ __forceinline__ float smooth_abs(float u, float ea2) { return sqrtf(u
 // ---------------------------------------------------------------------------
 // Forward rollout of one lane: particle i, side s, block slot b.  Every lane of
 // the wave runs it (cross-lane moves and readlane need all lanes): lanes past
-// the last particle repeat particle N-1 and write nothing.
+// the last particle repeat particle N-1 and idle slots block B-1: they store
+// the same values to the same places of the tape, so no store of the time loop
+// is masked.  tab: the wave's phase table in LDS.
 template <int B>
 __device__ __forceinline__ void rollout_fwd_lane(const SimConst& c, int N, const float* __restrict__ theta,
                                                  float* __restrict__ cost, float* __restrict__ tape,
-                                                 const TapeGeom& g, uint32_t* status, int64_t lane) {
+                                                 const TapeGeom& g, uint32_t* status, int64_t lane, float* tab) {
     constexpr int SL = Slots<B>::SL;
     const int64_t iw = lane / (4 * SL);
     const bool live = iw < N;
     const int i = live ? (int)iw : N - 1;
     const int r = (int)(lane % (4 * SL));
-    const int s = r / SL, b = r % SL;
-    const bool real = b < B && live;  // writes its block's states
+    const int s = r / SL, b = min(r % SL, B - 1);
     const int64_t slot = ((int64_t)4 * i + s) * B + b;
     const uint32_t off = (uint32_t)(slot * 6);  // within an entry (< 2^32 floats)
     const int64_t stride = 6 * B * g.lanes;  // floats per tape entry
     const int H = c.H, T = c.T;
+    const int lw = (int)(lane & 63);
+    phase_table(theta, N, i, s, H, tab, lw);
     const BlkConst<B> k = blk_const<B>(c, b);
 
     Blk S;
@@ -455,36 +502,31 @@ __device__ __forceinline__ void rollout_fwd_lane(const SimConst& c, int N, const
         const float invL = 1.0f / (float)(tk1 - tk);
         Px[kk] = S.x;
         Py[kk] = S.y;
-        const float z = side_weight(theta, N, i, kk, s);
-        const float o = theta[(int64_t)(6 * kk + 4) * N + i];
-        const float D = theta[(int64_t)(6 * kk + 5) * N + i];
+        const float* ph = tab + kk * kPhaseFloats + lw;
+        const float z = ph[0], o = ph[64], D = ph[128];
         Anchor an;
         phase_push(c, S.x, S.y, S.ph, o, D, p, an);  // block 0's anchor on slot 0
         Lbound += relu(fabsf(o) - c.omax) * relu(fabsf(o) - c.omax) + relu(-D) * relu(-D) +
                   relu(D - c.dmax) * relu(D - c.dmax);
         Blk X = S;
-        Profile prof;
-        prof.reset(invL);
         const int nst = tk1 - tk;
         if (tape && g.ckpt == 0) {
             float* e = tape + (int64_t)tk * stride;
-            for (int j = 0; j < nst; ++j, e += stride) {
-                if (real) store_blk_at(X, e, off);
-                step_forward<B>(c, k, b, X, p, prof.at(j));
+            for_steps(0, nst, invL, [&](int, float sig) {
+                store_blk_at(X, e, off);
+                e += stride;
+                step_forward<B>(c, k, b, X, p, sig);
+            });
+        } else if (tape) {
+            for (int js = 0; js < nst; js += g.ckpt, ++entry) {  // a checkpoint, then its segment
+                store_blk_at(X, tape + entry * stride, off);
+                for_steps(js, min(js + g.ckpt, nst), invL,
+                          [&](int, float sig) { step_forward<B>(c, k, b, X, p, sig); });
             }
         } else {
-            int until = 0;  // steps to the next checkpoint
-            for (int j = 0; j < nst; ++j) {
-                if (tape && until == 0) {
-                    if (real) store_blk_at(X, tape + entry * stride, off);
-                    ++entry;
-                    until = g.ckpt;
-                }
-                --until;
-                step_forward<B>(c, k, b, X, p, prof.at(j));
-            }
+            for_steps(0, nst, invL, [&](int, float sig) { step_forward<B>(c, k, b, X, p, sig); });
         }
-        if (tape && real) store_blk_at(X, tape + g.ends_off + (int64_t)kk * stride, off);
+        if (tape) store_blk_at(X, tape + g.ends_off + (int64_t)kk * stride, off);
         // phase mixture over the sides
         S.x = side_sum<SL>(z * X.x);
         S.y = side_sum<SL>(z * X.y);
@@ -495,7 +537,7 @@ __device__ __forceinline__ void rollout_fwd_lane(const SimConst& c, int N, const
     }
     Px[H] = S.x;
     Py[H] = S.y;
-    if (s != 0 || b != 0 || !live) return;
+    if (r != 0 || !live) return;
     // cost (Appendix E-B), on slot 0 of side 0
     const float dxg = fabsf(Px[H] - c.goal[0]) - c.tol, dyg = fabsf(Py[H] - c.goal[1]) - c.tol;
     const float Ltarget = relu(dxg) * relu(dxg) + relu(dyg) * relu(dyg);
@@ -518,22 +560,22 @@ __device__ __forceinline__ void rollout_adj_lane(const SimConst& c, int N, const
                                                  const float* __restrict__ tape, const TapeGeom& g,
                                                  const float* __restrict__ cost_bar, float cb_scalar,
                                                  float* __restrict__ grad, float* __restrict__ seg,
-                                                 uint32_t* status, int64_t lane) {
+                                                 uint32_t* status, int64_t lane, float* tab) {
     constexpr int SL = Slots<B>::SL;
     const int64_t iw = lane / (4 * SL);
     const bool live = iw < N;  // lanes past the last particle repeat particle N-1, write nothing
     const int i = live ? (int)iw : N - 1;
     const int r = (int)(lane % (4 * SL));
-    const int s = r / SL, b = r % SL;
-    const bool blk = b < B;        // a block slot (not an idle one)
-    const bool real = blk && live;  // writes scratch and results
+    const int s = r / SL, b = min(r % SL, B - 1);
+    const bool blk = r % SL < B;  // a block slot (an idle one duplicates block B - 1)
     const int64_t slot = ((int64_t)4 * i + s) * B + b;
     const int64_t slot0 = ((int64_t)4 * i + s) * B;  // block 0 of this sub-rollout
-    const int64_t lslot = blk ? slot : slot0;         // idle slots read block 0's data
-    const uint32_t off = (uint32_t)(slot * 6), loff = (uint32_t)(lslot * 6);
+    const uint32_t off = (uint32_t)(slot * 6);
     const int H = c.H, T = c.T;
     const int64_t stride = 6 * B * g.lanes;  // floats per tape entry
     const BlkConst<B> k = blk_const<B>(c, b);
+    const int lw = (int)(lane & 63);
+    phase_table(theta, N, i, s, H, tab, lw);
 
     // entry index of each phase start
     int ent[kMaxPushes];
@@ -553,7 +595,7 @@ __device__ __forceinline__ void rollout_adj_lane(const SimConst& c, int N, const
     }
     float phT;
     {
-        const float z = side_weight(theta, N, i, H - 1, s);
+        const float z = tab[(H - 1) * kPhaseFloats + lw];
         const float* e = tape + g.ends_off + (int64_t)(H - 1) * stride + slot0 * 6;
         Px[H] = side_sum<SL>(z * e[0]);
         Py[H] = side_sum<SL>(z * e[1]);
@@ -610,12 +652,11 @@ __device__ __forceinline__ void rollout_adj_lane(const SimConst& c, int N, const
     for (int kk = H - 1; kk >= 0; --kk) {
         const int tk = phase_start(kk, T, H), tk1 = phase_start(kk + 1, T, H);
         const float invL = 1.0f / (float)(tk1 - tk);
-        const float z = side_weight(theta, N, i, kk, s);
-        const float o = theta[(int64_t)(6 * kk + 4) * N + i];
-        const float D = theta[(int64_t)(6 * kk + 5) * N + i];
+        const float* pt = tab + kk * kPhaseFloats + lw;
+        const float z = pt[0], o = pt[64], D = pt[128];
         // phase end: S_{k+1} = sum_s z_s X_s
         Blk Xe, L;
-        load_blk_at(Xe, tape + g.ends_off + (int64_t)kk * stride, loff);
+        load_blk_at(Xe, tape + g.ends_off + (int64_t)kk * stride, off);
         const float zp = Ls.x * Xe.x + Ls.y * Xe.y + Ls.ph * Xe.ph + Ls.vx * Xe.vx + Ls.vy * Xe.vy + Ls.om * Xe.om;
         const float zb = slot_sum<SL>(blk ? zp : 0.0f);
         L.x = z * Ls.x;
@@ -627,7 +668,7 @@ __device__ __forceinline__ void rollout_adj_lane(const SimConst& c, int N, const
         const float ab = z * (zb - side_sum<SL>(z * zb));  // softmax VJP
         // anchor of the phase (block 0's pose, on slot 0)
         Blk A;
-        load_blk_at(A, tape + ent[kk] * stride, loff);
+        load_blk_at(A, tape + ent[kk] * stride, off);
         Anchor an;
         phase_push(c, A.x, A.y, A.ph, o, D, p, an);
         float P0xb = 0.0f, P0yb = 0.0f, Vxb = 0.0f, Vyb = 0.0f;
@@ -642,14 +683,14 @@ __device__ __forceinline__ void rollout_adj_lane(const SimConst& c, int N, const
             const float* base = tape + (int64_t)tk * stride;  // step j's entry: base + j stride
             int j = tk1 - tk - 1;
             Blk XA, XB;
-            load_blk_at(XA, base + (int64_t)j * stride, loff);
-            load_blk_at(XB, base + (int64_t)max(j - 1, 0) * stride, loff);
+            load_blk_at(XA, base + (int64_t)j * stride, off);
+            load_blk_at(XB, base + (int64_t)max(j - 1, 0) * stride, off);
             for (; j >= 1; j -= 2) {
                 Blk X = XA;
-                load_blk_at(XA, base + (int64_t)max(j - 2, 0) * stride, loff);
+                load_blk_at(XA, base + (int64_t)max(j - 2, 0) * stride, off);
                 step_reverse<B>(c, k, b, X, L, p, prof.at(j), P0xb, P0yb, Vxb, Vyb);
                 X = XB;
-                load_blk_at(XB, base + (int64_t)max(j - 3, 0) * stride, loff);
+                load_blk_at(XB, base + (int64_t)max(j - 3, 0) * stride, off);
                 step_reverse<B>(c, k, b, X, L, p, prof.at(j - 1), P0xb, P0yb, Vxb, Vyb);
             }
             if (j == 0) step_reverse<B>(c, k, b, XA, L, p, prof.at(0), P0xb, P0yb, Vxb, Vyb);
@@ -659,13 +700,13 @@ __device__ __forceinline__ void rollout_adj_lane(const SimConst& c, int N, const
                 const int js = q * g.ckpt;
                 const int je = min(js + g.ckpt, tk1 - tk);
                 Blk X;
-                load_blk_at(X, tape + (int64_t)(ent[kk] + q) * stride, loff);
+                load_blk_at(X, tape + (int64_t)(ent[kk] + q) * stride, off);
                 for (int j = js; j < je; ++j) {  // replay the segment
-                    if (real) store_blk_at(X, seg + (int64_t)(j - js) * stride, off);
+                    store_blk_at(X, seg + (int64_t)(j - js) * stride, off);
                     step_forward<B>(c, k, b, X, p, prof.at(j));
                 }
                 for (int j = je - 1; j >= js; --j) {
-                    if (real) load_blk_at(X, seg + (int64_t)(j - js) * stride, off);  // a lane reads its own writes
+                    load_blk_at(X, seg + (int64_t)(j - js) * stride, off);  // a lane reads its own writes
                     step_reverse<B>(c, k, b, X, L, p, prof.at(j), P0xb, P0yb, Vxb, Vyb);
                 }
             }
@@ -935,11 +976,12 @@ __device__ __forceinline__ void stage_blks(const Blk (&X)[B], float* stage, int 
 }
 
 // Forward rollout of one packed lane (particle i, side s); as rollout_fwd_lane.
-// WAVES: waves per workgroup (each stages its tape stores in its own LDS region).
-template <int B, int WAVES>
+// lds: this wave's LDS, the phase table [H][3][64] and then the staging of its
+// tape stores (64 lanes x 6B floats).
+template <int B>
 __device__ __forceinline__ void rollout_fwd_packed(const SimConst& c, int N, const float* __restrict__ theta,
                                                    float* __restrict__ cost, float* __restrict__ tape,
-                                                   const TapeGeom& g, uint32_t* status, int64_t lane) {
+                                                   const TapeGeom& g, uint32_t* status, int64_t lane, float* lds) {
     const int64_t iw = lane / 4;
     const bool live = iw < N;
     const int i = live ? (int)iw : N - 1;
@@ -950,9 +992,9 @@ __device__ __forceinline__ void rollout_fwd_packed(const SimConst& c, int N, con
     // the wave's span of a tape entry: its live lanes' 6B floats each, from
     // the first lane's slot on (a multiple of 4 floats: lanes come in
     // particles of 4)
-    __shared__ __align__(16) float stage_all[WAVES][64 * 6 * B];  // one region per wave of a workgroup
-    float* stage = stage_all[WAVES == 1 ? 0 : (threadIdx.x >> 6) % WAVES];
     const int lw = (int)(lane & 63);
+    float* stage = lds + H * kPhaseFloats;
+    phase_table(theta, N, i, s, H, lds, lw);
     const int64_t lane0 = lane - lw;
     const int64_t wave_off = lane0 * 6 * B;
     const int span4 = (int)(min((int64_t)64, (int64_t)4 * N - lane0) * 6 * B / 4);
@@ -974,9 +1016,8 @@ __device__ __forceinline__ void rollout_fwd_packed(const SimConst& c, int N, con
         const float invL = 1.0f / (float)(tk1 - tk);
         Px[kk] = S[0].x;
         Py[kk] = S[0].y;
-        const float z = side_weight(theta, N, i, kk, s);
-        const float o = theta[(int64_t)(6 * kk + 4) * N + i];
-        const float D = theta[(int64_t)(6 * kk + 5) * N + i];
+        const float* ph = lds + kk * kPhaseFloats + lw;
+        const float z = ph[0], o = ph[64], D = ph[128];
         Anchor an;
         phase_push(c, S[0].x, S[0].y, S[0].ph, o, D, p, an);
         Lbound += relu(fabsf(o) - c.omax) * relu(fabsf(o) - c.omax) + relu(-D) * relu(-D) +
@@ -984,8 +1025,6 @@ __device__ __forceinline__ void rollout_fwd_packed(const SimConst& c, int N, con
         Blk X[B];
 #pragma unroll
         for (int b = 0; b < B; ++b) X[b] = S[b];
-        Profile prof;
-        prof.reset(invL);
         const int nst = tk1 - tk;
         if (tape && g.ckpt == 0) {
             // Each step's states go through LDS so that the wave writes its
@@ -993,25 +1032,22 @@ __device__ __forceinline__ void rollout_fwd_packed(const SimConst& c, int N, con
             // lanes (a lane's own 6B floats would make every store
             // instruction touch B times the cache lines).
             float* e = tape + (int64_t)tk * stride + wave_off;
-            for (int j = 0; j < nst; ++j, e += stride) {
+            for_steps(0, nst, invL, [&](int, float sig) {
                 stage_blks<B>(X, stage, lw);
                 wave_lds_sync();
                 for (int k = lw; k < span4; k += 64)
                     *reinterpret_cast<float4*>(e + 4 * k) = *reinterpret_cast<const float4*>(stage + 4 * k);
                 wave_lds_sync();
-                step_forward_packed<B>(c, X, p, prof.at(j));
+                e += stride;
+                step_forward_packed<B>(c, X, p, sig);
+            });
+        } else if (tape) {
+            for (int js = 0; js < nst; js += g.ckpt, ++entry) {
+                if (live) store_blks<B>(X, tape + entry * stride, off);
+                for_steps(js, min(js + g.ckpt, nst), invL, [&](int, float sig) { step_forward_packed<B>(c, X, p, sig); });
             }
         } else {
-            int until = 0;
-            for (int j = 0; j < nst; ++j) {
-                if (tape && until == 0) {
-                    if (live) store_blks<B>(X, tape + entry * stride, off);
-                    ++entry;
-                    until = g.ckpt;
-                }
-                --until;
-                step_forward_packed<B>(c, X, p, prof.at(j));
-            }
+            for_steps(0, nst, invL, [&](int, float sig) { step_forward_packed<B>(c, X, p, sig); });
         }
         if (tape && live) store_blks<B>(X, tape + g.ends_off + (int64_t)kk * stride, off);
 #pragma unroll
@@ -1047,7 +1083,7 @@ __device__ __forceinline__ void rollout_adj_packed(const SimConst& c, int N, con
                                                    const float* __restrict__ tape, const TapeGeom& g,
                                                    const float* __restrict__ cost_bar, float cb_scalar,
                                                    float* __restrict__ grad, float* __restrict__ seg,
-                                                   uint32_t* status, int64_t lane) {
+                                                   uint32_t* status, int64_t lane, float* tab) {
     const int64_t iw = lane / 4;
     const bool live = iw < N;
     const int i = live ? (int)iw : N - 1;
@@ -1056,6 +1092,8 @@ __device__ __forceinline__ void rollout_adj_packed(const SimConst& c, int N, con
     const uint32_t off = (uint32_t)(slot0 * 6);
     const int H = c.H, T = c.T;
     const int64_t stride = 6 * B * g.lanes;
+    const int lw = (int)(lane & 63);
+    phase_table(theta, N, i, s, H, tab, lw);
 
     int ent[kMaxPushes];
     {
@@ -1073,7 +1111,7 @@ __device__ __forceinline__ void rollout_adj_packed(const SimConst& c, int N, con
     }
     float phT;
     {
-        const float z = side_weight(theta, N, i, H - 1, s);
+        const float z = tab[(H - 1) * kPhaseFloats + lw];
         const float* e = tape + g.ends_off + (int64_t)(H - 1) * stride + slot0 * 6;
         Px[H] = side_sum<1>(z * e[0]);
         Py[H] = side_sum<1>(z * e[1]);
@@ -1121,9 +1159,8 @@ __device__ __forceinline__ void rollout_adj_packed(const SimConst& c, int N, con
     for (int kk = H - 1; kk >= 0; --kk) {
         const int tk = phase_start(kk, T, H), tk1 = phase_start(kk + 1, T, H);
         const float invL = 1.0f / (float)(tk1 - tk);
-        const float z = side_weight(theta, N, i, kk, s);
-        const float o = theta[(int64_t)(6 * kk + 4) * N + i];
-        const float D = theta[(int64_t)(6 * kk + 5) * N + i];
+        const float* pt = tab + kk * kPhaseFloats + lw;
+        const float z = pt[0], o = pt[64], D = pt[128];
         Blk Xe[B], L[B];
         load_blks<B>(Xe, tape + g.ends_off + (int64_t)kk * stride, off);
         float zpb[B];
@@ -1231,7 +1268,8 @@ __global__ __launch_bounds__(kRolloutBlock) void k_rollout_fwd_packed(SimConst c
                                                                       float* __restrict__ tape, TapeGeom g,
                                                                       uint32_t* status) {
     const int64_t lane = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    rollout_fwd_packed<B, 1>(c, N, theta, cost, tape, g, status, lane);
+    extern __shared__ __align__(16) float lds[];
+    rollout_fwd_packed<B>(c, N, theta, cost, tape, g, status, lane, lds);
 }
 
 template <int B>
@@ -1242,7 +1280,8 @@ __global__ __launch_bounds__(kRolloutBlock) void k_rollout_adj_packed(SimConst c
                                                                       float cb_scalar, float* __restrict__ grad,
                                                                       float* __restrict__ seg, uint32_t* status) {
     const int64_t lane = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    rollout_adj_packed<B>(c, N, theta, tape, g, cost_bar, cb_scalar, grad, seg, status, lane);
+    extern __shared__ __align__(16) float lds[];
+    rollout_adj_packed<B>(c, N, theta, tape, g, cost_bar, cb_scalar, grad, seg, status, lane, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -1251,7 +1290,8 @@ __global__ __launch_bounds__(kRolloutBlock) void k_rollout_fwd(SimConst c, int N
                                                                float* __restrict__ cost, float* __restrict__ tape,
                                                                TapeGeom g, uint32_t* status) {
     const int64_t lane = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    rollout_fwd_lane<B>(c, N, theta, cost, tape, g, status, lane);
+    extern __shared__ __align__(16) float lds[];
+    rollout_fwd_lane<B>(c, N, theta, cost, tape, g, status, lane, lds);
 }
 
 template <int B>
@@ -1261,7 +1301,8 @@ __global__ __launch_bounds__(kRolloutBlock) void k_rollout_adj(SimConst c, int N
                                                                float* __restrict__ grad, float* __restrict__ seg,
                                                                uint32_t* status) {
     const int64_t lane = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    rollout_adj_lane<B>(c, N, theta, tape, g, cost_bar, cb_scalar, grad, seg, status, lane);
+    extern __shared__ __align__(16) float lds[];
+    rollout_adj_lane<B>(c, N, theta, tape, g, cost_bar, cb_scalar, grad, seg, status, lane, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -1271,45 +1312,48 @@ __global__ __launch_bounds__(kRolloutBlock) void k_rollout_adj(SimConst c, int N
 // block count B of the problem selects the compiled body at run time.
 template <int B, bool PK>
 __device__ __forceinline__ void fwd_tile(const ProblemDesc& D, int i0, int l, const float* theta, float* cost,
-                                         float* tape, uint32_t* status) {
+                                         float* tape, uint32_t* status, float* lds) {
     const int64_t lane = (int64_t)(PK ? 4 : Slots<B>::LANES) * i0 + l;
     if constexpr (PK)
-        rollout_fwd_packed<B, 4>(D.c, D.N, theta + D.theta_off, cost + D.cost_off, tape ? tape + D.tape_off : nullptr,
-                              D.g, status, lane);
+        rollout_fwd_packed<B>(D.c, D.N, theta + D.theta_off, cost + D.cost_off, tape ? tape + D.tape_off : nullptr,
+                              D.g, status, lane, lds);
     else
         rollout_fwd_lane<B>(D.c, D.N, theta + D.theta_off, cost + D.cost_off, tape ? tape + D.tape_off : nullptr,
-                            D.g, status, lane);
+                            D.g, status, lane, lds);
 }
 
 template <int B, bool PK>
 __device__ __forceinline__ void adj_tile(const ProblemDesc& D, int i0, int l, const float* theta, const float* tape,
-                                         float cb_scalar, float* grad, float* seg, uint32_t* status) {
+                                         float cb_scalar, float* grad, float* seg, uint32_t* status, float* lds) {
     const int64_t lane = (int64_t)(PK ? 4 : Slots<B>::LANES) * i0 + l;
     if constexpr (PK)
         rollout_adj_packed<B>(D.c, D.N, theta + D.theta_off, tape + D.tape_off, D.g, nullptr, cb_scalar,
-                              grad + D.theta_off, seg + D.seg_off, status, lane);
+                              grad + D.theta_off, seg + D.seg_off, status, lane, lds);
     else
         rollout_adj_lane<B>(D.c, D.N, theta + D.theta_off, tape + D.tape_off, D.g, nullptr, cb_scalar,
-                            grad + D.theta_off, seg + D.seg_off, status, lane);
+                            grad + D.theta_off, seg + D.seg_off, status, lane, lds);
 }
 
 template <bool PK>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PK ? 2 : 4))) void k_rollout_fwd_batched(const ProblemDesc* __restrict__ descs,
                                                              const int2* __restrict__ tiles, int ntiles,
                                                              const float* __restrict__ theta, float* __restrict__ cost,
-                                                             float* __restrict__ tape, uint32_t* status) {
+                                                             float* __restrict__ tape, uint32_t* status,
+                                                             int wave_floats) {
     const int waves = blockDim.x >> 6;
     // the wave index is uniform across the wave: readfirstlane lets the tile,
     // its problem descriptor and the scene constants live in scalar registers
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    extern __shared__ __align__(16) float lds_all[];
+    float* lds = lds_all + wave * wave_floats;
     for (int t = blockIdx.x * waves + wave; t < ntiles; t += gridDim.x * waves) {
         const int2 tl = tiles[t];
         const ProblemDesc& D = descs[tl.x];
         switch (D.c.B) {
-            case 1: fwd_tile<1, PK>(D, tl.y, l, theta, cost, tape, status); break;
-            case 2: fwd_tile<2, PK>(D, tl.y, l, theta, cost, tape, status); break;
-            case 3: fwd_tile<3, PK>(D, tl.y, l, theta, cost, tape, status); break;
-            default: fwd_tile<4, PK>(D, tl.y, l, theta, cost, tape, status); break;
+            case 1: fwd_tile<1, PK>(D, tl.y, l, theta, cost, tape, status, lds); break;
+            case 2: fwd_tile<2, PK>(D, tl.y, l, theta, cost, tape, status, lds); break;
+            case 3: fwd_tile<3, PK>(D, tl.y, l, theta, cost, tape, status, lds); break;
+            default: fwd_tile<4, PK>(D, tl.y, l, theta, cost, tape, status, lds); break;
         }
     }
 }
@@ -1320,46 +1364,59 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PK ? 2 : 4)
                                                              const float* __restrict__ theta,
                                                              const float* __restrict__ tape, float cb_scalar,
                                                              float* __restrict__ grad, float* __restrict__ seg,
-                                                             uint32_t* status) {
+                                                             uint32_t* status, int wave_floats) {
     const int waves = blockDim.x >> 6;
     // the wave index is uniform across the wave: readfirstlane lets the tile,
     // its problem descriptor and the scene constants live in scalar registers
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    extern __shared__ __align__(16) float lds_all[];
+    float* lds = lds_all + wave * wave_floats;
     for (int t = blockIdx.x * waves + wave; t < ntiles; t += gridDim.x * waves) {
         const int2 tl = tiles[t];
         const ProblemDesc& D = descs[tl.x];
         switch (D.c.B) {
-            case 1: adj_tile<1, PK>(D, tl.y, l, theta, tape, cb_scalar, grad, seg, status); break;
-            case 2: adj_tile<2, PK>(D, tl.y, l, theta, tape, cb_scalar, grad, seg, status); break;
-            case 3: adj_tile<3, PK>(D, tl.y, l, theta, tape, cb_scalar, grad, seg, status); break;
-            default: adj_tile<4, PK>(D, tl.y, l, theta, tape, cb_scalar, grad, seg, status); break;
+            case 1: adj_tile<1, PK>(D, tl.y, l, theta, tape, cb_scalar, grad, seg, status, lds); break;
+            case 2: adj_tile<2, PK>(D, tl.y, l, theta, tape, cb_scalar, grad, seg, status, lds); break;
+            case 3: adj_tile<3, PK>(D, tl.y, l, theta, tape, cb_scalar, grad, seg, status, lds); break;
+            default: adj_tile<4, PK>(D, tl.y, l, theta, tape, cb_scalar, grad, seg, status, lds); break;
         }
     }
 }
 
 int rollout_tile_particles(int B, bool packed) { return packed ? 16 : 64 / (4 * (B == 1 ? 1 : (B == 2 ? 2 : 4))); }
 
+// LDS of one rollout wave (floats): the phase table, and the packed forward's
+// staging for B blocks (B = 0: none).  Sized at launch for the batch's largest
+// H and B, so that the waves a CU holds are bound by registers.
+static int rollout_lds_floats(int H, int B) { return H * kPhaseFloats + 64 * 6 * B; }
+
 hipError_t launch_rollout_fwd_batched(const ProblemDesc* descs, const int2* tiles, int ntiles, int block,
                                       int grid, const float* theta, float* cost, float* tape, uint32_t* status,
-                                      hipStream_t st, bool packed) {
+                                      hipStream_t st, bool packed, int max_H, int max_B) {
+    const int wf = rollout_lds_floats(max_H, packed ? max_B : 0);
     if (packed)
-        hipLaunchKernelGGL(k_rollout_fwd_batched<true>, dim3(grid), dim3(block), 0, st, descs, tiles, ntiles, theta,
-                           cost, tape, status);
+        hipLaunchKernelGGL(k_rollout_fwd_batched<true>, dim3(grid), dim3(block), (size_t)(block / 64) * wf * 4, st,
+                           descs, tiles, ntiles, theta,
+                           cost, tape, status, wf);
     else
-        hipLaunchKernelGGL(k_rollout_fwd_batched<false>, dim3(grid), dim3(block), 0, st, descs, tiles, ntiles, theta,
-                           cost, tape, status);
+        hipLaunchKernelGGL(k_rollout_fwd_batched<false>, dim3(grid), dim3(block), (size_t)(block / 64) * wf * 4, st,
+                           descs, tiles, ntiles, theta,
+                           cost, tape, status, wf);
     return hipGetLastError();
 }
 
 hipError_t launch_rollout_adj_batched(const ProblemDesc* descs, const int2* tiles, int ntiles, int block,
                                       int grid, const float* theta, const float* tape, float cb_scalar,
-                                      float* grad, float* seg, uint32_t* status, hipStream_t st, bool packed) {
+                                      float* grad, float* seg, uint32_t* status, hipStream_t st, bool packed, int max_H, int max_B) {
+    const int wf = rollout_lds_floats(max_H, 0);
     if (packed)
-        hipLaunchKernelGGL(k_rollout_adj_batched<true>, dim3(grid), dim3(block), 0, st, descs, tiles, ntiles, theta,
-                           tape, cb_scalar, grad, seg, status);
+        hipLaunchKernelGGL(k_rollout_adj_batched<true>, dim3(grid), dim3(block), (size_t)(block / 64) * wf * 4, st,
+                           descs, tiles, ntiles, theta,
+                           tape, cb_scalar, grad, seg, status, wf);
     else
-        hipLaunchKernelGGL(k_rollout_adj_batched<false>, dim3(grid), dim3(block), 0, st, descs, tiles, ntiles, theta,
-                           tape, cb_scalar, grad, seg, status);
+        hipLaunchKernelGGL(k_rollout_adj_batched<false>, dim3(grid), dim3(block), (size_t)(block / 64) * wf * 4, st,
+                           descs, tiles, ntiles, theta,
+                           tape, cb_scalar, grad, seg, status, wf);
     return hipGetLastError();
 }
 
@@ -1372,10 +1429,10 @@ static hipError_t launch_fwd_b(const SimConst& c, int N, const float* theta, flo
     const int64_t lanes = (int64_t)(pk ? 4 : Slots<B>::LANES) * N;
     const unsigned grid = (unsigned)((lanes + kRolloutBlock - 1) / kRolloutBlock);
     if (pk)
-        hipLaunchKernelGGL(k_rollout_fwd_packed<B>, dim3(grid), dim3(kRolloutBlock), 0, st, c, N, theta, cost, tape,
+        hipLaunchKernelGGL(k_rollout_fwd_packed<B>, dim3(grid), dim3(kRolloutBlock), rollout_lds_floats(c.H, B) * 4, st, c, N, theta, cost, tape,
                            g, status);
     else
-        hipLaunchKernelGGL(k_rollout_fwd<B>, dim3(grid), dim3(kRolloutBlock), 0, st, c, N, theta, cost, tape, g,
+        hipLaunchKernelGGL(k_rollout_fwd<B>, dim3(grid), dim3(kRolloutBlock), rollout_lds_floats(c.H, 0) * 4, st, c, N, theta, cost, tape, g,
                            status);
     return hipGetLastError();
 }
@@ -1388,10 +1445,10 @@ static hipError_t launch_adj_b(const SimConst& c, int N, const float* theta, con
     const int64_t lanes = (int64_t)(pk ? 4 : Slots<B>::LANES) * N;
     const unsigned grid = (unsigned)((lanes + kRolloutBlock - 1) / kRolloutBlock);
     if (pk)
-        hipLaunchKernelGGL(k_rollout_adj_packed<B>, dim3(grid), dim3(kRolloutBlock), 0, st, c, N, theta, tape, g,
+        hipLaunchKernelGGL(k_rollout_adj_packed<B>, dim3(grid), dim3(kRolloutBlock), rollout_lds_floats(c.H, 0) * 4, st, c, N, theta, tape, g,
                            cost_bar, cb_scalar, grad, seg, status);
     else
-        hipLaunchKernelGGL(k_rollout_adj<B>, dim3(grid), dim3(kRolloutBlock), 0, st, c, N, theta, tape, g, cost_bar,
+        hipLaunchKernelGGL(k_rollout_adj<B>, dim3(grid), dim3(kRolloutBlock), rollout_lds_floats(c.H, 0) * 4, st, c, N, theta, tape, g, cost_bar,
                            cb_scalar, grad, seg, status);
     return hipGetLastError();
 }
