@@ -284,7 +284,6 @@ __device__ __forceinline__ BlkConst<B> blk_const(const SimConst& c, int b) {
 template <int B>
 __device__ __forceinline__ void step_forward(const SimConst& c, const BlkConst<B>& k, int b, Blk& X, const Push& p,
                                              float sig) {
-    constexpr int SL = Slots<B>::SL;
     constexpr int NO = B - 1;
     float ox[NO > 0 ? NO : 1], oy[NO > 0 ? NO : 1];
 #pragma unroll
@@ -334,14 +333,79 @@ __device__ __forceinline__ void step_forward(const SimConst& c, const BlkConst<B
     X.ph = fmaf(c.dt, X.om, X.ph);
 }
 
-// Reverse of step_forward at pre-step state X of block b.  On entry L is the
-// adjoint of the block's post-step state; on exit that of its pre-step state.
-// Adjoints of the phase's pusher data (P0, V) are accumulated on block 0.
+// The reverse of step_forward splits in two: what depends on the pre-step
+// state X alone (linearise: the trigonometry, the contacts' forces and their
+// derivatives) and the adjoint's own recursion (step_adjoint: products of
+// these with the adjoint).  Only the second is a serial chain over the steps,
+// so another wave may compute the first ahead of it.
+// The values, in order: pusher relx rely ex ey s0 c0 cross f spg; friction vx
+// vy kf q w; per other block dx dy rinv fr fs.
 template <int B>
-__device__ __forceinline__ void step_reverse(const SimConst& c, const BlkConst<B>& k, int b, const Blk& X, Blk& L,
+struct Lin {
+    static constexpr int N = 14 + 5 * (B - 1);
+    static constexpr int N4 = (N + 3) / 4;
+    float v[4 * N4];
+};
+
+template <int B>
+__device__ __forceinline__ void linearise(const SimConst& c, const BlkConst<B>& k, const Blk& X, const Push& p,
+                                          float sig, Lin<B>& t) {
+    constexpr int NO = B - 1;
+    {
+        const float relx = fmaf(sig, p.Vx, p.P0x) - X.x;
+        const float rely = fmaf(sig, p.Vy, p.P0y) - X.y;
+        float s0, c0;
+        sincos_rd(X.ph, s0, c0);
+        const float ex = fmaf(c0, p.nx, -(s0 * p.ny)), ey = fmaf(s0, p.nx, c0 * p.ny);
+        const float pen = c.h0 - fmaf(ex, relx, ey * rely);
+        const float u = softplus_u(pen, c.beta_log2e);
+        const float rr = hw_rcp(1.0f + u);
+        t.v[0] = relx;
+        t.v[1] = rely;
+        t.v[2] = ex;
+        t.v[3] = ey;
+        t.v[4] = s0;
+        t.v[5] = c0;
+        t.v[6] = fmaf(relx, ey, -(rely * ex));                                             // cross
+        t.v[7] = c.kp * fmaf(hw_log2(1.0f + u), c.ln2_over_beta, fmaxf(pen, 0.0f));  // f
+        t.v[8] = pen >= 0.0f ? rr : u * rr;                                                // sp'(pen)
+    }
+    {
+        const float inv = hw_rsq(fmaf(X.vx, X.vx, fmaf(X.vy, X.vy, k.ev2)));
+        const float kf = k.cf * inv;
+        const float invw = hw_rsq(fmaf(X.om, X.om, k.ew2));
+        t.v[9] = X.vx;
+        t.v[10] = X.vy;
+        t.v[11] = kf;
+        t.v[12] = kf * inv * inv;
+        t.v[13] = -(k.crw2 * (invw * invw * invw));
+    }
+#pragma unroll
+    for (int K = 0; K < NO; ++K) {
+        const float dx = X.x - from_other<B>(X.x, K), dy = X.y - from_other<B>(X.y, K);
+        const float d2 = fmaf(dx, dx, fmaf(dy, dy, c.er2));
+        const float rinv = hw_rsq(d2);
+        const float pen = fmaf(-d2, rinv, k.hs[K]);
+        const float u = softplus_u(pen, c.beta_log2e);
+        const float fr = c.kb * fmaf(hw_log2(1.0f + u), c.ln2_over_beta, fmaxf(pen, 0.0f)) * rinv;
+        const float rr = hw_rcp(1.0f + u);
+        const float fp = c.kb * (pen >= 0.0f ? rr : u * rr);  // f'(pen)
+        float* q = t.v + 14 + 5 * K;
+        q[0] = dx;
+        q[1] = dy;
+        q[2] = rinv;
+        q[3] = fr;
+        q[4] = fr + fp;
+    }
+}
+
+// On entry L is the adjoint of the block's post-step state; on exit that of
+// its pre-step state.  Adjoints of the phase's pusher data (P0, V) are
+// accumulated on block 0.
+template <int B>
+__device__ __forceinline__ void step_adjoint(const SimConst& c, const BlkConst<B>& k, int b, const Lin<B>& t, Blk& L,
                                              const Push& p, float sig, float& P0xb, float& P0yb, float& Vxb,
                                              float& Vyb) {
-    constexpr int SL = Slots<B>::SL;
     constexpr int NO = B - 1;
     // integrator: x' = x + dt v', v' = v + (dt/m) F
     L.vx = fmaf(c.dt, L.x, L.vx);
@@ -350,27 +414,16 @@ __device__ __forceinline__ void step_reverse(const SimConst& c, const BlkConst<B
     const float Fxb = k.dtm * L.vx;
     const float Fyb = k.dtm * L.vy;
     const float Tqb = k.dtI * L.om;
-    float ox[NO > 0 ? NO : 1], oy[NO > 0 ? NO : 1], ofx[NO > 0 ? NO : 1], ofy[NO > 0 ? NO : 1];
+    float ofx[NO > 0 ? NO : 1], ofy[NO > 0 ? NO : 1];
 #pragma unroll
     for (int K = 0; K < NO; ++K) {
-        ox[K] = from_other<B>(X.x, K);
-        oy[K] = from_other<B>(X.y, K);
         ofx[K] = from_other<B>(Fxb, K);
         ofy[K] = from_other<B>(Fyb, K);
     }
     // pusher
     {
-        const float relx = fmaf(sig, p.Vx, p.P0x) - X.x;
-        const float rely = fmaf(sig, p.Vy, p.P0y) - X.y;
-        float s0, c0;
-        sincos_rd(X.ph, s0, c0);
-        const float ex = fmaf(c0, p.nx, -(s0 * p.ny)), ey = fmaf(s0, p.nx, c0 * p.ny);
-        const float cross = fmaf(relx, ey, -(rely * ex));
-        const float pen = c.h0 - fmaf(ex, relx, ey * rely);
-        const float u = softplus_u(pen, c.beta_log2e);
-        const float f = c.kp * fmaf(hw_log2(1.0f + u), c.ln2_over_beta, fmaxf(pen, 0.0f));
-        const float rr = hw_rcp(1.0f + u);
-        const float spg = pen >= 0.0f ? rr : u * rr;  // sp'(pen)
+        const float relx = t.v[0], rely = t.v[1], ex = t.v[2], ey = t.v[3], s0 = t.v[4], c0 = t.v[5];
+        const float cross = t.v[6], f = t.v[7], spg = t.v[8];
         // F0 += -f e, T0 += -f cross
         const float fb = -fmaf(cross, Tqb, fmaf(ex, Fxb, ey * Fyb));
         const float crossb = -f * Tqb;
@@ -397,29 +450,30 @@ __device__ __forceinline__ void step_reverse(const SimConst& c, const BlkConst<B
     // block-block contacts: F_b += f u with u = Delta / r, Delta = x_b - x_q
 #pragma unroll
     for (int K = 0; K < NO; ++K) {
-        const float dx = X.x - ox[K], dy = X.y - oy[K];
-        const float d2 = fmaf(dx, dx, fmaf(dy, dy, c.er2));
-        const float rinv = hw_rsq(d2);
-        const float pen = fmaf(-d2, rinv, k.hs[K]);
-        const float u = softplus_u(pen, c.beta_log2e);
-        const float fr = c.kb * fmaf(hw_log2(1.0f + u), c.ln2_over_beta, fmaxf(pen, 0.0f)) * rinv;
-        const float rr = hw_rcp(1.0f + u);
-        const float fp = c.kb * (pen >= 0.0f ? rr : u * rr);  // f'(pen)
+        const float* q = t.v + 14 + 5 * K;
+        const float dx = q[0], dy = q[1], rinv = q[2], fr = q[3];
         const float gx = Fxb - ofx[K], gy = Fyb - ofy[K];
         const float gu = fmaf(gx, dx, gy * dy) * rinv;  // adjoint of f
         // d(f u)/dDelta = f/r (I - u u^T) + f'(pen)(-u) u^T
-        const float k2 = (fr + fp) * gu * rinv;  // coefficient of Delta
+        const float k2 = q[4] * gu * rinv;  // coefficient of Delta
         L.x += fmaf(fr, gx, -(k2 * dx));
         L.y += fmaf(fr, gy, -(k2 * dy));
     }
     // friction
-    const float inv = hw_rsq(fmaf(X.vx, X.vx, fmaf(X.vy, X.vy, k.ev2)));
-    const float kf = k.cf * inv;
-    const float kd = kf * inv * inv * fmaf(Fxb, X.vx, Fyb * X.vy);
-    L.vx = fmaf(kd, X.vx, fmaf(-kf, Fxb, L.vx));
-    L.vy = fmaf(kd, X.vy, fmaf(-kf, Fyb, L.vy));
-    const float invw = hw_rsq(fmaf(X.om, X.om, k.ew2));
-    L.om = fmaf(-(k.crw2 * (invw * invw * invw)), Tqb, L.om);
+    const float vx = t.v[9], vy = t.v[10], kf = t.v[11];
+    const float kd = t.v[12] * fmaf(Fxb, vx, Fyb * vy);
+    L.vx = fmaf(kd, vx, fmaf(-kf, Fxb, L.vx));
+    L.vy = fmaf(kd, vy, fmaf(-kf, Fyb, L.vy));
+    L.om = fmaf(t.v[13], Tqb, L.om);
+}
+
+template <int B>
+__device__ __forceinline__ void step_reverse(const SimConst& c, const BlkConst<B>& k, int b, const Blk& X, Blk& L,
+                                             const Push& p, float sig, float& P0xb, float& P0yb, float& Vxb,
+                                             float& Vyb) {
+    Lin<B> t;
+    linearise<B>(c, k, X, p, sig, t);
+    step_adjoint<B>(c, k, b, t, L, p, sig, P0xb, P0yb, Vxb, Vyb);
 }
 
 __device__ __forceinline__ void side_frame(int s, Push& p) {
@@ -554,111 +608,163 @@ __device__ __forceinline__ void rollout_fwd_lane(const SimConst& c, int N, const
 }
 
 // ---------------------------------------------------------------------------
-// Reverse sweep of one lane; cost_bar (or cb_scalar when null) scales dC/dtheta.
-template <int B>
-__device__ __forceinline__ void rollout_adj_lane(const SimConst& c, int N, const float* __restrict__ theta,
-                                                 const float* __restrict__ tape, const TapeGeom& g,
-                                                 const float* __restrict__ cost_bar, float cb_scalar,
-                                                 float* __restrict__ grad, float* __restrict__ seg,
-                                                 uint32_t* status, int64_t lane, float* tab) {
-    constexpr int SL = Slots<B>::SL;
-    const int64_t iw = lane / (4 * SL);
-    const bool live = iw < N;  // lanes past the last particle repeat particle N-1, write nothing
-    const int i = live ? (int)iw : N - 1;
-    const int r = (int)(lane % (4 * SL));
-    const int s = r / SL, b = min(r % SL, B - 1);
-    const bool blk = r % SL < B;  // a block slot (an idle one duplicates block B - 1)
-    const int64_t slot = ((int64_t)4 * i + s) * B + b;
-    const int64_t slot0 = ((int64_t)4 * i + s) * B;  // block 0 of this sub-rollout
-    const uint32_t off = (uint32_t)(slot * 6);
-    const int H = c.H, T = c.T;
-    const int64_t stride = 6 * B * g.lanes;  // floats per tape entry
-    const BlkConst<B> k = blk_const<B>(c, b);
-    const int lw = (int)(lane & 63);
-    phase_table(theta, N, i, s, H, tab, lw);
+// A wave's LDS table in the reverse sweep: the phase inputs [H][3][64]
+// (phase_table), then the cost's adjoints of the phase starts [H][2][64].
+constexpr int kSeedFloats = 2 * 64;
+__host__ __device__ constexpr int adj_table_floats(int H) { return H * (kPhaseFloats + kSeedFloats); }
 
-    // entry index of each phase start
-    int ent[kMaxPushes];
+// dC/dP_k of the phase-start positions (times cost_bar) into the table, and
+// the adjoint of the final block-0 pose in xb, yb, phb.  pos(k): P_k.
+template <class F>
+__device__ __forceinline__ void cost_seeds(const SimConst& c, int H, float cb, F&& pos, float PHx, float PHy, float phT,
+                                           float* seeds, int lw, float& xb, float& yb, float& phb) {
+    float Px[kMaxPushes], Py[kMaxPushes], Pxb[kMaxPushes], Pyb[kMaxPushes];
+#pragma unroll
+    for (int k = 0; k < kMaxPushes; ++k) {
+        Pxb[k] = Pyb[k] = 0.0f;
+        if (k < H) pos(k, Px[k], Py[k]);
+    }
+    xb = yb = 0.0f;
     {
-        int e = 0;
-        for (int kk = 0; kk < H; ++kk) {
-            const int tk = phase_start(kk, T, H), tk1 = phase_start(kk + 1, T, H);
-            ent[kk] = (g.ckpt == 0) ? tk : e;
-            if (g.ckpt) e += (tk1 - tk + g.ckpt - 1) / g.ckpt;
-        }
+        const float ux = PHx - c.goal[0], uy = PHy - c.goal[1];
+        xb += cb * c.wt * 2.0f * relu(fabsf(ux) - c.tol) * copysignf(1.0f, ux);
+        yb += cb * c.wt * 2.0f * relu(fabsf(uy) - c.tol) * copysignf(1.0f, uy);
     }
-    // phase-start positions P_k and the final block-0 pose
-    float Px[kMaxPushes + 1], Py[kMaxPushes + 1];
-    for (int kk = 0; kk < H; ++kk) {
-        Px[kk] = tape[ent[kk] * stride + slot0 * 6 + 0];
-        Py[kk] = tape[ent[kk] * stride + slot0 * 6 + 1];
-    }
-    float phT;
-    {
-        const float z = tab[(H - 1) * kPhaseFloats + lw];
-        const float* e = tape + g.ends_off + (int64_t)(H - 1) * stride + slot0 * 6;
-        Px[H] = side_sum<SL>(z * e[0]);
-        Py[H] = side_sum<SL>(z * e[1]);
-        phT = side_sum<SL>(z * e[2]);
-    }
-    const float cb = cost_bar ? cost_bar[i] : cb_scalar;
-
-    // dC/dP_k and dC/dphi_T, scaled by cost_bar
-    float Pxb[kMaxPushes + 1], Pyb[kMaxPushes + 1];
-    for (int kk = 0; kk <= H; ++kk) Pxb[kk] = Pyb[kk] = 0.0f;
-    {
-        const float ux = Px[H] - c.goal[0], uy = Py[H] - c.goal[1];
-        Pxb[H] += cb * c.wt * 2.0f * relu(fabsf(ux) - c.tol) * copysignf(1.0f, ux);
-        Pyb[H] += cb * c.wt * 2.0f * relu(fabsf(uy) - c.tol) * copysignf(1.0f, uy);
-    }
-    const float phTb = cb * c.wr * sinf(phT - c.goal[2]);
+    phb = cb * c.wr * sinf(phT - c.goal[2]);
     const float wtr = cb * c.wtr;
     if (!c.per_phase) {
-        for (int kk = 1; kk <= H; ++kk) {
+#pragma unroll
+        for (int k = 1; k <= kMaxPushes; ++k) {
             float u, dd;
-            u = Px[kk - 1] - Px[kk];  dd = wtr * u / smooth_abs(u, c.ea2);  Pxb[kk - 1] += dd; Pxb[kk] -= dd;
-            u = Py[kk - 1] - Py[kk];  dd = wtr * u / smooth_abs(u, c.ea2);  Pyb[kk - 1] += dd; Pyb[kk] -= dd;
-            u = Px[kk] - Px[H];       dd = wtr * u / smooth_abs(u, c.ea2);  Pxb[kk] += dd;     Pxb[H] -= dd;
-            u = Py[kk] - Py[H];       dd = wtr * u / smooth_abs(u, c.ea2);  Pyb[kk] += dd;     Pyb[H] -= dd;
-            u = Px[kk - 1] - Px[H];   dd = wtr * u / smooth_abs(u, c.ea2);  Pxb[kk - 1] -= dd; Pxb[H] += dd;
-            u = Py[kk - 1] - Py[H];   dd = wtr * u / smooth_abs(u, c.ea2);  Pyb[kk - 1] -= dd; Pyb[H] += dd;
+            if (k < H) {
+                u = Px[k - 1] - Px[k];  dd = wtr * u / smooth_abs(u, c.ea2);  Pxb[k - 1] += dd;  Pxb[k] -= dd;
+                u = Py[k - 1] - Py[k];  dd = wtr * u / smooth_abs(u, c.ea2);  Pyb[k - 1] += dd;  Pyb[k] -= dd;
+                u = Px[k] - PHx;        dd = wtr * u / smooth_abs(u, c.ea2);  Pxb[k] += dd;      xb -= dd;
+                u = Py[k] - PHy;        dd = wtr * u / smooth_abs(u, c.ea2);  Pyb[k] += dd;      yb -= dd;
+                u = Px[k - 1] - PHx;    dd = wtr * u / smooth_abs(u, c.ea2);  Pxb[k - 1] -= dd;  xb += dd;
+                u = Py[k - 1] - PHy;    dd = wtr * u / smooth_abs(u, c.ea2);  Pyb[k - 1] -= dd;  yb += dd;
+            } else if (k == H) {  // P_k is P_H itself: its own term MH(P_H, P_H) has no gradient
+                u = Px[k - 1] - PHx;    dd = wtr * u / smooth_abs(u, c.ea2);  Pxb[k - 1] += dd;  xb -= dd;
+                u = Py[k - 1] - PHy;    dd = wtr * u / smooth_abs(u, c.ea2);  Pyb[k - 1] += dd;  yb -= dd;
+                u = PHx - PHx;          dd = wtr * u / smooth_abs(u, c.ea2);  xb += dd;          xb -= dd;
+                u = PHy - PHy;          dd = wtr * u / smooth_abs(u, c.ea2);  yb += dd;          yb -= dd;
+                u = Px[k - 1] - PHx;    dd = wtr * u / smooth_abs(u, c.ea2);  Pxb[k - 1] -= dd;  xb += dd;
+                u = Py[k - 1] - PHy;    dd = wtr * u / smooth_abs(u, c.ea2);  Pyb[k - 1] -= dd;  yb += dd;
+            }
         }
     } else {
-        // Per-phase split: term kk of L_traj is phase kk-1's and reaches only
-        // that phase's end P_kk (its start P_{kk-1} and the final P_H are other
+        // Per-phase split: term k of L_traj is phase k-1's and reaches only
+        // that phase's end P_k (its start P_{k-1} and the final P_H are other
         // phases' constants); the last term, MH(P_H, P_H) = 2 eps_a, has no
         // gradient.  The target and rotation terms stay on the last phase.
-        for (int kk = 1; kk < H; ++kk) {
-            float u, dd;
-            u = Px[kk - 1] - Px[kk];  dd = wtr * u / smooth_abs(u, c.ea2);  Pxb[kk] -= dd;
-            u = Py[kk - 1] - Py[kk];  dd = wtr * u / smooth_abs(u, c.ea2);  Pyb[kk] -= dd;
-            u = Px[kk] - Px[H];       dd = wtr * u / smooth_abs(u, c.ea2);  Pxb[kk] += dd;
-            u = Py[kk] - Py[H];       dd = wtr * u / smooth_abs(u, c.ea2);  Pyb[kk] += dd;
+#pragma unroll
+        for (int k = 1; k < kMaxPushes; ++k) {
+            if (k < H) {
+                float u, dd;
+                u = Px[k - 1] - Px[k];  dd = wtr * u / smooth_abs(u, c.ea2);  Pxb[k] -= dd;
+                u = Py[k - 1] - Py[k];  dd = wtr * u / smooth_abs(u, c.ea2);  Pyb[k] -= dd;
+                u = Px[k] - PHx;        dd = wtr * u / smooth_abs(u, c.ea2);  Pxb[k] += dd;
+                u = Py[k] - PHy;        dd = wtr * u / smooth_abs(u, c.ea2);  Pyb[k] += dd;
+            }
         }
     }
+#pragma unroll
+    for (int k = 0; k < kMaxPushes; ++k)
+        if (k < H) {
+            seeds[k * kSeedFloats + lw] = Pxb[k];
+            seeds[k * kSeedFloats + 64 + lw] = Pyb[k];
+        }
+}
 
+// Checkpoints of phase k (K > 0), and the tape entry its states start at.
+__device__ __forceinline__ int phase_segments(int k, int T, int H, int K) {
+    return (phase_start(k + 1, T, H) - phase_start(k, T, H) + K - 1) / K;
+}
+__device__ __forceinline__ int phase_entry(const TapeGeom& g, int k, int T, int H) {
+    if (g.ckpt == 0) return phase_start(k, T, H);
+    int e = 0;
+    for (int q = 0; q < k; ++q) e += phase_segments(q, T, H, g.ckpt);
+    return e;
+}
+
+// One lane of the block-per-lane layout in the reverse sweep.
+template <int B>
+struct AdjLane {
+    int i, s, b, lw;
+    bool live;  // lanes past the last particle repeat particle N-1, write nothing
+    bool blk;   // a block slot (an idle one duplicates block B - 1)
+    int64_t slot0, stride;
+    uint32_t off;
+    __device__ __forceinline__ AdjLane(int N, int64_t lane, const TapeGeom& g) {
+        constexpr int SL = Slots<B>::SL;
+        const int64_t iw = lane / (4 * SL);
+        live = iw < N;
+        i = live ? (int)iw : N - 1;
+        const int r = (int)(lane % (4 * SL));
+        s = r / SL;
+        b = min(r % SL, B - 1);
+        blk = r % SL < B;
+        lw = (int)(lane & 63);
+        slot0 = ((int64_t)4 * i + s) * B;
+        off = (uint32_t)((slot0 + b) * 6);
+        stride = 6 * B * g.lanes;  // floats per tape entry
+    }
+};
+
+// Reverse sweep of one lane; cost_bar (or cb_scalar when null) scales dC/dtheta.
+// rev(k, entry, p, L, P0xb, P0yb, Vxb, Vyb) takes the adjoint L back through
+// the steps of phase k, whose first tape entry is `entry`.  The phase's end
+// states and anchor are read a phase ahead.
+template <int B, class F>
+__device__ __forceinline__ void reverse_sweep(const SimConst& c, int N, const AdjLane<B>& a,
+                                              const float* __restrict__ tape, const TapeGeom& g,
+                                              const float* __restrict__ cost_bar, float cb_scalar,
+                                              float* __restrict__ grad, uint32_t* status, float* tab, F&& rev) {
+    constexpr int SL = Slots<B>::SL;
+    const int H = c.H, T = c.T, i = a.i, s = a.s, b = a.b, lw = a.lw;
+    const int64_t stride = a.stride;
+    float* seeds = tab + H * kPhaseFloats;
+    int entry = phase_entry(g, H - 1, T, H);
+    Blk Xe, A;  // the phase's end states and its start (block 0's pose: the anchor, on slot 0)
+    load_blk_at(Xe, tape + g.ends_off + (int64_t)(H - 1) * stride, a.off);
+    load_blk_at(A, tape + (int64_t)entry * stride, a.off);
+    const float cb = cost_bar ? cost_bar[i] : cb_scalar;
+    float PHx, PHy, phT;
+    {
+        const float z = tab[(H - 1) * kPhaseFloats + lw];
+        const float* e = tape + g.ends_off + (int64_t)(H - 1) * stride + a.slot0 * 6;
+        PHx = side_sum<SL>(z * e[0]);
+        PHy = side_sum<SL>(z * e[1]);
+        phT = side_sum<SL>(z * e[2]);
+    }
     // adjoint of S_H (block 0 carries the cost's terms)
+    float xb, yb, phb;
+    cost_seeds(
+        c, H, cb,
+        [&](int k, float& x, float& y) {
+            const float* e = tape + (int64_t)phase_entry(g, k, T, H) * stride + a.slot0 * 6;
+            x = e[0];
+            y = e[1];
+        },
+        PHx, PHy, phT, seeds, lw, xb, yb, phb);
     Blk Ls;
     Ls.x = Ls.y = Ls.ph = Ls.vx = Ls.vy = Ls.om = 0.0f;
     if (b == 0) {
-        Ls.x = Pxb[H];
-        Ls.y = Pyb[H];
-        Ls.ph = phTb;
+        Ls.x = xb;
+        Ls.y = yb;
+        Ls.ph = phb;
     }
 
     Push p;
     side_frame(s, p);
     bool bad = false;
     for (int kk = H - 1; kk >= 0; --kk) {
-        const int tk = phase_start(kk, T, H), tk1 = phase_start(kk + 1, T, H);
-        const float invL = 1.0f / (float)(tk1 - tk);
         const float* pt = tab + kk * kPhaseFloats + lw;
         const float z = pt[0], o = pt[64], D = pt[128];
         // phase end: S_{k+1} = sum_s z_s X_s
-        Blk Xe, L;
-        load_blk_at(Xe, tape + g.ends_off + (int64_t)kk * stride, off);
+        Blk L;
         const float zp = Ls.x * Xe.x + Ls.y * Xe.y + Ls.ph * Xe.ph + Ls.vx * Xe.vx + Ls.vy * Xe.vy + Ls.om * Xe.om;
-        const float zb = slot_sum<SL>(blk ? zp : 0.0f);
+        const float zb = slot_sum<SL>(a.blk ? zp : 0.0f);
         L.x = z * Ls.x;
         L.y = z * Ls.y;
         L.ph = z * Ls.ph;
@@ -666,51 +772,17 @@ __device__ __forceinline__ void rollout_adj_lane(const SimConst& c, int N, const
         L.vy = z * Ls.vy;
         L.om = z * Ls.om;
         const float ab = z * (zb - side_sum<SL>(z * zb));  // softmax VJP
-        // anchor of the phase (block 0's pose, on slot 0)
-        Blk A;
-        load_blk_at(A, tape + ent[kk] * stride, off);
         Anchor an;
         phase_push(c, A.x, A.y, A.ph, o, D, p, an);
-        float P0xb = 0.0f, P0yb = 0.0f, Vxb = 0.0f, Vyb = 0.0f;
-        Profile prof;
-        prof.reset(invL);
-        if (g.ckpt == 0) {
-            // reverse sweep over the full tape; the states of the next two
-            // (earlier) steps are in flight while a step is reversed.  The
-            // loads are unconditional (indices clamped at entry 0, whose
-            // extra copies go unused): with a load on some paths only, the
-            // compiler waits for every load in flight at the loop head.
-            const float* base = tape + (int64_t)tk * stride;  // step j's entry: base + j stride
-            int j = tk1 - tk - 1;
-            Blk XA, XB;
-            load_blk_at(XA, base + (int64_t)j * stride, off);
-            load_blk_at(XB, base + (int64_t)max(j - 1, 0) * stride, off);
-            for (; j >= 1; j -= 2) {
-                Blk X = XA;
-                load_blk_at(XA, base + (int64_t)max(j - 2, 0) * stride, off);
-                step_reverse<B>(c, k, b, X, L, p, prof.at(j), P0xb, P0yb, Vxb, Vyb);
-                X = XB;
-                load_blk_at(XB, base + (int64_t)max(j - 3, 0) * stride, off);
-                step_reverse<B>(c, k, b, X, L, p, prof.at(j - 1), P0xb, P0yb, Vxb, Vyb);
-            }
-            if (j == 0) step_reverse<B>(c, k, b, XA, L, p, prof.at(0), P0xb, P0yb, Vxb, Vyb);
-        } else {
-            const int nseg = (tk1 - tk + g.ckpt - 1) / g.ckpt;
-            for (int q = nseg - 1; q >= 0; --q) {
-                const int js = q * g.ckpt;
-                const int je = min(js + g.ckpt, tk1 - tk);
-                Blk X;
-                load_blk_at(X, tape + (int64_t)(ent[kk] + q) * stride, off);
-                for (int j = js; j < je; ++j) {  // replay the segment
-                    store_blk_at(X, seg + (int64_t)(j - js) * stride, off);
-                    step_forward<B>(c, k, b, X, p, prof.at(j));
-                }
-                for (int j = je - 1; j >= js; --j) {
-                    load_blk_at(X, seg + (int64_t)(j - js) * stride, off);  // a lane reads its own writes
-                    step_reverse<B>(c, k, b, X, L, p, prof.at(j), P0xb, P0yb, Vxb, Vyb);
-                }
-            }
+        const int here = entry;
+        if (kk > 0) {
+            entry -= g.ckpt == 0 ? phase_start(kk, T, H) - phase_start(kk - 1, T, H)
+                                 : phase_segments(kk - 1, T, H, g.ckpt);
+            load_blk_at(Xe, tape + g.ends_off + (int64_t)(kk - 1) * stride, a.off);
+            load_blk_at(A, tape + (int64_t)entry * stride, a.off);
         }
+        float P0xb = 0.0f, P0yb = 0.0f, Vxb = 0.0f, Vyb = 0.0f;
+        rev(kk, here, p, L, P0xb, P0yb, Vxb, Vyb);
         // back to the anchor and (o, D): P0 = A + R(A) q0, q0 = (h0 + standoff) n + o t,
         // V = -D e_A, e_A = R(A) n (meaningful on slot 0, zero elsewhere)
         const float eAx = fmaf(an.cA, p.nx, -(an.sA * p.ny)), eAy = fmaf(an.sA, p.nx, an.cA * p.ny);
@@ -736,19 +808,20 @@ __device__ __forceinline__ void rollout_adj_lane(const SimConst& c, int N, const
             Ls.x = Ls.y = Ls.ph = Ls.vx = Ls.vy = Ls.om = 0.0f;
         }
         if (b == 0) {
+            const float Pxb = seeds[kk * kSeedFloats + lw], Pyb = seeds[kk * kSeedFloats + 64 + lw];
             if (c.per_phase) {
-                Ls.x = Pxb[kk];
-                Ls.y = Pyb[kk];
+                Ls.x = Pxb;
+                Ls.y = Pyb;
             } else {
-                Ls.x += Axs + Pxb[kk];
-                Ls.y += Ays + Pyb[kk];
+                Ls.x += Axs + Pxb;
+                Ls.y += Ays + Pyb;
                 Ls.ph += Aphs;
             }
             // bound loss on o_k, D_k
             const float wb2 = 2.0f * cb * c.wb;
             const float obt = obs + wb2 * relu(fabsf(o) - c.omax) * copysignf(1.0f, o);
             const float Dbt = Dbs + wb2 * (relu(D - c.dmax) - relu(-D));
-            if (live) {
+            if (a.live) {
                 grad[(int64_t)(6 * kk + s) * N + i] = ab;
                 if (s == 0) grad[(int64_t)(6 * kk + 4) * N + i] = obt;
                 if (s == 1) grad[(int64_t)(6 * kk + 5) * N + i] = Dbt;
@@ -757,6 +830,440 @@ __device__ __forceinline__ void rollout_adj_lane(const SimConst& c, int N, const
         }
     }
     if (status && bad) atomicOr(status, STAMP_STATUS_NONFINITE_GRAD);
+}
+
+// The reverse sweep with each wave doing its own steps: the batched kernel's,
+// and the per-call one's where the split below does not pay.
+template <int B>
+__device__ __forceinline__ void rollout_adj_lane(const SimConst& c, int N, const float* __restrict__ theta,
+                                                 const float* __restrict__ tape, const TapeGeom& g,
+                                                 const float* __restrict__ cost_bar, float cb_scalar,
+                                                 float* __restrict__ grad, float* __restrict__ seg,
+                                                 uint32_t* status, int64_t lane, float* tab) {
+    const AdjLane<B> a(N, lane, g);
+    const BlkConst<B> k = blk_const<B>(c, a.b);
+    const int H = c.H, T = c.T, b = a.b;
+    const int64_t stride = a.stride;
+    const uint32_t off = a.off;
+    phase_table(theta, N, a.i, a.s, H, tab, a.lw);
+    auto rev = [&](int kk, int entry, const Push& p, Blk& L, float& P0xb, float& P0yb, float& Vxb, float& Vyb) {
+        const int nst = phase_start(kk + 1, T, H) - phase_start(kk, T, H);
+        Profile prof;
+        prof.reset(1.0f / (float)nst);
+        if (g.ckpt == 0) {
+            // reverse sweep over the full tape; the states of the next two
+            // (earlier) steps are in flight while a step is reversed.  The
+            // loads are unconditional (indices clamped at entry 0, whose
+            // extra copies go unused): with a load on some paths only, the
+            // compiler waits for every load in flight at the loop head.
+            const float* base = tape + (int64_t)entry * stride;  // step j's entry: base + j stride
+            int j = nst - 1;
+            Blk XA, XB;
+            load_blk_at(XA, base + (int64_t)j * stride, off);
+            load_blk_at(XB, base + (int64_t)max(j - 1, 0) * stride, off);
+            for (; j >= 1; j -= 2) {
+                Blk X = XA;
+                load_blk_at(XA, base + (int64_t)max(j - 2, 0) * stride, off);
+                step_reverse<B>(c, k, b, X, L, p, prof.at(j), P0xb, P0yb, Vxb, Vyb);
+                X = XB;
+                load_blk_at(XB, base + (int64_t)max(j - 3, 0) * stride, off);
+                step_reverse<B>(c, k, b, X, L, p, prof.at(j - 1), P0xb, P0yb, Vxb, Vyb);
+            }
+            if (j == 0) step_reverse<B>(c, k, b, XA, L, p, prof.at(0), P0xb, P0yb, Vxb, Vyb);
+        } else {
+            for (int q = (nst + g.ckpt - 1) / g.ckpt - 1; q >= 0; --q) {
+                const int js = q * g.ckpt;
+                const int je = min(js + g.ckpt, nst);
+                Blk X;
+                load_blk_at(X, tape + (int64_t)(entry + q) * stride, off);
+                for (int j = js; j < je; ++j) {  // replay the segment
+                    store_blk_at(X, seg + (int64_t)(j - js) * stride, off);
+                    step_forward<B>(c, k, b, X, p, prof.at(j));
+                }
+                for (int j = je - 1; j >= js; --j) {
+                    load_blk_at(X, seg + (int64_t)(j - js) * stride, off);  // a lane reads its own writes
+                    step_reverse<B>(c, k, b, X, L, p, prof.at(j), P0xb, P0yb, Vxb, Vyb);
+                }
+            }
+        }
+    };
+    reverse_sweep<B>(c, N, a, tape, g, cost_bar, cb_scalar, grad, status, tab, rev);
+}
+
+// ---------------------------------------------------------------------------
+// The reverse sweep of a small particle set, split over the waves of a
+// workgroup.  Such a set has fewer waves than the chip has SIMDs, and the
+// sweep is one serial chain of T steps per lane: its time is the chain's
+// length times the latency of a step.  Half of a step's instructions do not
+// depend on the adjoint (linearise), so other waves of the workgroup, on SIMDs
+// that would idle, compute them a chunk of steps ahead and pass them through
+// LDS; wave 0 runs the recursion alone (step_adjoint).  The same instructions
+// on the same operands as step_reverse: the same bits.
+// Full tape, T = 200, N = 1024: B = 1 58 -> 33 us, B = 3 90 -> 47, B = 4 104 ->
+// 54 (chunks of 2, 6 or 8 steps and 1, 3 or 4 helpers were no faster; one
+// helper is the bottleneck itself, 83 us at B = 3).  Checkpoints every 32
+// steps, T = 1000, N = 4096, B = 1: 490 -> 198 us (292 with a replay wave alone).
+
+// A workgroup barrier that orders LDS only: __syncthreads would also wait for
+// the loads of tape states in flight.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+constexpr int kPipeHelpers = 2;  // waves that linearise: each takes every kPipeHelpers-th step of a chunk
+// one of the two buffers of chunks of C steps
+template <int B, int C>
+__host__ __device__ constexpr int pipe_buffer_floats() { return C * Lin<B>::N4 * 4 * 64; }
+
+// Step o of a chunk in its LDS buffer (q: this lane's column).
+template <int B>
+__device__ __forceinline__ void put_lin(float4* q, int o, Lin<B>& t) {
+    constexpr int N4 = Lin<B>::N4;
+#pragma unroll
+    for (int v = Lin<B>::N; v < 4 * N4; ++v) t.v[v] = 0.0f;
+#pragma unroll
+    for (int v = 0; v < N4; ++v)
+        q[(o * N4 + v) * 64] = make_float4(t.v[4 * v], t.v[4 * v + 1], t.v[4 * v + 2], t.v[4 * v + 3]);
+}
+
+// Push profile of the steps j0 .. j0 + 63, one per lane (profile_block's
+// expression from any first step; profile_lane(v, j - j0) reads step j).
+__device__ __forceinline__ float profile_from(int j0, float invL) {
+    return push_profile((float)(j0 + 1 + (int)__lane_id()) * invL);
+}
+
+// The recursion over a chunk's steps jh, jh - 1, ... (those >= jl).
+template <int B, int C>
+__device__ __forceinline__ void chunk_adjoint(const SimConst& c, const BlkConst<B>& k, int b, const float4* q, int jh,
+                                              int jl, float invL, Blk& L, const Push& p, float& P0xb, float& P0yb,
+                                              float& Vxb, float& Vyb) {
+    constexpr int N4 = Lin<B>::N4;
+    const float v = profile_from(jh - C + 1, invL);
+    Lin<B> t[C];
+#pragma unroll
+    for (int o = 0; o < C; ++o)
+#pragma unroll
+        for (int v = 0; v < N4; ++v) {
+            const float4 x = q[(o * N4 + v) * 64];
+            t[o].v[4 * v + 0] = x.x;
+            t[o].v[4 * v + 1] = x.y;
+            t[o].v[4 * v + 2] = x.z;
+            t[o].v[4 * v + 3] = x.w;
+        }
+#pragma unroll
+    for (int o = 0; o < C; ++o)
+        if (jh - o >= jl) step_adjoint<B>(c, k, b, t[o], L, p, profile_lane(v, C - 1 - o), P0xb, P0yb, Vxb, Vyb);
+}
+
+// Full tape: two chunk buffers, filled and read in turn.
+template <int B, int C>
+__global__ __launch_bounds__(64 * (1 + kPipeHelpers)) void k_rollout_adj_split(SimConst c, int N, const float* __restrict__ theta,
+                                                               const float* __restrict__ tape, TapeGeom g,
+                                                               const float* __restrict__ cost_bar, float cb_scalar,
+                                                               float* __restrict__ grad, uint32_t* status) {
+    constexpr int W = kPipeHelpers, PER = C / W;
+    static_assert(C % W == 0, "whole steps per helper");
+    extern __shared__ __align__(16) float lds[];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const AdjLane<B> a(N, (int64_t)blockIdx.x * 64 + (threadIdx.x & 63), g);
+    const BlkConst<B> k = blk_const<B>(c, a.b);
+    const int H = c.H, T = c.T;
+    float4* buf = reinterpret_cast<float4*>(lds + adj_table_floats(H)) + a.lw;
+    constexpr int kBuf = pipe_buffer_floats<B, C>() / 4;  // float4 of one buffer
+    if (wave == 0) phase_table(theta, N, a.i, a.s, H, lds, a.lw);
+    lds_barrier();
+    int it = 0;  // chunk counter, the same in every wave
+    if (wave == 0) {
+        auto rev = [&](int kk, int, const Push& p, Blk& L, float& P0xb, float& P0yb, float& Vxb, float& Vyb) {
+            const int nst = phase_start(kk + 1, T, H) - phase_start(kk, T, H);
+            const float invL = 1.0f / (float)nst;
+            for (int jh = nst - 1; jh >= 0; jh -= C, ++it) {
+                lds_barrier();  // the chunk is filled
+                chunk_adjoint<B, C>(c, k, a.b, buf + (it & 1) * kBuf, jh, 0, invL, L, p, P0xb, P0yb, Vxb, Vyb);
+            }
+        };
+        reverse_sweep<B>(c, N, a, tape, g, cost_bar, cb_scalar, grad, status, lds, rev);
+        lds_barrier();
+        return;
+    }
+    // helpers: steps jh - o of each chunk, o = wave - 1, wave - 1 + W, ...
+    const int o0 = wave - 1;
+    Push p;
+    side_frame(a.s, p);
+    Blk A, X[PER];
+    load_blk_at(A, tape + (int64_t)phase_start(H - 1, T, H) * a.stride, a.off);
+#pragma unroll
+    for (int m = 0; m < PER; ++m)
+        load_blk_at(X[m], tape + (int64_t)max(T - 1 - (o0 + W * m), 0) * a.stride, a.off);
+    for (int kk = H - 1; kk >= 0; --kk) {
+        const int tk = phase_start(kk, T, H), nst = phase_start(kk + 1, T, H) - tk;
+        const float* pt = lds + kk * kPhaseFloats + a.lw;
+        Anchor an;
+        phase_push(c, A.x, A.y, A.ph, pt[64], pt[128], p, an);
+        if (kk > 0) load_blk_at(A, tape + (int64_t)phase_start(kk - 1, T, H) * a.stride, a.off);
+        const float invL = 1.0f / (float)nst;
+        for (int jh = nst - 1; jh >= 0; jh -= C, ++it) {
+            // the next chunk's states load while this one's are linearised (the
+            // next phase's first chunk starts at its last step)
+            const int tn = jh - C >= 0 ? tk + jh - C : tk - 1;
+            Blk Xn[PER];
+#pragma unroll
+            for (int m = 0; m < PER; ++m)
+                load_blk_at(Xn[m], tape + (int64_t)max(tn - (o0 + W * m), 0) * a.stride, a.off);
+            float4* q = buf + (it & 1) * kBuf;
+            const float v = profile_from(jh - C + 1, invL);
+#pragma unroll
+            for (int m = 0; m < PER; ++m) {
+                const int o = o0 + W * m, j = jh - o;
+                if (j >= 0) {
+                    Lin<B> t;
+                    linearise<B>(c, k, X[m], p, profile_lane(v, C - 1 - o), t);
+                    put_lin<B>(q, o, t);
+                }
+                X[m] = Xn[m];
+            }
+            lds_barrier();  // the chunk is filled; wave 0 is past the other buffer
+        }
+    }
+    lds_barrier();
+}
+
+// The segments of a checkpointed tape in reverse order, as every wave of the
+// kernels below walks them: segment q of phase k, steps js .. js + n - 1.
+struct SegWalk {
+    int H, T, K, k, q, nst, n;
+    __device__ __forceinline__ void phase(int kk) {
+        k = kk;
+        nst = phase_start(kk + 1, T, H) - phase_start(kk, T, H);
+        q = (nst + K - 1) / K - 1;
+        n = nst - q * K;
+    }
+    __device__ __forceinline__ SegWalk(int H_, int T_, int K_) : H(H_), T(T_), K(K_) { phase(H - 1); }
+    // false past the first segment (n = 0 then)
+    __device__ __forceinline__ bool next() {
+        if (q > 0) {
+            --q;
+            n = K;
+            return true;
+        }
+        if (k > 0) {
+            phase(k - 1);
+            return true;
+        }
+        n = 0;
+        return false;
+    }
+};
+
+// Checkpoints: while wave 0 runs the recursion over one segment, waves 1 and 2
+// linearise its steps a chunk ahead, from states in LDS, and wave 3 replays
+// the segment before it from its checkpoint into the other state buffer
+// [K][3][64] float2 (a segment's replay needs no other's).  Everything moves in
+// intervals of C steps, one barrier each; a segment's stage has as many
+// intervals as its own chunks or the next replay's need.
+template <int B, int C>
+__global__ __launch_bounds__(64 * (2 + kPipeHelpers)) void k_rollout_adj_ckpt(SimConst c, int N, const float* __restrict__ theta,
+                                                              const float* __restrict__ tape, TapeGeom g,
+                                                              const float* __restrict__ cost_bar, float cb_scalar,
+                                                              float* __restrict__ grad, uint32_t* status) {
+    constexpr int W = kPipeHelpers, PER = C / W;
+    extern __shared__ __align__(16) float lds[];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const AdjLane<B> a(N, (int64_t)blockIdx.x * 64 + (threadIdx.x & 63), g);
+    const BlkConst<B> k = blk_const<B>(c, a.b);
+    const int H = c.H, T = c.T, K = g.ckpt;
+    constexpr int kBuf = pipe_buffer_floats<B, C>() / 4;
+    float4* buf = reinterpret_cast<float4*>(lds + adj_table_floats(H)) + a.lw;
+    float2* states = reinterpret_cast<float2*>(lds + adj_table_floats(H) + 8 * kBuf) + a.lw;
+    const int kStates = K * 3 * 64;  // float2 of one state buffer
+    auto intervals = [&](int n) { return (n + C - 1) / C; };
+    if (wave == 0) phase_table(theta, N, a.i, a.s, H, lds, a.lw);
+    lds_barrier();
+    SegWalk w(H, T, K);
+    int it = 0;  // interval counter, the same in every wave
+    if (wave == 0) {
+        auto rev = [&](int kk, int, const Push& p, Blk& L, float& P0xb, float& P0yb, float& Vxb, float& Vyb) {
+            if (kk == H - 1)  // the first segment's replay
+                for (int m = intervals(w.n); m > 0; --m, ++it) lds_barrier();
+            const float invL = 1.0f / (float)w.nst;
+            for (bool more = true; more && w.k == kk;) {
+                const int js = w.q * K, n = w.n, nc = intervals(n);
+                more = w.next();
+                for (int m = 0; m < max(nc, intervals(w.n)); ++m, ++it) {
+                    lds_barrier();  // the chunk is filled
+                    if (m < nc)
+                        chunk_adjoint<B, C>(c, k, a.b, buf + (it & 1) * kBuf, js + n - 1 - m * C, js, invL, L, p, P0xb,
+                                            P0yb, Vxb, Vyb);
+                }
+            }
+        };
+        reverse_sweep<B>(c, N, a, tape, g, cost_bar, cb_scalar, grad, status, lds, rev);
+        lds_barrier();
+        return;
+    }
+    Push p;
+    side_frame(a.s, p);
+    int kp = -1;  // the phase p is for
+    float invL = 0.0f;
+    Blk A;  // the next phase's anchor
+    load_blk_at(A, tape + (int64_t)phase_entry(g, H - 1, T, H) * a.stride, a.off);
+    auto enter = [&](int kk, int nst) {  // at a phase's first segment
+        if (kk == kp) return;
+        kp = kk;
+        const float* pt = lds + kk * kPhaseFloats + a.lw;
+        Anchor an;
+        phase_push(c, A.x, A.y, A.ph, pt[64], pt[128], p, an);
+        if (kk > 0) load_blk_at(A, tape + (int64_t)phase_entry(g, kk - 1, T, H) * a.stride, a.off);
+        invL = 1.0f / (float)nst;
+    };
+    if (wave <= W) {
+        const int o0 = wave - 1;
+        for (int m = intervals(w.n); m > 0; --m, ++it) lds_barrier();
+        int par = 0;
+        for (bool more = true; more; par ^= 1) {
+            enter(w.k, w.nst);
+            const int js = w.q * K, n = w.n, nc = intervals(n);
+            more = w.next();
+            for (int m = 0; m < max(nc, intervals(w.n)); ++m, ++it) {
+                float4* q = buf + (it & 1) * kBuf;
+                const float v = profile_from(js + n - (m + 1) * C, invL);
+#pragma unroll
+                for (int u = 0; u < PER; ++u) {
+                    const int o = o0 + W * u, r = n - 1 - m * C - o;  // step js + r
+                    if (r >= 0) {
+                        const float2* e = states + par * kStates + 3 * r * 64;
+                        const float2 x = e[0], y = e[64], z = e[128];
+                        const Blk X{x.x, x.y, y.x, y.y, z.x, z.y};
+                        Lin<B> t;
+                        linearise<B>(c, k, X, p, profile_lane(v, C - 1 - o), t);
+                        put_lin<B>(q, o, t);
+                    }
+                }
+                lds_barrier();
+            }
+        }
+        lds_barrier();
+        return;
+    }
+    // replay: the first segment in a stage of its own, each other one during
+    // the stage of the segment after it
+    int64_t entry = g.n_entries - 1;  // the segment's checkpoint
+    Blk X, Xn;
+    load_blk_at(Xn, tape + entry * a.stride, a.off);
+    int par = 0, before = 0;  // before: chunks of the segment whose stage this is
+    for (;; par ^= 1) {
+        const int n = w.n;
+        X = Xn;
+        if (n > 0) enter(w.k, w.nst);
+        entry = max(entry - 1, (int64_t)0);
+        load_blk_at(Xn, tape + entry * a.stride, a.off);
+        const int js = w.q * K;
+        float2* e = states + par * kStates;
+        for (int m = 0; m < max(before, intervals(n)); ++m, ++it) {
+            const float v = profile_from(js + m * C, invL);
+            auto step = [&](int o) {
+                e[0] = make_float2(X.x, X.y);
+                e[64] = make_float2(X.ph, X.vx);
+                e[128] = make_float2(X.vy, X.om);
+                e += 3 * 64;
+                step_forward<B>(c, k, a.b, X, p, profile_lane(v, o));
+            };
+            if (n >= (m + 1) * C) {
+#pragma unroll
+                for (int o = 0; o < C; ++o) step(o);
+            } else {
+                for (int o = 0; m * C + o < n; ++o) step(o);
+            }
+            lds_barrier();
+        }
+        if (n == 0) break;
+        before = intervals(n);
+        w.next();
+    }
+    lds_barrier();
+}
+
+// The same for segments too long for that kernel's LDS: wave 1 replays, wave
+// 0 reverses the segment after it, each step whole.
+template <int B>
+__global__ __launch_bounds__(128) void k_rollout_adj_replay(SimConst c, int N, const float* __restrict__ theta,
+                                                            const float* __restrict__ tape, TapeGeom g,
+                                                            const float* __restrict__ cost_bar, float cb_scalar,
+                                                            float* __restrict__ grad, uint32_t* status) {
+    extern __shared__ __align__(16) float lds[];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const AdjLane<B> a(N, (int64_t)blockIdx.x * 64 + (threadIdx.x & 63), g);
+    const BlkConst<B> k = blk_const<B>(c, a.b);
+    const int H = c.H, T = c.T, K = g.ckpt;
+    float2* buf = reinterpret_cast<float2*>(lds + adj_table_floats(H)) + a.lw;
+    const int kBuf = K * 3 * 64;  // float2 of one buffer
+    if (wave == 0) phase_table(theta, N, a.i, a.s, H, lds, a.lw);
+    lds_barrier();
+    int it = 0;  // segment counter, the same in both waves
+    if (wave == 0) {
+        auto rev = [&](int kk, int, const Push& p, Blk& L, float& P0xb, float& P0yb, float& Vxb, float& Vyb) {
+            const int nst = phase_start(kk + 1, T, H) - phase_start(kk, T, H);
+            Profile prof;
+            prof.reset(1.0f / (float)nst);
+            for (int q = (nst + K - 1) / K - 1; q >= 0; --q, ++it) {
+                lds_barrier();  // the segment is replayed
+                const int js = q * K, je = min(js + K, nst);
+                const float2* e = buf + (it & 1) * kBuf;
+                auto read = [&](int j) {
+                    const float2 x = e[3 * (j - js) * 64], y = e[(3 * (j - js) + 1) * 64], w = e[(3 * (j - js) + 2) * 64];
+                    return Blk{x.x, x.y, y.x, y.y, w.x, w.y};
+                };
+                Blk X = read(je - 1);
+                for (int j = je - 1; j >= js; --j) {
+                    const Blk Xn = read(max(j - 1, js));  // the next step's state loads during this one
+                    step_reverse<B>(c, k, a.b, X, L, p, prof.at(j), P0xb, P0yb, Vxb, Vyb);
+                    X = Xn;
+                }
+            }
+        };
+        reverse_sweep<B>(c, N, a, tape, g, cost_bar, cb_scalar, grad, status, lds, rev);
+        lds_barrier();
+        return;
+    }
+    Push p;
+    side_frame(a.s, p);
+    int entry = phase_entry(g, H - 1, T, H);
+    Blk A, X;
+    load_blk_at(A, tape + (int64_t)entry * a.stride, a.off);
+    load_blk_at(X, tape + (g.n_entries - 1) * a.stride, a.off);
+    for (int kk = H - 1; kk >= 0; --kk) {
+        const int nst = phase_start(kk + 1, T, H) - phase_start(kk, T, H);
+        const float* pt = lds + kk * kPhaseFloats + a.lw;
+        Anchor an;
+        phase_push(c, A.x, A.y, A.ph, pt[64], pt[128], p, an);
+        const int here = entry;
+        if (kk > 0) {
+            entry -= phase_segments(kk - 1, T, H, K);
+            load_blk_at(A, tape + (int64_t)entry * a.stride, a.off);
+        }
+        for (int q = (nst + K - 1) / K - 1; q >= 0; --q, ++it) {
+            const int js = q * K, je = min(js + K, nst);
+            Blk Xn;  // the checkpoint of the segment before
+            load_blk_at(Xn, tape + (int64_t)max(here + q - 1, 0) * a.stride, a.off);
+            float2* e = buf + (it & 1) * kBuf;
+            auto put = [&]() {
+                e[0] = make_float2(X.x, X.y);
+                e[64] = make_float2(X.ph, X.vx);
+                e[128] = make_float2(X.vy, X.om);
+                e += 3 * 64;
+            };
+            for_steps(js, je - 1, 1.0f / (float)nst, [&](int, float sig) {
+                put();
+                step_forward<B>(c, k, a.b, X, p, sig);
+            });
+            put();  // the last step's result is the next segment's checkpoint
+            X = Xn;
+            lds_barrier();  // the segment is replayed; wave 0 is past the other buffer
+        }
+    }
+    lds_barrier();
 }
 
 // ---------------------------------------------------------------------------
@@ -1095,68 +1602,38 @@ __device__ __forceinline__ void rollout_adj_packed(const SimConst& c, int N, con
     const int lw = (int)(lane & 63);
     phase_table(theta, N, i, s, H, tab, lw);
 
-    int ent[kMaxPushes];
-    {
-        int e = 0;
-        for (int kk = 0; kk < H; ++kk) {
-            const int tk = phase_start(kk, T, H), tk1 = phase_start(kk + 1, T, H);
-            ent[kk] = (g.ckpt == 0) ? tk : e;
-            if (g.ckpt) e += (tk1 - tk + g.ckpt - 1) / g.ckpt;
-        }
-    }
-    float Px[kMaxPushes + 1], Py[kMaxPushes + 1];
-    for (int kk = 0; kk < H; ++kk) {
-        Px[kk] = tape[ent[kk] * stride + slot0 * 6 + 0];
-        Py[kk] = tape[ent[kk] * stride + slot0 * 6 + 1];
-    }
-    float phT;
+    float* seeds = tab + H * kPhaseFloats;
+    float PHx, PHy, phT;
     {
         const float z = tab[(H - 1) * kPhaseFloats + lw];
         const float* e = tape + g.ends_off + (int64_t)(H - 1) * stride + slot0 * 6;
-        Px[H] = side_sum<1>(z * e[0]);
-        Py[H] = side_sum<1>(z * e[1]);
+        PHx = side_sum<1>(z * e[0]);
+        PHy = side_sum<1>(z * e[1]);
         phT = side_sum<1>(z * e[2]);
     }
     const float cb = cost_bar ? cost_bar[i] : cb_scalar;
-    float Pxb[kMaxPushes + 1], Pyb[kMaxPushes + 1];
-    for (int kk = 0; kk <= H; ++kk) Pxb[kk] = Pyb[kk] = 0.0f;
-    {
-        const float ux = Px[H] - c.goal[0], uy = Py[H] - c.goal[1];
-        Pxb[H] += cb * c.wt * 2.0f * relu(fabsf(ux) - c.tol) * copysignf(1.0f, ux);
-        Pyb[H] += cb * c.wt * 2.0f * relu(fabsf(uy) - c.tol) * copysignf(1.0f, uy);
-    }
-    const float phTb = cb * c.wr * sinf(phT - c.goal[2]);
-    const float wtr = cb * c.wtr;
-    if (!c.per_phase) {
-        for (int kk = 1; kk <= H; ++kk) {
-            float u, dd;
-            u = Px[kk - 1] - Px[kk];  dd = wtr * u / smooth_abs(u, c.ea2);  Pxb[kk - 1] += dd; Pxb[kk] -= dd;
-            u = Py[kk - 1] - Py[kk];  dd = wtr * u / smooth_abs(u, c.ea2);  Pyb[kk - 1] += dd; Pyb[kk] -= dd;
-            u = Px[kk] - Px[H];       dd = wtr * u / smooth_abs(u, c.ea2);  Pxb[kk] += dd;     Pxb[H] -= dd;
-            u = Py[kk] - Py[H];       dd = wtr * u / smooth_abs(u, c.ea2);  Pyb[kk] += dd;     Pyb[H] -= dd;
-            u = Px[kk - 1] - Px[H];   dd = wtr * u / smooth_abs(u, c.ea2);  Pxb[kk - 1] -= dd; Pxb[H] += dd;
-            u = Py[kk - 1] - Py[H];   dd = wtr * u / smooth_abs(u, c.ea2);  Pyb[kk - 1] -= dd; Pyb[H] += dd;
-        }
-    } else {
-        for (int kk = 1; kk < H; ++kk) {
-            float u, dd;
-            u = Px[kk - 1] - Px[kk];  dd = wtr * u / smooth_abs(u, c.ea2);  Pxb[kk] -= dd;
-            u = Py[kk - 1] - Py[kk];  dd = wtr * u / smooth_abs(u, c.ea2);  Pyb[kk] -= dd;
-            u = Px[kk] - Px[H];       dd = wtr * u / smooth_abs(u, c.ea2);  Pxb[kk] += dd;
-            u = Py[kk] - Py[H];       dd = wtr * u / smooth_abs(u, c.ea2);  Pyb[kk] += dd;
-        }
-    }
+    float xb, yb, phb;
+    cost_seeds(
+        c, H, cb,
+        [&](int k, float& x, float& y) {
+            const float* e = tape + (int64_t)phase_entry(g, k, T, H) * stride + slot0 * 6;
+            x = e[0];
+            y = e[1];
+        },
+        PHx, PHy, phT, seeds, lw, xb, yb, phb);
     Blk Ls[B];
 #pragma unroll
     for (int b = 0; b < B; ++b) Ls[b].x = Ls[b].y = Ls[b].ph = Ls[b].vx = Ls[b].vy = Ls[b].om = 0.0f;
-    Ls[0].x = Pxb[H];
-    Ls[0].y = Pyb[H];
-    Ls[0].ph = phTb;
+    Ls[0].x = xb;
+    Ls[0].y = yb;
+    Ls[0].ph = phb;
 
     Push p;
     side_frame(s, p);
     bool bad = false;
+    int entry = phase_entry(g, H, T, H);  // of the phase's first step
     for (int kk = H - 1; kk >= 0; --kk) {
+        entry -= g.ckpt == 0 ? phase_start(kk + 1, T, H) - phase_start(kk, T, H) : phase_segments(kk, T, H, g.ckpt);
         const int tk = phase_start(kk, T, H), tk1 = phase_start(kk + 1, T, H);
         const float invL = 1.0f / (float)(tk1 - tk);
         const float* pt = tab + kk * kPhaseFloats + lw;
@@ -1178,7 +1655,7 @@ __device__ __forceinline__ void rollout_adj_packed(const SimConst& c, int N, con
         const float zb = blocks_sum<B>(zpb);
         const float ab = z * (zb - side_sum<1>(z * zb));  // softmax VJP
         Blk A;
-        load_blk_at(A, tape + ent[kk] * stride, off);  // block 0's pose: the anchor
+        load_blk_at(A, tape + (int64_t)entry * stride, off);  // block 0's pose: the anchor
         Anchor an;
         phase_push(c, A.x, A.y, A.ph, o, D, p, an);
         float P0xb = 0.0f, P0yb = 0.0f, Vxb = 0.0f, Vyb = 0.0f;
@@ -1208,7 +1685,7 @@ __device__ __forceinline__ void rollout_adj_packed(const SimConst& c, int N, con
                 const int js = q * g.ckpt;
                 const int je = min(js + g.ckpt, tk1 - tk);
                 Blk X[B];
-                load_blks<B>(X, tape + (int64_t)(ent[kk] + q) * stride, off);
+                load_blks<B>(X, tape + (int64_t)(entry + q) * stride, off);
                 for (int j = js; j < je; ++j) {
                     if (live) store_blks<B>(X, seg + (int64_t)(j - js) * stride, off);
                     step_forward_packed<B>(c, X, p, prof.at(j));
@@ -1238,14 +1715,15 @@ __device__ __forceinline__ void rollout_adj_packed(const SimConst& c, int N, con
         }
         const float Axs = side_sum<1>(P0xb), Ays = side_sum<1>(P0yb), Aphs = side_sum<1>(Aphb);
         const float obs = side_sum<1>(ob), Dbs = side_sum<1>(Db);
+        const float Pxb = seeds[kk * kSeedFloats + lw], Pyb = seeds[kk * kSeedFloats + 64 + lw];
         if (c.per_phase) {
 #pragma unroll
             for (int b = 0; b < B; ++b) Ls[b].x = Ls[b].y = Ls[b].ph = Ls[b].vx = Ls[b].vy = Ls[b].om = 0.0f;
-            Ls[0].x = Pxb[kk];
-            Ls[0].y = Pyb[kk];
+            Ls[0].x = Pxb;
+            Ls[0].y = Pyb;
         } else {
-            Ls[0].x += Axs + Pxb[kk];
-            Ls[0].y += Ays + Pyb[kk];
+            Ls[0].x += Axs + Pxb;
+            Ls[0].y += Ays + Pyb;
             Ls[0].ph += Aphs;
         }
         const float wb2 = 2.0f * cb * c.wb;
@@ -1408,7 +1886,7 @@ hipError_t launch_rollout_fwd_batched(const ProblemDesc* descs, const int2* tile
 hipError_t launch_rollout_adj_batched(const ProblemDesc* descs, const int2* tiles, int ntiles, int block,
                                       int grid, const float* theta, const float* tape, float cb_scalar,
                                       float* grad, float* seg, uint32_t* status, hipStream_t st, bool packed, int max_H, int max_B) {
-    const int wf = rollout_lds_floats(max_H, 0);
+    const int wf = adj_table_floats(max_H);
     if (packed)
         hipLaunchKernelGGL(k_rollout_adj_batched<true>, dim3(grid), dim3(block), (size_t)(block / 64) * wf * 4, st,
                            descs, tiles, ntiles, theta,
@@ -1437,6 +1915,16 @@ static hipError_t launch_fwd_b(const SimConst& c, int N, const float* theta, flo
     return hipGetLastError();
 }
 
+// Whether the split reverse sweep's workgroups (64 lanes and lds bytes each)
+// are on the chip at once.  A second round of them costs as long as the first,
+// while the waves of the whole-step sweep all fit: N = 4096, B = 3, H = 5 (1024
+// workgroups, 54 KB with chunks of four steps) took 131 us in two rounds, 99
+// whole-step, 93 with chunks of two steps (31 KB, one round).
+constexpr int64_t kLdsBytes = 160 * 1024;
+static bool split_adjoint_pays(unsigned grid, int64_t lds) {
+    return lds <= kLdsBytes && grid <= 256 * (kLdsBytes / lds);
+}
+
 template <int B>
 static hipError_t launch_adj_b(const SimConst& c, int N, const float* theta, const float* tape,
                                const TapeGeom& g, const float* cost_bar, float cb_scalar, float* grad,
@@ -1444,11 +1932,27 @@ static hipError_t launch_adj_b(const SimConst& c, int N, const float* theta, con
     const bool pk = packed && B > 1;
     const int64_t lanes = (int64_t)(pk ? 4 : Slots<B>::LANES) * N;
     const unsigned grid = (unsigned)((lanes + kRolloutBlock - 1) / kRolloutBlock);
+    // LDS of the split sweeps: the table, two chunk buffers of 4 or 2 steps,
+    // two buffers of a replayed segment's states
+    const int64_t table = adj_table_floats(c.H) * 4, states = (int64_t)2 * g.ckpt * 6 * 64 * 4;
+    const int64_t lds4 = table + 2 * pipe_buffer_floats<B, 4>() * 4, lds2 = table + 2 * pipe_buffer_floats<B, 2>() * 4;
     if (pk)
-        hipLaunchKernelGGL(k_rollout_adj_packed<B>, dim3(grid), dim3(kRolloutBlock), rollout_lds_floats(c.H, 0) * 4, st, c, N, theta, tape, g,
+        hipLaunchKernelGGL(k_rollout_adj_packed<B>, dim3(grid), dim3(kRolloutBlock), adj_table_floats(c.H) * 4, st, c, N, theta, tape, g,
                            cost_bar, cb_scalar, grad, seg, status);
+    else if (g.ckpt == 0 && split_adjoint_pays(grid, lds4))
+        hipLaunchKernelGGL((k_rollout_adj_split<B, 4>), dim3(grid), dim3(64 * (1 + kPipeHelpers)), lds4, st, c, N,
+                           theta, tape, g, cost_bar, cb_scalar, grad, status);
+    else if (g.ckpt == 0 && split_adjoint_pays(grid, lds2))
+        hipLaunchKernelGGL((k_rollout_adj_split<B, 2>), dim3(grid), dim3(64 * (1 + kPipeHelpers)), lds2, st, c, N,
+                           theta, tape, g, cost_bar, cb_scalar, grad, status);
+    else if (g.ckpt > 0 && split_adjoint_pays(grid, lds4 + states))
+        hipLaunchKernelGGL((k_rollout_adj_ckpt<B, 4>), dim3(grid), dim3(64 * (2 + kPipeHelpers)), lds4 + states, st, c,
+                           N, theta, tape, g, cost_bar, cb_scalar, grad, status);
+    else if (g.ckpt > 0 && split_adjoint_pays(grid, table + states))
+        hipLaunchKernelGGL(k_rollout_adj_replay<B>, dim3(grid), dim3(128), table + states, st, c, N, theta, tape, g,
+                           cost_bar, cb_scalar, grad, status);
     else
-        hipLaunchKernelGGL(k_rollout_adj<B>, dim3(grid), dim3(kRolloutBlock), rollout_lds_floats(c.H, 0) * 4, st, c, N, theta, tape, g, cost_bar,
+        hipLaunchKernelGGL(k_rollout_adj<B>, dim3(grid), dim3(kRolloutBlock), adj_table_floats(c.H) * 4, st, c, N, theta, tape, g, cost_bar,
                            cb_scalar, grad, seg, status);
     return hipGetLastError();
 }

@@ -225,21 +225,26 @@ bool scene_ok(const stamp_scene* s) {
 int64_t block_lanes(int N, int B) { return (int64_t)4 * (B == 1 ? 1 : (B == 2 ? 2 : 4)) * N; }
 
 // Automatic layout.  The block-per-lane form keeps more waves in flight,
-// which pays while a rollout is latency-bound (few waves per SIMD: at N = 1024
-// or 4096 particles of 3 blocks it is 1.3-1.6x faster).  Once its lanes fill
-// the chip (kPackedAutoLanes), one lane per sub-rollout issues about half the
-// instructions per particle and wins: N = 16384, B = 3, forward 177 vs 236 us,
-// adjoint 178 vs 336 us; the 64-problem batch 1.88 vs 2.12 ms per iteration.
-// The tape layout is the same, and so are the results, bit for bit.  (The
-// forward and the adjoint take the rule separately, so either may be chosen
-// on its own.)
+// which pays while a rollout is latency-bound (few waves per SIMD); once its
+// waves fill the chip, one lane per sub-rollout issues about half the
+// instructions per particle and wins.  A packed rollout of one problem takes
+// about the same time up to some 12 000 particles (its waves do not fill the
+// chip before), so its line is a particle count, the same for every block
+// count: T = 200, H = 5, block per lane against packed, forward / adjoint in us,
+//   B = 2: 8 192 particles 68 / 87 against 93 / 99, 12 288 108 / 120 against 94 / 103;
+//   B = 3: 8 192 114 / 146 against 132 / 141, 12 288 161 / 207 against 138 / 143;
+//   B = 4: 8 192 135 / 180 against 170 / 199, 12 288 197 / 255 against 176 / 206.
+// A batch of problems goes by its lanes: the 64-problem batch takes 1.88 ms per
+// iteration packed, 2.12 ms block per lane.  The tape layout is the same, and
+// so are the results, bit for bit.
 constexpr int64_t kPackedAutoLanes = (int64_t)2 * 64 * 1024;
-bool packed_for(const stamp_ctx* ctx, int64_t lanes, bool adjoint) {
-    (void)adjoint;
+constexpr int kPackedAutoParticles = 9216;
+bool packed_for(const stamp_ctx* ctx, bool automatic) {
     if (ctx->rollout_layout == STAMP_LAYOUT_BLOCKS) return false;
     if (ctx->rollout_layout == STAMP_LAYOUT_PACKED) return true;
-    return lanes >= kPackedAutoLanes;
+    return automatic;
 }
+bool packed_one(const stamp_ctx* ctx, int N) { return packed_for(ctx, N >= kPackedAutoParticles); }
 
 constexpr int kGraphUnroll = 4;  // iterations per unrolled graph
 constexpr int kMaxSvgdDim = 64;
@@ -304,10 +309,6 @@ void build_plan(int n, const stamp_scene* scenes, const int32_t* N, int K, float
         sv += align256(D.sv.total);
         snprintf(buf, sizeof buf, "%d/%d/%d/%d;", N[p], s->H, s->B, s->T);
         P.key += buf;
-        for (int i0 = 0; i0 < D.N; i0 += rollout_tile_particles(s->B, packed_fwd))
-            P.roll_tiles.push_back(make_int2(p, i0));
-        for (int i0 = 0; i0 < D.N; i0 += rollout_tile_particles(s->B, packed_adj))
-            P.adj_tiles.push_back(make_int2(p, i0));
         // median passes over all pairs, for problems whose pairs exceed the sample:
         // every (row block, column chunk) item (items without a pair i < j write
         // zero counts), and (segment, part) of the candidate passes
@@ -344,18 +345,21 @@ void build_plan(int n, const stamp_scene* scenes, const int32_t* N, int K, float
         for (int64_t e = 0; e < ne; e += kRedChunk)
             P.red_work.push_back(make_int4(p, (int)e, (int)std::min<int64_t>(e + kRedChunk, ne), 0));
     }
-    // the tiles that take longest first (a tile's time grows with its blocks
-    // and steps): the launch's last workgroups are then its cheapest.  The
-    // 64-problem batch (4 192 tiles, 1 to 4 blocks): forward 760 -> 690 us,
-    // adjoint 815 -> 710 us by the kernel trace.
-    auto longest_first = [&](std::vector<int2>& tiles) {
-        std::stable_sort(tiles.begin(), tiles.end(), [&](const int2& a, const int2& b) {
-            const stamp_scene &x = scenes[a.x], &y = scenes[b.x];
-            return (int64_t)x.B * x.T > (int64_t)y.B * y.T;
-        });
-    };
-    longest_first(P.roll_tiles);
-    longest_first(P.adj_tiles);
+    // rollout tiles, those that take longest first (a tile's time grows with
+    // its blocks and steps): the launch's last workgroups are then its
+    // cheapest.  The 64-problem batch (4 192 tiles, 1 to 4 blocks): forward 760
+    // -> 690 us, adjoint 815 -> 710 us by the kernel trace.
+    std::vector<int> longest(n);
+    for (int p = 0; p < n; ++p) longest[p] = p;
+    std::stable_sort(longest.begin(), longest.end(), [&](int x, int y) {
+        return (int64_t)scenes[x].B * scenes[x].T > (int64_t)scenes[y].B * scenes[y].T;
+    });
+    for (int p : longest) {
+        const int step_f = rollout_tile_particles(scenes[p].B, packed_fwd);
+        const int step_a = rollout_tile_particles(scenes[p].B, packed_adj);
+        for (int i0 = 0; i0 < N[p]; i0 += step_f) P.roll_tiles.push_back(make_int2(p, i0));
+        for (int i0 = 0; i0 < N[p]; i0 += step_a) P.adj_tiles.push_back(make_int2(p, i0));
+    }
     P.n_theta = th;
     for (int c = 0; c < kMedLists; ++c) {
         P.dist_start[c] = (int)P.dist_work.size();
@@ -657,7 +661,7 @@ int32_t stamp_rollout_fwd(stamp_ctx* ctx, const stamp_scene* scene, const stamp_
         return fail(ctx, STAMP_ENOSPACE, "tape %zu < %zu floats", tape_len, tape_floats(scene, N, ckpt_every));
     const TapeGeom g = tape_geom(scene, N, ckpt_every);
     hipError_t e = launch_rollout_fwd(c, N, theta, cost, tape, g, status, (hipStream_t)stream,
-                                      packed_for(ctx, block_lanes(N, c.B), false));
+                                      packed_one(ctx, N));
     return e == hipSuccess ? STAMP_OK : hip_fail(ctx, e, "rollout_fwd");
 }
 
@@ -692,7 +696,7 @@ int32_t stamp_plan_readout(stamp_ctx* ctx, const stamp_scene* scene, const stamp
     if (e == hipSuccess) e = launch_onehot(N, scene->H, theta, plan, st);
     if (e == hipSuccess)
         e = launch_rollout_fwd(c, N, plan, cost, nullptr, tape_geom(scene, N, 0), status, st,
-                               packed_for(ctx, block_lanes(N, c.B), false));
+                               packed_one(ctx, N));
     return e == hipSuccess ? STAMP_OK : hip_fail(ctx, e, "plan_readout");
 }
 
@@ -715,7 +719,7 @@ static int32_t rollout_adj_impl(stamp_ctx* ctx, const stamp_scene* scene, const 
     const TapeGeom g = tape_geom(scene, N, ckpt_every);
     c.per_phase = per_phase;
     hipError_t e = launch_rollout_adj(c, N, theta, tape, g, cost_bar, 1.0f, grad, (float*)workspace, status,
-                                      (hipStream_t)stream, packed_for(ctx, block_lanes(N, c.B), true));
+                                      (hipStream_t)stream, packed_one(ctx, N));
     return e == hipSuccess ? STAMP_OK : hip_fail(ctx, e, "rollout_adj");
 }
 
@@ -973,7 +977,8 @@ static int32_t solve_impl(stamp_ctx* ctx, int32_t n_problems, const stamp_scene*
         max_H = std::max(max_H, scenes[p].H);
         max_B = std::max(max_B, scenes[p].B);
     }
-    const bool packed = packed_for(ctx, all_lanes, false), packed_adj = packed_for(ctx, all_lanes, true);
+    const bool packed = n_problems == 1 ? packed_one(ctx, N[0]) : packed_for(ctx, all_lanes >= kPackedAutoLanes);
+    const bool packed_adj = packed;
     SolvePlan P;
     build_plan(n_problems, scenes, N, K, cfg->bandwidth, 256, &consts, P, packed, packed_adj);
     // Every rebuild below (another row block) must keep the regions where the
@@ -1590,7 +1595,7 @@ int32_t stamp_mlp_label(stamp_ctx* ctx, const stamp_scene* scene, const stamp_co
     if (n_in > d && !enc) return fail(ctx, STAMP_EINVAL, "null scene encoding");
     const TapeGeom g = tape_geom(scene, N, 0);
     hipError_t e = launch_rollout_fwd(c, N, theta, cost, nullptr, g, status, (hipStream_t)stream,
-                                      packed_for(ctx, block_lanes(N, c.B), false));
+                                      packed_one(ctx, N));
     if (e == hipSuccess) e = launch_mlp_pack_rows(theta, N, d, enc, n_in, x, (hipStream_t)stream);
     return e == hipSuccess ? STAMP_OK : hip_fail(ctx, e, "mlp_label");
 }
