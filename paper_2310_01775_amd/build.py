@@ -31,9 +31,10 @@ FLAGS = [
 ]
 
 
-# per-source additions: the BF16 contraction turns its Gram products into
-# kernel values with VALU code, which then reads them from VGPRs directly
-EXTRA = {"phi16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+# per-source additions: the BF16 contraction and the median turn their Gram
+# products into kernel values and distances with VALU code, which then reads
+# them from VGPRs directly
+EXTRA = {"phi16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"], "median.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def build(verbose: bool = False) -> str:

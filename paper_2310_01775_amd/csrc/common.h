@@ -70,31 +70,31 @@ constexpr int kTile = 64;        // rows/cols of a distance tile
 constexpr int kMedBins = 2048;   // bins of one interval-select pass
 constexpr int kMedCols = 64;     // columns of an all-pairs work item (rows: med_rows)
 constexpr int kCandSegs = 64;    // candidate buffer segments (one counter each)
-constexpr int kCandParts = 4;    // workgroups per segment of a candidate pass
 constexpr uint32_t kCandSegMin = 16384;  // candidate slots per segment at least
 
-// Median select state (one per problem): the interval [lo, hi] of FP32 bit
-// patterns known to hold the median, its rank inside, the pass bookkeeping,
-// and the resulting bandwidth.
+// Median select state (one per problem): the sample's bracket, pass 0's
+// counts, the interval each later pass leaves, and the resulting bandwidth.
 struct SelState {
-    uint32_t lo, hi;     // inclusive interval of bit patterns
-    uint32_t rank;       // 1-based rank of the median among the values in it
-    uint32_t shift;      // histogram bin = (bits - lo) >> shift
-    uint32_t mode;       // 0 done, 1 pass 0 pending, 2 candidate passes, 3 all-pairs passes
-    uint32_t overflow;   // pass 0: a candidate segment overflowed
-    uint32_t seg[kCandSegs];  // pass 0: slots used in each candidate segment
-    float h;             // resulting bandwidth
-    float m2;            // the median
+    uint32_t lo, hi;      // bracket, inclusive, of FP32 bit patterns
+    uint32_t rank;        // 1-based rank of the median among all pairs
+    uint32_t mode;        // 0 done, 1 the passes are wanted
+    // pass 0, per candidate segment: pairs below the bracket << 32 | candidates;
+    // a counter per cache line: the workgroups' atomics on a line run one by one
+    unsigned long long seg[kCandSegs][16];
+    uint32_t lo1, hi1, rank1, all;      // pass 1's interval and rank in it; all = 1: over every pair again
+    uint32_t lo2, hi2, rank2;           // pass 2's
+    uint32_t arrived;     // workgroups that ended pass 3
+    float h;              // resulting bandwidth
+    float m2;             // the median
 };
 
 // Byte offsets inside one problem's SVGD workspace.
 struct SvgdLayout {
     size_t cand_off;                // bracket values of the median select (uint32 bit patterns)
     uint32_t cand_cap;              // their capacity: kCandSegs segments of cand_cap / kCandSegs
-    size_t cnt_off;                 // per all-pairs item: pairs under, over the bracket
     int med_rows;                   // rows (one per thread) of an all-pairs item: 64 or 256
     int med_rb, med_cc;             // all-pairs items: row blocks x column chunks
-    size_t hist_off;                // kMedBins histogram of the median select
+    size_t hist_off;                // [3][kMedBins] histograms of the median select
     size_t sel_off;                 // SelState
     size_t part_off, part_floats;   // phi partial sums [splits][d][N]
     int splits;                     // column chunks of the phi contraction
@@ -171,21 +171,37 @@ __host__ __device__ inline int phi32_ot(int d) { return (d + 16) / 16; }
 __host__ __device__ inline int med_dp(int d) { return d <= 16 ? 16 : d <= 32 ? 32 : 64; }
 __host__ __device__ inline int med_class(int dp, int rows) { return (dp == 16 ? 0 : dp == 32 ? 2 : 4) + (rows == 256); }
 // Work lists of the median's all-pairs items, one per item shape: 6 direct
-// shapes (med_class), then 16 Gram-form shapes (ks32, rows) of the problems
-// above 2^20 pairs, then 2 of the split-form Gram (ks32 = 0: d <= 31, the
-// rows as three BF16 parts).
-constexpr int kMedLists = 6 + 16 + 2;
-__host__ __device__ inline int med_gram_list(int ks32, int rows) {
-    return (ks32 == 0 ? 22 : 6 + 2 * (ks32 / 2 - 1)) + (rows == 256);
+// shapes (med_class), then the Gram-form shapes of the problems above 2^20
+// pairs: 2 of the split form (ks = 0: d <= 31), 10 of the FP32 matrix cores
+// (8..16 k-steps), by rows.
+constexpr int kMedDirect = 6, kMedGram = 12, kMedLists = kMedDirect + kMedGram;
+__host__ __device__ inline int med_gram_list(int ks, int rows) {
+    return kMedDirect + (ks == 0 ? 0 : 2 * (ks / 2 - 3)) + (rows == 256);
+}
+__host__ __device__ inline int med_gram_ks(const SvgdLayout& L) { return L.split3 ? 0 : L.ks32; }
+// Workgroups of the Gram-form pass 0: a resident round of them (4 a compute
+// unit), at least two steps of 2^12 pairs each.
+__host__ __device__ inline int med_gram_groups(int N) {
+    const int64_t g = ((int64_t)N * N / 2) >> 13;
+    return g < 1024 ? (int)g : 1024;
+}
+// Workgroups of a pass over the candidates, one to four per segment: each adds
+// its up to 2048 bins to the global histogram, which costs as much as the
+// reads it shares.  Pass 1 with 64 / 128 / 256 workgroups: N = 4096 7.3 / 8.7 /
+// 13.5 us, N = 8192 11.0 / 10.6 / 14.0, N = 32768 99 / 56 / 31.
+__host__ __device__ inline int med_pass_groups(int N) {
+    const uint64_t p = ((uint64_t)N * (uint64_t)(N - 1) / 2) >> 24;
+    return kCandSegs * (int)(p < 1 ? 1 : p > 4 ? 4 : p);
 }
 
 struct BatchPlan {
     int n_problems;
-    const int4* dist_work;  int n_dist;   // (p, row block, column chunk, -) of the median passes,
+    const int4* dist_work;  int n_dist;   // (p, row block, column chunk, -) of pass 0,
     int dist_start[kMedLists];            // sorted by item shape: list c = entries
     int dist_n[kMedLists];                //   [dist_start[c], dist_start[c] + dist_n[c])
-    const int4* cand_work;  int n_cand;   // (p, segment, part, -) of the median's candidate passes
-                                          //   (problems above 2^20 pairs)
+    const int4* pass_work;                // (p, workgroup, workgroups, -) of the median's later passes
+    int pass_start[kMedGram];             //   (problems above 2^20 pairs), sorted by Gram shape
+    int pass_n[kMedGram];
     const int4* fin_work;   int n_fin;    // (p, -, -, -): problems of 2^20 pairs at most, whose select
                                           //   ends in one workgroup after pass 0
     const int4* phi_work[kPhi32Classes];  // (p, row block, split, -) per contraction class

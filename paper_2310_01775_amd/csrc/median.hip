@@ -14,14 +14,14 @@
 //      stage and every candidate pass read more candidates.  When all pairs fit in the
 //      sample, it is the population and its median is final.  The sample sits
 //      in LDS for the select.
-//   2. Pass 0 over every pair counts the pairs below lo and above hi and
-//      copies the in-bracket bit patterns into a candidate buffer.
-//   3. Each later pass histograms the current interval [lo, hi] into 2048
-//      linear bins and a select step narrows the interval to the bin holding
-//      rank k (with k's rank inside it).  The passes read the candidates when
-//      they cover the interval, else every pair again (rank k outside the
-//      bracket, or the buffer overflowed).  Widths are below 2^32 and each
-//      pass divides them by 2048, so three passes end at a single value.
+//   2. Pass 0 over every pair counts the pairs below lo and copies the
+//      in-bracket bit patterns into a candidate buffer.
+//   3. Pass 1 histograms the bracket into 2048 linear bins, pass 2 the bin that
+//      holds rank k: below a bracket of 2^22 bit patterns (nearly always) its
+//      bins are single values and pass 3 only looks up rank k; else pass 3 is
+//      the third histogram (widths are below 2^32).  The passes read the
+//      candidates when they cover the interval, else every pair again (rank k
+//      outside the bracket, or the buffer overflowed).
 // Every count is an integer and every comparison exact, so the result is the
 // exact order statistic, independent of scheduling.
 //
@@ -32,10 +32,10 @@
 //
 // An all-pairs work item is (ROWS-row block, 64-column chunk) in a workgroup of
 // 256: each thread keeps its row's coordinates in registers and reads the
-// staged columns as LDS broadcasts, four columns at a time.  Counts go to a
-// per-item array (no shared counters); a wave gathers its in-bracket values in
-// LDS and appends them to one of kCandSegs buffer segments with one atomic per
-// flush, so the segments hold candidates only.
+// staged columns as LDS broadcasts, four columns at a time.  A lane keeps its
+// in-bracket values in a list of its own in LDS, and a wave appends its lists
+// to one of kCandSegs buffer segments with one atomic per flush, which carries
+// its count of pairs below the bracket too.
 //
 // Sampled path: the bandwidth from the sample's own lower median.
 #include <math.h>
@@ -53,10 +53,8 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8v;
 
 namespace {
 
-constexpr uint32_t kModeDone = 0, kModePass0 = 1, kModeCand = 2, kModeAll = 3;
+constexpr uint32_t kModeDone = 0, kModePass0 = 1;
 constexpr float kBracketSigmas = 4.0f;
-constexpr uint32_t kWaveBuf = 512;        // candidates a wave stages in LDS between flushes
-constexpr int kGramGroup = 2;             // column chunks of one Gram-form item
 constexpr uint32_t kSentinel = 0xffffffffu;  // above every candidate interval
 constexpr int kSelThreads = 1024;         // threads of the sample select
 
@@ -84,12 +82,11 @@ struct MedView {
     int N, d;
     float fixed_h;
     int rows, rb, cc;    // all-pairs items: rows each, row blocks, column chunks
-    uint32_t cap;        // candidate slots (kCandSegs segments)
+    uint32_t seg_cap;    // candidate slots of a segment, whole 16-byte words
     float* smp;
     SelState* sel;
-    uint32_t* hist;
+    uint32_t* hist;      // [3][kMedBins], one histogram per pass
     uint32_t* cand;
-    uint32_t* cnt;       // [rb * cc][2]: pairs under, over the bracket
     const float* xr;     // Gram form: centred rows in MFMA operand order (4 ks floats each)
     const float* nrm;    // and their squared norms (FP32 matrix-core operands)
     const __bf16* xs3;   // split form (d <= 31): the same rows as three BF16 parts, [npad][3][32]
@@ -103,12 +100,11 @@ __device__ __forceinline__ MedView med_view(int N, int d, float fixed_h, const S
     v.rows = L.med_rows;
     v.rb = L.med_rb;
     v.cc = L.med_cc;
-    v.cap = L.cand_cap;
+    v.seg_cap = L.cand_cap / kCandSegs & ~3u;
     v.smp = reinterpret_cast<float*>(b + L.smp_off);
     v.sel = reinterpret_cast<SelState*>(b + L.sel_off);
     v.hist = reinterpret_cast<uint32_t*>(b + L.hist_off);
     v.cand = reinterpret_cast<uint32_t*>(b + L.cand_off);
-    v.cnt = reinterpret_cast<uint32_t*>(b + L.cnt_off);
     v.xr = reinterpret_cast<const float*>(b + L.x32_off);
     v.nrm = reinterpret_cast<const float*>(b + L.n32_off);
     v.xs3 = reinterpret_cast<const __bf16*>(b + L.xs3_off);
@@ -244,6 +240,26 @@ __device__ __forceinline__ void strided_hist(const uint32_t* __restrict__ a, uin
         const uint32_t x = a[e] - lo;
         if (x <= w) atomicAdd(&lh[x >> s], 1u);
     }
+}
+
+// The same by a workgroup of 256 over a 16-byte aligned array, sixteen values a
+// thread in flight.
+__device__ __forceinline__ void wide_hist(const uint32_t* __restrict__ a, uint32_t n, uint32_t lo, uint32_t hi,
+                                          uint32_t s, uint32_t* lh) {
+    const uint32_t w = hi - lo, whole = n & ~4095u;
+    for (uint32_t e = 4 * threadIdx.x; e < whole; e += 4096) {
+        uint4 q[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) q[u] = *reinterpret_cast<const uint4*>(a + e + 1024 * u);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const uint32_t x[4] = {q[u].x - lo, q[u].y - lo, q[u].z - lo, q[u].w - lo};
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                if (x[t] <= w) atomicAdd(&lh[x[t] >> s], 1u);
+        }
+    }
+    strided_hist<256>(a + whole, n - whole, threadIdx.x, lo, hi, s, lh);
 }
 
 template <int NT>
@@ -386,8 +402,8 @@ __device__ void sample_select_body(const MedView& v, int exact, float* h_out) {
         hi2 = z2;
     }
     if (exact && !all) {  // the passes add into a clear histogram and fresh segment counters
-        for (int b = tid; b < kMedBins; b += NT) v.hist[b] = 0;
-        for (int g = tid; g < kCandSegs; g += NT) sel->seg[g] = 0;
+        for (int b = tid; b < 3 * kMedBins; b += NT) v.hist[b] = 0;
+        for (int g = tid; g < kCandSegs; g += NT) sel->seg[g][0] = 0;
     }
     if (tid != 0) return;
     if (!exact || all) {
@@ -397,48 +413,114 @@ __device__ void sample_select_body(const MedView& v, int exact, float* h_out) {
     sel->lo = lo0;
     sel->hi = hi2;
     sel->rank = (uint32_t)((P + 1) / 2);
-    sel->shift = shift_for((uint64_t)hi2 - lo0 + 1);
-    sel->overflow = 0;
+    sel->arrived = 0;
     sel->mode = kModePass0;
 }
 
+// ---- candidate lists -----------------------------------------------------------
+// Pass 0 appends about one pair in twenty.  Each lane keeps its own list, a
+// column of the wave's LDS region [kDepth + 1][64]: every value is stored at
+// the lane's next place and the place advances when the value is inside the
+// bracket, so an append is one count, one address and one LDS store with no
+// ballot and nothing shared between lanes (a wave-wide compaction per value
+// took 34 VALU and scalar instructions and made every value wait for the one
+// before it).  The flush compacts: place by place, the lanes that hold a value
+// write it to consecutive slots.
+constexpr int kListStep = 4;  // values a lane may take between two depth checks
+template <int DEPTH>
+struct LaneList {
+    uint32_t* col;  // this lane's column
+    uint32_t cnt = 0, nb = 0;  // values held; pairs below the bracket since the last flush
+    uint32_t nb_wave = 0;      // more of them, counted for the whole wave
+    uint32_t flushes = 0;
+    static constexpr int kWords = (DEPTH + 1) * 64;
+    __device__ __forceinline__ void put(uint32_t x, bool in) {
+        col[cnt * 64] = x;
+        cnt += in ? 1u : 0u;
+    }
+    // The next flush's segment (hashed, so that the segments fill evenly).
+    __device__ __forceinline__ int segment() {
+        const uint32_t w = (blockIdx.x << 4) + (threadIdx.x >> 6);
+        return (int)(mix32(w + mix32(flushes++)) % kCandSegs);
+    }
+    // Room for another kListStep values in every lane (wave-uniform).
+    __device__ __forceinline__ bool full() const { return __any(cnt > (uint32_t)(DEPTH - kListStep)); }
+};
+
+// Sum over the wave (wave-uniform), by DPP moves: no LDS round trips.
+__device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, true);   // quad_perm [1,0,3,2]
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xF, 0xF, true);   // quad_perm [2,3,0,1]
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xF, 0xF, true);  // row_half_mirror
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x140, 0xF, 0xF, true);  // row_mirror: every lane its row's sum
+    uint32_t t = 0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) t += (uint32_t)__builtin_amdgcn_readlane((int)x, 16 * r);
+    return t;
+}
+
+// The wave's lists to its candidate segment in one reservation, which also
+// counts its pairs below the bracket.  conv(x): the distance's bit pattern.
+template <int DEPTH, class F>
+__device__ __forceinline__ void flush_lists(const MedView& v, LaneList<DEPTH>& l, F&& conv) {
+    const int lane = threadIdx.x & 63, seg = l.segment();
+    const uint32_t tot = wave_sum(l.cnt), below = wave_sum(l.nb) + l.nb_wave;
+    const uint32_t seg_cap = v.seg_cap;
+    uint32_t base = 0;
+    if (lane == 0 && (tot | below))
+        base = (uint32_t)atomicAdd(&v.sel->seg[seg][0], ((unsigned long long)below << 32) | tot);
+    base = __builtin_amdgcn_readfirstlane(base);
+    uint32_t* segbuf = v.cand + (size_t)seg * seg_cap;
+    static_assert(DEPTH % 4 == 0, "the values leave four places at a time");
+    for (uint32_t s = 0; __any(l.cnt > s); s += 4) {
+        uint32_t x[4];
+#pragma unroll
+        for (uint32_t u = 0; u < 4; ++u) x[u] = l.col[(s + u) * 64];
+#pragma unroll
+        for (uint32_t u = 0; u < 4; ++u) {
+            const bool has = l.cnt > s + u;
+            const uint64_t m = __ballot(has);
+            const uint32_t pos =
+                base + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            if (has && pos < seg_cap) segbuf[pos] = conv(x[u]);
+            base += (uint32_t)__popcll(m);
+        }
+    }
+    l.cnt = l.nb = l.nb_wave = 0;
+}
+
+// What a pass over every pair does with a pair: pass 0, or the histogram of
+// [lo, hi] into lh.
+constexpr int kPass0 = 0, kPassHist = 1;
+
 // ---- all-pairs work item (row block rb, column chunk cc) ---------------------------
-// Pass 0: counts under / over [lo, hi] into cnt[item], in-bracket values into
-// the candidate segments.  Mode all: histogram of [lo, hi] (LDS, flushed with
-// one atomic per non-empty bin).
-//
 // 256 threads: ROWS rows and 256 / ROWS column groups (a 64-row item gives each
 // wave a quarter of the columns, so small problems still fill the chip).  A
 // thread measures four columns at a time (four independent FMA chains, 16-byte
-// LDS broadcasts); each distance is summed over the coordinates in order.
-template <int DP, int ROWS>
-__device__ void med_item(const MedView& v, const float* __restrict__ theta, int rb, int cc) {
+// LDS broadcasts); each distance is summed over the coordinates in order, the
+// coordinates past d, which are zero, skipped four at a time.
+template <int ROWS>
+constexpr int kItemDepth = ROWS == 64 ? 16 : 32;  // 16 columns a wave, or 64
+
+template <int DP, int ROWS, int MODE>
+__device__ void med_item(const MedView& v, const float* __restrict__ theta, int rb, int cc, uint32_t lo, uint32_t hi,
+                         uint32_t s, uint32_t* lh) {
     constexpr int NT = 256;
     constexpr int CG = NT / ROWS;       // column groups
     constexpr int CPG = kMedCols / CG;  // columns per group
     constexpr int LD = DP + 4;          // staged row stride: 16-byte aligned rows
-    static_assert(NT % ROWS == 0 && CPG % 4 == 0 && ROWS % 64 == 0, "item shape");
+    constexpr int DEPTH = kItemDepth<ROWS>;
+    using List = LaneList<DEPTH>;
+    static_assert(NT % ROWS == 0 && CPG % kListStep == 0 && ROWS % 64 == 0, "item shape");
     static_assert(kMedCols * DP % NT == 0, "staging covers the columns exactly");
     __shared__ __align__(16) float tj[kMedCols][LD];
-    __shared__ uint32_t lh[kMedBins];
-    __shared__ uint32_t red[2][NT / 64];
-    __shared__ uint32_t wbuf[NT / 64][kWaveBuf];  // each wave's candidates before a flush
-    SelState* sel = v.sel;
-    const uint32_t mode = sel->mode;
-    if (mode != kModePass0 && mode != kModeAll) return;
+    __shared__ uint32_t lists[MODE == kPass0 ? NT / 64 : 1][MODE == kPass0 ? List::kWords : 1];
     const int tid = threadIdx.x, lane = tid & 63;
     const int rloc = tid % ROWS, cg = tid / ROWS;
     const int N = v.N, d = v.d;
     const int row0 = rb * ROWS, col0 = cc * kMedCols;
-    const bool pass0 = mode == kModePass0;
-    uint32_t* cnt = v.cnt + 2 * ((int64_t)rb * v.cc + cc);
-    if (col0 + kMedCols <= row0 + 1) {  // no pair i < j in this item
-        if (pass0 && tid == 0) cnt[0] = cnt[1] = 0;
-        return;
-    }
-    const uint32_t lo = sel->lo, hi = sel->hi, s = sel->shift;
-    if (!pass0)
-        for (int b = tid; b < kMedBins; b += NT) lh[b] = 0;
+    if (col0 + kMedCols <= row0 + 1) return;  // no pair i < j in this item
+    if (MODE != kPass0) __syncthreads();      // a pass takes several items: the columns before are read
     {  // stage the columns: consecutive threads read consecutive columns
         constexpr int SPT = kMedCols * DP / NT;
         float x[SPT];
@@ -459,476 +541,387 @@ __device__ void med_item(const MedView& v, const float* __restrict__ theta, int 
 #pragma unroll
     for (int l = 0; l < DP; ++l) ti[l] = (i < N && l < d) ? theta[(int64_t)l * N + i] : 0.0f;
     __syncthreads();
-    // this wave's candidate segment; its candidates gather in wb and go out
-    // in one reservation per flush
-    const int wave = tid >> 6;
-    const int seg = (int)(((blockIdx.y * gridDim.x + blockIdx.x) * (uint32_t)(NT / 64) + (uint32_t)wave) % kCandSegs);
-    const uint32_t seg_cap = v.cap / kCandSegs;
-    uint32_t* segbuf = v.cand + (size_t)seg * seg_cap;
-    uint32_t* wb = wbuf[wave];
-    uint32_t nwb = 0;
-    const uint64_t lt = (1ull << lane) - 1ull;
-    auto flush = [&]() {
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the wave's LDS writes before its reads
-        uint32_t base = 0;
-        if (lane == 0) {
-            base = atomicAdd(&sel->seg[seg], nwb);
-            if ((uint64_t)base + nwb > seg_cap) atomicOr(&sel->overflow, 1u);
-        }
-        base = __shfl(base, 0);
-        for (uint32_t e = (uint32_t)lane; e < nwb; e += 64)
-            if (base + e < seg_cap) segbuf[base + e] = wb[e];
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // reads before the next writes
-        nwb = 0;
-    };
-    uint32_t nb = 0, na = 0;
+    List list;
+    list.col = lists[MODE == kPass0 ? tid >> 6 : 0] + (MODE == kPass0 ? lane : 0);
+    auto same = [](uint32_t x) { return x; };
+    const uint32_t wlo = hi - lo;  // x in [lo, hi] iff x - lo <= hi - lo (unsigned)
     // the wave's columns, from the first one past its first row (j > i)
     const int wrow0 = row0 + (rloc & ~63);
     const int cbeg = cg * CPG, cend = cbeg + CPG;
     const int jskip = wrow0 + 1 - col0 - cbeg;
     const int cstart = cbeg + (jskip > 0 ? (jskip & ~3) : 0);
     for (int c = cstart; c < cend; c += 4) {
+        if (MODE == kPass0 && CPG > DEPTH && list.full())
+            flush_lists(v, list, same);
         float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int l = 0; l < DP; l += 4) {
+            if (l < d) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float4 t = *reinterpret_cast<const float4*>(&tj[c + q][l]);
+                    float df = ti[l] - t.x;
+                    acc[q] = fmaf(df, df, acc[q]);
+                    df = ti[l + 1] - t.y;
+                    acc[q] = fmaf(df, df, acc[q]);
+                    df = ti[l + 2] - t.z;
+                    acc[q] = fmaf(df, df, acc[q]);
+                    df = ti[l + 3] - t.w;
+                    acc[q] = fmaf(df, df, acc[q]);
+                }
+            }
+        }
+        const int jb = col0 + c;
+        auto classify = [&](auto whole_tag) __attribute__((always_inline)) {
+            constexpr bool WHOLE = decltype(whole_tag)::value;  // every pair of the four columns is one
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const float4 t = *reinterpret_cast<const float4*>(&tj[c + q][l]);
-                float df = ti[l] - t.x;
-                acc[q] = fmaf(df, df, acc[q]);
-                df = ti[l + 1] - t.y;
-                acc[q] = fmaf(df, df, acc[q]);
-                df = ti[l + 2] - t.z;
-                acc[q] = fmaf(df, df, acc[q]);
-                df = ti[l + 3] - t.w;
-                acc[q] = fmaf(df, df, acc[q]);
+                uint32_t x = __float_as_uint(acc[q]);
+                bool valid = true;
+                if constexpr (!WHOLE) {
+                    const int j = jb + q;
+                    valid = i < N && j < N && j > i;
+                }
+                if (MODE == kPass0) {
+                    if constexpr (!WHOLE) x = valid ? x : 0xffffffffu;  // above every bracket (hi is no NaN)
+                    list.nb += x < lo ? 1u : 0u;
+                    list.put(x, x - lo <= wlo);
+                } else {
+                    const bool in = valid && x - lo <= wlo;
+                    if (in) atomicAdd(&lh[(x - lo) >> s], 1u);
+                }
             }
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int j = col0 + c + q;
-            const bool valid = i < N && j < N && j > i;
-            const uint32_t bits = __float_as_uint(acc[q]);
-            const bool below = valid && bits < lo;
-            const bool above = valid && bits > hi;
-            const bool inr = valid && !below && !above;
-            if (!pass0) {
-                if (inr) atomicAdd(&lh[(bits - lo) >> s], 1u);
-                continue;
-            }
-            nb += below ? 1u : 0u;
-            na += above ? 1u : 0u;
-            const uint64_t mi = __ballot(inr);
-            if (mi) {
-                if (nwb + 64 > kWaveBuf) flush();
-                if (inr) wb[nwb + (uint32_t)__popcll(mi & lt)] = bits;
-                nwb += (uint32_t)__popcll(mi);
-            }
-        }
+        };
+        if (MODE == kPass0 && jb > wrow0 + 63 && jb + 4 <= N) classify(std::true_type{});  // wave-uniform
+        else classify(std::false_type{});
     }
-    if (!pass0) {
-        __syncthreads();
-        for (int b = tid; b < kMedBins; b += NT)
-            if (lh[b]) atomicAdd(&v.hist[b], lh[b]);
-        return;
-    }
-    if (nwb) flush();
-    for (int off = 32; off > 0; off >>= 1) {  // counts of the workgroup
-        nb += __shfl_xor(nb, off);
-        na += __shfl_xor(na, off);
-    }
-    if (lane == 0) {
-        red[0][tid >> 6] = nb;
-        red[1][tid >> 6] = na;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        uint32_t b = 0, a = 0;
-        for (int w = 0; w < NT / 64; ++w) {
-            b += red[0][w];
-            a += red[1][w];
-        }
-        cnt[0] = b;
-        cnt[1] = a;
-    }
+    if (MODE == kPass0) flush_lists(v, list, same);
 }
 
-// The same item with the distances in Gram form on the FP32 matrix cores:
-// D_ij = max(|x_i|^2 + |x_j|^2 - 2 x_i . x_j, 0) over the centred rows the
-// FP32 contraction uses (built before the median).  Each wave takes 64 rows
-// as four 16-row tiles; with 256-row items it takes every column of the item,
-// with 64-row items a 16-column quarter.  Per 16 columns and row tile, KS
-// MFMAs (16x16x4) give S[i][j] with lane l holding rows 4 (l / 16) + t of
-// column l % 16.  KS = 0 is the split form (d <= 31): the rows as three
-// BF16 parts and x_i . x_j as the six part products of order >= 2^-16 on the
-// BF16 matrix cores (16x16x32, the same output layout), FP32-accurate as the
-// FP32 direction's split form (its rows' slot 31, which holds -|x|^2 / 2's
-// parts for the contraction, is zeroed in the row operand).  Every pass computes a pair's distance with
-// the same instructions, so the counts stay exact.
+// The same with the distances in Gram form on the matrix cores, from the
+// centred rows the FP32 contraction uses (built before the median):
+// S = x_i . x_j + (e_i + e_j) with e = -|x|^2 / 2, D_ij = max(-2 S, 0).  Each
+// wave takes 64 rows as four 16-row tiles, of its own in a 256-row block, shared
+// by the four waves, which take a 16-column quarter each, in a 64-row block.  Per 16 columns
+// and row tile the MFMAs give S[i][j] with lane l holding rows 4 (l / 16) + t
+// of column l % 16.  KS > 0: KS FP32 products (16x16x4) and the two e added
+// after.  KS = 0 is the split form (d <= 31): the rows as three BF16 parts and
+// x_i . x_j as the six part products of order >= 2^-16 on the BF16 matrix cores
+// (16x16x32, the same output layout), FP32-accurate as the FP32 direction's
+// split form (the contraction's e_j in slot 31 meets a zero of the row operand).
+// Every pass computes a pair's S with the same instructions, so the counts stay
+// exact.
+//
+// Pass 0 classifies S itself: D in [lo, hi] iff S in [-hi/2, -lo/2] (exact
+// halves of normal values), whose bit patterns are consecutive.  Bounds this
+// does not hold for (a subnormal or zero lo, an infinite hi) take the general
+// classification on D.
+// Bound: VALU issue, eight instructions a value beside six MFMAs per four
+// values a lane (45 us of issue at N = 16384).  d = 30, a grid of equal items
+// and a compaction per value -> one resident round of equal runs and lane lists:
+// N = 16384 129 -> 74 us (a quarter of it the appends), 8192 46 -> 27 us.
 // The split form's part products (row part, column part), smallest first.
 __device__ constexpr int kGramPairs3[6][2] = {{1, 1}, {2, 0}, {0, 2}, {1, 0}, {0, 1}, {0, 0}};
 
-template <int KS, int ROWS>
-__device__ void med_item_gram(const MedView& v, int rb, int cc) {
-    // an item spans kGramGroup column chunks: its counts go to the first
-    // chunk's slot and zeros to the others
-    const int cc1 = min(cc + kGramGroup, v.cc);
+// A workgroup's share of the sweep: the steps (16 columns for each wave of a
+// 256-row block; 64 columns, 16 a wave, of a 64-row block) of row block after
+// row block from its diagonal to the last column, counted through, in equal
+// runs of consecutive steps.  A run that ends in one row block goes on in the
+// next.
+struct GramSteps {
+    int cols, per, rb;  // steps of the first row block, steps fewer per block, row blocks
+    __host__ __device__ int64_t before(int64_t r) const { return r * cols - per * (r * (r - 1) / 2); }
+    __host__ __device__ int64_t count() const { return before(rb); }
+    __device__ int block_of(int64_t t) const {  // the row block of step t
+        int a = 0, b = rb;                      // before(a) <= t < before(b)
+        while (b - a > 1) {
+            const int m = (a + b) >> 1;
+            if (before(m) <= t) a = m;
+            else b = m;
+        }
+        return a;
+    }
+};
+
+__host__ __device__ __forceinline__ GramSteps gram_steps(int N, int rows, int rb) {
+    return rows == 256 ? GramSteps{(N + 15) / 16, 16, rb} : GramSteps{(N + 63) / 64, 1, rb};
+}
+
+template <int KS, int ROWS, int MODE>
+__device__ void med_gram(const MedView& v, int blk, int nblk, uint32_t lo, uint32_t hi, uint32_t s, uint32_t* lh) {
     constexpr int NT = 256;
+    constexpr int DEPTH = 32;
+    using List = LaneList<DEPTH>;
     static_assert(ROWS == 64 || ROWS == 256, "item shape");
-    // pass 0 stages candidates per wave, the histogram passes count into lh:
-    // one LDS region serves both
-    constexpr uint32_t kBuf = 2048;  // flushed when a step (at most 16 x 64 values) might not fit
-    // a wave's staging is kBuf words and 64 more, one per lane, that take the
-    // stores of the values outside the bracket (the unconditional store)
-    constexpr uint32_t kWave = kBuf + 64;
-    static_assert(kMedBins <= (NT / 64) * kWave, "histogram inside the staging region");
-    __shared__ uint32_t lds_region[(NT / 64) * kWave];
-    uint32_t* const lh = lds_region;
-    __shared__ uint32_t red[2][NT / 64];
-    SelState* sel = v.sel;
-    const uint32_t mode = sel->mode;
-    if (mode != kModePass0 && mode != kModeAll) return;
+    __shared__ uint32_t lists[MODE == kPass0 ? NT / 64 : 1][MODE == kPass0 ? List::kWords : 1];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 15, kq = lane >> 4;
     const int N = v.N;
-    const int row0 = rb * ROWS, col0 = cc * kMedCols;
-    const bool pass0 = mode == kModePass0;
-    uint32_t* cnt = v.cnt + 2 * ((int64_t)rb * v.cc + cc);
-    if (pass0)
-        for (int e = 2 + tid; e < 2 * (cc1 - cc); e += NT) cnt[e] = 0;
-    if (cc1 * kMedCols <= row0 + 1) {  // no pair i < j in this item
-        if (pass0 && tid == 0) cnt[0] = cnt[1] = 0;
-        return;
-    }
-    const uint32_t lo = sel->lo, hi = sel->hi, s = sel->shift;
-    if (!pass0)
-        for (int b = tid; b < kMedBins; b += NT) lh[b] = 0;
-    __syncthreads();
-    const int wrow = ROWS == 256 ? row0 + 64 * wave : row0;
-    // 256-row items: every 16-column step for each wave; 64-row items: the
-    // waves take the steps in turn
-    const int cbeg = ROWS == 256 ? 0 : 16 * wave, cend = (cc1 - cc) * kMedCols, cstep = ROWS == 256 ? 16 : 64;
+    const GramSteps steps = gram_steps(N, ROWS, v.rb);
+    const uint32_t n_steps = (uint32_t)steps.count(), per = n_steps / nblk, more = n_steps % nblk;
+    const int64_t t0 = (int64_t)per * blk + min((uint32_t)blk, more), t1 = t0 + per + ((uint32_t)blk < more ? 1 : 0);
+    if (t0 == t1) return;
+    constexpr int cstep = ROWS == 256 ? 16 : 64;
     constexpr bool SPLIT = KS == 0;
     constexpr int KA = SPLIT ? 1 : KS;   // FP32 operand steps
     constexpr int NP = SPLIT ? 3 : 1;    // split-form parts
-    float xa[4][KA];
-    bf16x8v xa3[NP][4];
-    f4v ni[4];  // |x_i|^2 for i = wrow + 16 r + 4 kq + t
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
+    List list;
+    list.col = lists[MODE == kPass0 ? wave : 0] + (MODE == kPass0 ? lane : 0);
+    auto load = [&](int c, float (&x)[KA], bf16x8v (&x3)[NP], float& e) __attribute__((always_inline)) {
         if constexpr (SPLIT) {
-            const __bf16* p = v.xs3 + (int64_t)(wrow + 16 * r + col) * 96 + 8 * kq;
-#pragma unroll
-            for (int q = 0; q < NP; ++q) {
-                xa3[q][r] = *reinterpret_cast<const bf16x8v*>(p + 32 * q);
-                if (kq == 3) xa3[q][r][7] = (__bf16)0.0f;  // slot 31 holds e_i's part for the contraction
-            }
-        } else {
-            const float* p = v.xr + (int64_t)(wrow + 16 * r + col) * (4 * KS) + kq * KS;
-#pragma unroll
-            for (int k = 0; k < KS; ++k) xa[r][k] = p[k];
-        }
-        ni[r] = *reinterpret_cast<const f4v*>(v.nrm + wrow + 16 * r + 4 * kq);
-    }
-    // one candidate segment per workgroup (hashed: in a work list only every
-    // kGramGroup-th entry runs, and a plain modulus would leave segments unused)
-    const int seg = (int)(mix32(blockIdx.y * gridDim.x + blockIdx.x) % kCandSegs);
-    const uint32_t seg_cap = v.cap / kCandSegs;
-    uint32_t* segbuf = v.cand + (size_t)seg * seg_cap;
-    uint32_t* wb = lds_region + wave * kWave;
-    uint32_t nwb = 0;
-    auto flush = [&]() __attribute__((always_inline)) {
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the wave's LDS writes before its reads
-        uint32_t base = 0;
-        if (lane == 0) {
-            base = atomicAdd(&sel->seg[seg], nwb);
-            if ((uint64_t)base + nwb > seg_cap) atomicOr(&sel->overflow, 1u);
-        }
-        base = __shfl(base, 0);
-        for (uint32_t e = (uint32_t)lane; e < nwb; e += 64)
-            if (base + e < seg_cap) segbuf[base + e] = wb[e];
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // reads before the next writes
-        nwb = 0;
-    };
-    // wave-uniform counts of the wave's valid pairs, of those below lo and of
-    // those inside [lo, hi] (a pair is inside iff bits - lo <= hi - lo,
-    // unsigned); the pairs above hi are the rest
-    uint32_t nvalid = 0, nb = 0, nin = 0;
-    uint32_t nbl = 0;  // this lane's pairs below lo on the steps without checks (added to nb at the end)
-    const uint32_t wlo = hi - lo;
-    // the first step with a pair j > i for some row of the wave; the next
-    // step's operands load while this one computes
-    int c0 = cbeg;
-    while (c0 < cend && col0 + c0 + 15 <= wrow) c0 += cstep;
-    float xb[KA], xn[KA];
-    bf16x8v xb3[NP], xn3[NP];
-    float nj = 0.0f, nn = 0.0f;
-    auto load = [&](int c, float (&x)[KA], bf16x8v (&x3)[NP], float& n) __attribute__((always_inline)) {
-        if constexpr (SPLIT) {
-            const __bf16* p = v.xs3 + (int64_t)(col0 + c + col) * 96 + 8 * kq;
+            const __bf16* p = v.xs3 + (int64_t)(c + col) * 96 + 8 * kq;
 #pragma unroll
             for (int q = 0; q < NP; ++q) x3[q] = *reinterpret_cast<const bf16x8v*>(p + 32 * q);
         } else {
-            const float* p = v.xr + (int64_t)(col0 + c + col) * (4 * KS) + kq * KS;
+            const float* p = v.xr + (int64_t)(c + col) * (4 * KS) + kq * KS;
 #pragma unroll
             for (int k = 0; k < KS; ++k) x[k] = p[k];
         }
-        n = v.nrm[col0 + c + col];
+        e = v.nrm[c + col] * -0.5f;
     };
-    // one distance of the step: counted, and appended (pass 0) or
-    // histogrammed when inside the bracket; ALL: every pair of the step is
-    // valid (no row or column checks)
-    auto classify = [&](auto all_tag, auto p0_tag, uint32_t x, bool valid) __attribute__((always_inline)) {
-        constexpr bool ALL = decltype(all_tag)::value, P0 = decltype(p0_tag)::value;
-        if constexpr (ALL && P0) {
-            // the common step, without branches: the lane counts its pairs
-            // below lo, and every lane stores, an in-bracket value at its
-            // compacted place, any other value at the lane's own spare word
-            nbl += x < lo ? 1u : 0u;
-            const bool inb = x - lo <= wlo;
-            const uint64_t mb = __ballot(inb);
-            const uint32_t nm = (uint32_t)__popcll(mb);
-            const uint32_t pos =
-                nwb + __builtin_amdgcn_mbcnt_hi((uint32_t)(mb >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mb, 0u));
-            wb[inb ? pos : kBuf + (uint32_t)lane] = x;
-            nin += nm;
-            nwb = __builtin_amdgcn_readfirstlane(nwb + nm);
-            return;
-        }
-        const bool in = (ALL || valid) && x - lo <= wlo;
-        if (P0) {
-            nb += (uint32_t)__popcll(__ballot((ALL || valid) && x < lo));
-            if (!ALL) nvalid += (uint32_t)__popcll(__ballot(valid));
-        }
-        const uint64_t m = __ballot(in);
-        if (m) {
-            if (P0) {
-                const uint32_t nm = (uint32_t)__popcll(m);
-                nin += nm;
-                const uint32_t pos =
-                    nwb + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                if (in) wb[pos] = x;
-                nwb = __builtin_amdgcn_readfirstlane(nwb + nm);  // uniform: keep it scalar
-            } else if (in) {
-                atomicAdd(&lh[(x - lo) >> s], 1u);
-            }
-        }
-    };
-    auto sweep = [&](auto p0_tag) __attribute__((always_inline)) {
-        constexpr bool P0 = decltype(p0_tag)::value;
-        if (c0 < cend) load(c0, xb, xb3, nj);
-        for (int c = c0; c < cend; c += cstep) {
-            if (c + cstep < cend) load(c + cstep, xn, xn3, nn);
-            const int jb = col0 + c, j = jb + col;
-            // a step appends at most 16 x 64 values
-            if (P0 && nwb + 1024 > kBuf) flush();
-            uint32_t bv[16];
+    const uint32_t wlo = hi - lo;
+    // the bracket in S: bits of -lo/2 and -hi/2
+    const float slo = __uint_as_float(lo) * -0.5f;
+    const uint32_t blo = __float_as_uint(slo), bw = __float_as_uint(__uint_as_float(hi) * -0.5f) - blo;
+    auto dist_bits = [](float S) { return __float_as_uint(fmaxf(-2.0f * S, 0.0f)); };
+    using std::false_type;
+    using std::true_type;
+    auto sweep = [&](auto fast_tag) __attribute__((always_inline)) {
+        constexpr bool FAST = decltype(fast_tag)::value;
+        auto conv = [&](uint32_t x) { return FAST ? dist_bits(__uint_as_float(x)) : x; };
+        int rb = steps.block_of(t0);
+        int64_t before = steps.before(rb);
+        for (int64_t t = t0; t < t1; ++rb) {
+            // columns [c0, cend) of this row block, for this wave
+            const int64_t after = before + steps.cols - (int64_t)steps.per * rb, end = t1 < after ? t1 : after;
+            const int wrow = rb * ROWS + (ROWS == 256 ? 64 * wave : 0);
+            const int off = rb * ROWS + (ROWS == 256 ? 0 : 16 * wave);
+            int c0 = off + (int)(t - before) * cstep;
+            const int cend = off + (int)(end - before) * cstep;
+            t = end;
+            before = after;
+            while (c0 < cend && c0 + 15 <= wrow) c0 += cstep;  // no pair j > i for the wave's rows
+            if (c0 >= cend) continue;
+            float xa[4][KA];
+            bf16x8v xa3[NP][4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                f4v S = f4v{0.f, 0.f, 0.f, 0.f};
                 if constexpr (SPLIT) {
+                    const __bf16* p = v.xs3 + (int64_t)(wrow + 16 * r + col) * 96 + 8 * kq;
 #pragma unroll
-                    for (int e = 0; e < 6; ++e)
-                        S = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa3[kGramPairs3[e][0]][r], xb3[kGramPairs3[e][1]],
-                                                                    S, 0, 0, 0);
+                    for (int q = 0; q < NP; ++q) {
+                        xa3[q][r] = *reinterpret_cast<const bf16x8v*>(p + 32 * q);
+                        if (kq == 3) xa3[q][r][7] = (__bf16)0.0f;
+                    }
                 } else {
+                    const float* p = v.xr + (int64_t)(wrow + 16 * r + col) * (4 * KS) + kq * KS;
 #pragma unroll
-                    for (int k = 0; k < KS; ++k) S = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[r][k], xb[k], S, 0, 0, 0);
+                    for (int k = 0; k < KS; ++k) xa[r][k] = p[k];
                 }
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    bv[4 * r + t] = __float_as_uint(fmaxf(fmaf(-2.0f, S[t], ni[r][t] + nj), 0.0f));
             }
-            if constexpr (SPLIT) {
+            f4v ei[4];  // e_i for i = wrow + 16 r + 4 kq + t
 #pragma unroll
-                for (int q = 0; q < NP; ++q) xb3[q] = xn3[q];
-            } else {
+            for (int r = 0; r < 4; ++r) ei[r] = *reinterpret_cast<const f4v*>(v.nrm + wrow + 16 * r + 4 * kq) * -0.5f;
+            float xb[KA];
+            bf16x8v xb3[NP];
+            float ej = 0.0f;
+            auto step = [&](int c, const float (&xb)[KA], const bf16x8v (&xb3)[NP], float ej) __attribute__((always_inline)) {
+                const int jb = c, j = jb + col;
+                // two row tiles at a time: their products in turn, two chains in
+                // flight beside the other waves', then their sixteen pairs
+                auto tiles = [&](int r0, float (&S)[8]) __attribute__((always_inline)) {
+                    f4v a[2] = {};
+                    if constexpr (SPLIT) {
 #pragma unroll
-                for (int k = 0; k < KS; ++k) xb[k] = xn[k];
-            }
-            nj = nn;
-            if (jb > wrow + 63 && jb + 16 <= N) {  // wave-uniform
+                        for (int e = 0; e < 6; ++e)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) classify(std::true_type{}, p0_tag, bv[e], true);
-                nvalid += 1024;
-            } else {
+                            for (int r = 0; r < 2; ++r)
+                                a[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                    xa3[kGramPairs3[e][0]][r0 + r], xb3[kGramPairs3[e][1]], a[r], 0, 0, 0);
+                    } else {
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int i = wrow + 16 * (e >> 2) + 4 * kq + (e & 3);
-                    classify(std::false_type{}, p0_tag, bv[e], i < N && j < N && j > i);
+                        for (int k = 0; k < KS; ++k)
+#pragma unroll
+                            for (int r = 0; r < 2; ++r)
+                                a[r] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[r0 + r][k], xb[k], a[r], 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int r = 0; r < 2; ++r)
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) S[4 * r + t] = a[r][t] + (ei[r0 + r][t] + ej);
+                };
+                auto classify = [&](auto whole_tag, int r0, const float (&S)[8]) __attribute__((always_inline)) {
+                    constexpr bool WHOLE = decltype(whole_tag)::value;  // every pair of the step is one
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        if (MODE == kPass0 && e % kListStep == 0 && list.full()) flush_lists(v, list, conv);
+                        bool valid = true;
+                        if constexpr (!WHOLE) {
+                            const int i = wrow + 16 * (r0 + (e >> 2)) + 4 * kq + (e & 3);
+                            valid = i < N && j < N && j > i;
+                        }
+                        if (FAST) {
+                            float x = S[e];
+                            if constexpr (!WHOLE) x = valid ? x : -INFINITY;  // above the bracket
+                            // a NaN counts as D = 0, as max(-2 S, 0) does; counted by the scalar unit
+                            list.nb_wave += (uint32_t)__popcll(__ballot(!(x <= slo)));
+                            const uint32_t b = __float_as_uint(x);
+                            list.put(b, b - blo <= bw);
+                        } else {
+                            const uint32_t x = dist_bits(S[e]);
+                            const bool in = valid && x - lo <= wlo;
+                            if (MODE == kPass0) {
+                                list.nb += valid && x < lo ? 1u : 0u;
+                                list.put(x, in);
+                            } else if (in) {
+                                atomicAdd(&lh[(x - lo) >> s], 1u);
+                            }
+                        }
+                    }
+                };
+                const bool whole = FAST && jb > wrow + 63 && jb + 16 <= N;  // wave-uniform
+#pragma unroll
+                for (int r0 = 0; r0 < 4; r0 += 2) {
+                    float S[8];
+                    tiles(r0, S);
+                    if (whole) classify(true_type{}, r0, S);
+                    else classify(false_type{}, r0, S);
                 }
+            };
+            // no prefetch: four waves on a SIMD hide the loads, and a second
+            // operand buffer would not fit their registers
+            for (int c = c0; c < cend; c += cstep) {
+                load(c, xb, xb3, ej);
+                step(c, xb, xb3, ej);
             }
         }
+        if (MODE == kPass0) flush_lists(v, list, conv);
     };
-    if (pass0) {
-        sweep(std::true_type{});
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) nbl += __shfl_xor(nbl, o);
-        nb += __builtin_amdgcn_readfirstlane(nbl);
+    if constexpr (MODE == kPass0) {
+        if (lo >= 0x01000000u && hi < 0x7f800000u) sweep(true_type{});
+        else sweep(false_type{});
     } else {
-        sweep(std::false_type{});
-    }
-    if (!pass0) {
-        __syncthreads();
-        for (int b = tid; b < kMedBins; b += NT)
-            if (lh[b]) atomicAdd(&v.hist[b], lh[b]);
-        return;
-    }
-    // the workgroup's remaining candidates go out under one reservation (the
-    // segment counters are shared by every workgroup: one atomic each)
-    __shared__ uint32_t wn[NT / 64 + 1];
-    if (lane == 0) wn[wave] = nwb;
-    __syncthreads();
-    if (tid == 0) {
-        const uint32_t tot = wn[0] + wn[1] + wn[2] + wn[3];
-        uint32_t base = 0;
-        if (tot) {
-            base = atomicAdd(&sel->seg[seg], tot);
-            if ((uint64_t)base + tot > seg_cap) atomicOr(&sel->overflow, 1u);
-        }
-        wn[NT / 64] = base;
-    }
-    __syncthreads();
-    {
-        uint32_t off = wn[NT / 64];
-        for (int w = 0; w < wave; ++w) off += wn[w];
-        for (uint32_t e = (uint32_t)lane; e < nwb; e += 64)
-            if (off + e < seg_cap) segbuf[off + e] = wb[e];
-    }
-    if (lane == 0) {  // counts of the workgroup
-        red[0][wave] = nb;
-        red[1][wave] = nvalid - nb - nin;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        uint32_t b = 0, a = 0;
-        for (int w = 0; w < NT / 64; ++w) {
-            b += red[0][w];
-            a += red[1][w];
-        }
-        cnt[0] = b;
-        cnt[1] = a;
+        sweep(false_type{});
     }
 }
 
-// Candidate pass: histogram of the candidates in [lo, hi] (sentinels and
-// values outside are skipped); segment g, part `part` of kCandParts.
-__device__ void med_cand_body(const MedView& v, int g, int part) {
+// ---- the passes after pass 0 -------------------------------------------------------
+// blk of nblk workgroups of 256; items(lo, hi, s, lh) histograms this
+// workgroup's share of all pairs.
+//   1: where rank k lies (the bracket's candidates, or, when it lies outside
+//      or a segment overflowed, every pair), and the histogram of that interval;
+//   2: the bin with rank k, and its histogram;
+//   3: the bin with rank k of that; if it is wider than one value (a bracket
+//      of more than 2^22 patterns) the next histogram, which the workgroup that
+//      ends last narrows to the one value left.
+// Every workgroup derives the interval itself from the counts before it, so no
+// launch of a single workgroup sits between the passes.
+struct Interval {
+    uint32_t lo, hi, rank;
+};
+
+template <class Items>
+__device__ __forceinline__ void pass_values(const MedView& v, int blk, int nblk, bool all, const Interval& I, uint32_t s,
+                                            uint32_t* lh, Items&& items) {
+    if (all) {
+        items(I.lo, I.hi, s, lh);
+        return;
+    }
+    const int parts = nblk / kCandSegs, g = blk / parts, part = blk % parts;
+    const uint32_t got = (uint32_t)v.sel->seg[g][0];
+    const uint32_t n = got < v.seg_cap ? got : v.seg_cap;
+    const uint32_t per = ((n + parts - 1) / parts + 3) & ~3u, b0 = (uint32_t)part * per;
+    if (b0 >= n) return;
+    wide_hist(v.cand + (size_t)g * v.seg_cap + b0, b0 + per < n ? per : n - b0, I.lo, I.hi, s, lh);
+}
+
+// The interval's bin with rank I.rank in the histogram h (shift s), by the
+// workgroup; the number of values in it.
+__device__ __forceinline__ uint32_t narrow_from(const uint32_t* __restrict__ h, uint32_t s, Interval& I, uint32_t* lh,
+                                                uint32_t* wt, uint32_t* part) {
+    for (int b = threadIdx.x; b < kMedBins; b += 256) lh[b] = h[b];
+    return wg_narrow<256>(lh, wt, part, s, I.lo, I.hi, I.rank);
+}
+
+template <class Items>
+__device__ __forceinline__ void med_pass(const MedView& v, int pass, int blk, int nblk, float* h_out, Items&& items) {
     __shared__ uint32_t lh[kMedBins];
-    const SelState* sel = v.sel;
-    if (sel->mode != kModeCand) return;
-    const uint32_t lo = sel->lo, hi = sel->hi, s = sel->shift;
-    const uint32_t seg_cap = v.cap / kCandSegs;
-    const uint32_t n = sel->seg[g] < seg_cap ? sel->seg[g] : seg_cap;
-    const uint32_t* segbuf = v.cand + (size_t)g * seg_cap;
-    for (int b = threadIdx.x; b < kMedBins; b += 256) lh[b] = 0;
-    __syncthreads();
-    const uint32_t per = (n + kCandParts - 1) / kCandParts;  // this part's slice of the segment
-    const uint32_t b0 = (uint32_t)part * per;
-    if (b0 < n) wg_hist<256>(segbuf + b0, (b0 + per < n ? per : n - b0), lo, hi, s, lh);
-    __syncthreads();
-    for (int b = threadIdx.x; b < kMedBins; b += 256)
-        if (lh[b]) atomicAdd(&v.hist[b], lh[b]);
-}
-
-// Select step (one workgroup of 256).  After pass 0: is rank k under, in or
-// over the bracket?  After a histogram pass: the bin holding the rank.  The
-// histogram is cleared for the next pass; h is set once the interval is one
-// value.
-__device__ void med_select_body(const MedView& v, float* h_out) {
-    constexpr int PER = kMedBins / 256;
-    __shared__ uint32_t psum[256];
-    __shared__ uint32_t tot[2];
-    const int tid = threadIdx.x;
+    __shared__ __align__(16) uint32_t wt[4];
+    __shared__ uint32_t part[4];
     SelState* sel = v.sel;
-    const uint32_t mode = sel->mode;
-    if (mode == kModeDone) return;
-    const uint32_t lo = sel->lo, hi = sel->hi, s = sel->shift;
-    const uint32_t r = sel->rank;
-    if (mode == kModePass0) {
-        // sum the items' counts in a fixed order, sixteen 8-byte loads in
-        // flight per thread (this step waits on memory, often beside a
-        // bandwidth-bound rollout)
-        const int items = v.rb * v.cc;
-        const uint2* cnt2 = reinterpret_cast<const uint2*>(v.cnt);
-        uint32_t cb = 0, ca = 0;
-        for (int e = tid; e < items; e += 256 * 16) {
-            uint2 q[16];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) q[u] = cnt2[min(e + 256 * u, items - 1)];
-#pragma unroll
-            for (int u = 0; u < 16; ++u)
-                if (e + 256 * u < items) {
-                    cb += q[u].x;
-                    ca += q[u].y;
-                }
+    if (sel->mode != kModePass0) return;
+    const int tid = threadIdx.x;
+    auto flush = [&](uint32_t* h) {
+        __syncthreads();
+        for (int b = tid; b < kMedBins; b += 256)
+            if (lh[b]) atomicAdd(&h[b], lh[b]);
+    };
+    if (pass == 1) {
+        const uint32_t seg_cap = v.seg_cap;
+        const unsigned long long q = sel->seg[tid & 63][0];
+        static_assert(kCandSegs == 64, "a lane per segment");
+        const uint32_t inside = wave_sum((uint32_t)q), below = wave_sum((uint32_t)(q >> 32));
+        bool all = __any((uint32_t)q > seg_cap);
+        Interval I{sel->lo, sel->hi, sel->rank};
+        if (I.rank <= below) {
+            all = true;
+            I.hi = I.lo - 1;
+            I.lo = 0;
+        } else if (I.rank > below + inside) {
+            all = true;
+            I.rank -= below + inside;
+            I.lo = I.hi + 1;
+            I.hi = 0xffffffffu;
+        } else {
+            I.rank -= below;
         }
-        for (int k = 0; k < 2; ++k) {
-            psum[tid] = k == 0 ? cb : ca;
-            __syncthreads();
-            for (int w = 128; w > 0; w >>= 1) {
-                if (tid < w) psum[tid] += psum[tid + w];
-                __syncthreads();
-            }
-            if (tid == 0) tot[k] = psum[0];
-            __syncthreads();
+        if (blk == 0 && tid == 0) {
+            sel->lo1 = I.lo;
+            sel->hi1 = I.hi;
+            sel->rank1 = I.rank;
+            sel->all = all;
         }
-        if (tid == 0) {
-            const uint32_t below = tot[0], above = tot[1];
-            const uint32_t inside = (uint32_t)(pair_count(v.N) - below - above);
-            if (r <= below) {  // under the bracket: every pair again over [0, lo - 1]
-                sel->hi = lo - 1;
-                sel->lo = 0;
-                sel->shift = shift_for((uint64_t)lo);
-                sel->mode = kModeAll;
-            } else if (r > below + inside) {  // over it: over [hi + 1, 0xffffffff]
-                sel->rank = r - below - inside;
-                sel->lo = hi + 1;
-                sel->hi = 0xffffffffu;
-                sel->shift = shift_for((uint64_t)0xffffffffu - hi);
-                sel->mode = kModeAll;
-            } else {
-                sel->rank = r - below;
-                sel->mode = sel->overflow ? kModeAll : kModeCand;
-            }
-        }
+        if (I.lo == I.hi) return;
+        for (int b = tid; b < kMedBins; b += 256) lh[b] = 0;
+        __syncthreads();
+        pass_values(v, blk, nblk, all, I, shift_for((uint64_t)I.hi - I.lo + 1), lh, items);
+        flush(v.hist);
         return;
     }
-    uint32_t loc[PER];
-    uint32_t sum = 0;
-    for (int q = 0; q < PER; ++q) {
-        loc[q] = v.hist[tid * PER + q];
-        v.hist[tid * PER + q] = 0;
-        sum += loc[q];
-    }
-    psum[tid] = sum;
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {  // inclusive scan
-        const uint32_t x = tid >= off ? psum[tid - off] : 0;
-        __syncthreads();
-        psum[tid] += x;
-        __syncthreads();
-    }
-    const uint32_t incl = psum[tid], excl = incl - sum;
-    if (excl < r && r <= incl) {
-        uint32_t c = excl;
-        for (int q = 0; q < PER; ++q) {
-            if (c < r && r <= c + loc[q]) {
-                const uint64_t nlo = (uint64_t)lo + ((uint64_t)(tid * PER + q) << s);
-                const uint64_t top = nlo + ((uint64_t)1 << s) - 1;
-                const uint64_t nhi = top < (uint64_t)hi ? top : (uint64_t)hi;
-                sel->rank = r - c;
-                sel->lo = (uint32_t)nlo;
-                sel->hi = (uint32_t)nhi;
-                if (nlo == nhi) set_bandwidth(sel, v.N, (uint32_t)nlo, h_out);
-                else sel->shift = shift_for(nhi - nlo + 1);
-                break;
-            }
-            c += loc[q];
+    const bool all = sel->all != 0;
+    Interval I{sel->lo1, sel->hi1, sel->rank1};
+    if (pass == 2) {
+        if (I.lo == I.hi) return;
+        narrow_from(v.hist, shift_for((uint64_t)I.hi - I.lo + 1), I, lh, wt, part);  // clears lh
+        if (blk == 0 && tid == 0) {
+            sel->lo2 = I.lo;
+            sel->hi2 = I.hi;
+            sel->rank2 = I.rank;
         }
+        if (I.lo == I.hi) return;
+        pass_values(v, blk, nblk, all, I, shift_for((uint64_t)I.hi - I.lo + 1), lh, items);
+        flush(v.hist + kMedBins);
+        return;
     }
+    if (I.lo != I.hi) I = Interval{sel->lo2, sel->hi2, sel->rank2};
+    if (I.lo != I.hi) narrow_from(v.hist + kMedBins, shift_for((uint64_t)I.hi - I.lo + 1), I, lh, wt, part);
+    if (I.lo == I.hi) {
+        if (blk == 0 && tid == 0) set_bandwidth(sel, v.N, I.lo, h_out);
+        return;
+    }
+    const uint32_t s = shift_for((uint64_t)I.hi - I.lo + 1);
+    pass_values(v, blk, nblk, all, I, s, lh, items);
+    flush(v.hist + 2 * kMedBins);
+    __threadfence();  // this workgroup's counts before its arrival
+    __syncthreads();
+    if (tid == 0) part[3] = atomicAdd(&sel->arrived, 1u);
+    __syncthreads();
+    if (part[3] != (uint32_t)nblk - 1) return;
+    __threadfence();
+    for (int b = tid; b < kMedBins; b += 256) lh[b] = __hip_atomic_load(&v.hist[2 * kMedBins + b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    wg_narrow<256>(lh, wt, part, s, I.lo, I.hi, I.rank);
+    if (tid == 0) set_bandwidth(sel, v.N, I.lo, h_out);
 }
-
 
 // Small problems (P <= kFinishPairs): everything after pass 0 in one
 // workgroup of kFinishThreads.  The counts decide where rank k lies.  Inside
@@ -942,7 +935,7 @@ constexpr uint64_t kFinishPairs = 1ull << 20;
 // all-pairs passes (when the caller provides the operands); smaller ones keep
 // direct differences, in the single-problem and the batched paths alike, so
 // both reach the same bandwidth bit for bit.
-__host__ __device__ __forceinline__ bool med_gram(int N) { return pair_count(N) > kFinishPairs; }
+__host__ __device__ __forceinline__ bool med_takes_gram(int N) { return pair_count(N) > kFinishPairs; }
 constexpr int kFinishThreads = 1024;
 constexpr int kFinishRegs = 40;         // candidate slots per thread held in registers
 constexpr int kSegThreads = kFinishThreads / kCandSegs;
@@ -959,21 +952,17 @@ __device__ void med_finish_body(const MedView& v, const float* __restrict__ thet
     const int N = v.N, d = v.d;
     uint32_t lo = sel->lo, hi = sel->hi;
     uint32_t r = sel->rank;
-    uint32_t b = 0, a = 0;
-    for (int e = tid; e < v.rb * v.cc; e += NT) {
-        b += v.cnt[2 * e];
-        a += v.cnt[2 * e + 1];
-    }
-    const uint32_t below = wg_sum<NT>(b, wt), above = wg_sum<NT>(a, wt);
-    const uint32_t inside = (uint32_t)(pair_count(N) - below - above);
+    const uint32_t seg_cap = v.seg_cap;
+    const unsigned long long q64 = sel->seg[tid & 63][0];
+    const uint32_t inside = wave_sum((uint32_t)q64), below = wave_sum((uint32_t)(q64 >> 32));
+    const bool overflow = __any((uint32_t)q64 > seg_cap);
     for (int q = tid; q < kMedBins; q += NT) lh[q] = 0;
     __syncthreads();
-    if (r > below && r <= below + inside && !sel->overflow) {
+    if (r > below && r <= below + inside && !overflow) {
         // select among the candidates in [lo, hi] (sentinels lie above hi)
         r -= below;
-        const uint32_t seg_cap = v.cap / kCandSegs;
         const int g = tid / kSegThreads, sub = tid % kSegThreads;
-        const uint32_t n = sel->seg[g] < seg_cap ? sel->seg[g] : seg_cap;
+        const uint32_t n = (uint32_t)sel->seg[g][0];
         const uint32_t* sb = v.cand + (size_t)g * seg_cap;
         // the first kFinishRegs * kSegThreads slots of each segment stay in
         // registers (one load round trip); longer segments stream the rest
@@ -1031,6 +1020,37 @@ __device__ void med_finish_body(const MedView& v, const float* __restrict__ thet
     if (tid == 0) set_bandwidth(sel, N, lo, h_out);
 }
 
+// The items with a pair i < j, counted column group by column group (`width`
+// columns a group, a multiple of `rows` or a divisor): below(g) = items of the
+// groups before g, whose items are their first row blocks.  The grid holds
+// only these: workgroups go to the shader engines in turn, whether or not an
+// engine is free, and a (row block, column group) grid, half of it below the
+// diagonal, gives one engine up to three times the items of another (the Gram
+// form of N = 16384 on such a grid took 102 us, on a list like this 82).
+struct ItemList {
+    int rows, width, rb, groups;
+    __host__ __device__ int64_t below(int64_t g) const {
+        if (width >= rows) return (width / rows) * (g * (g + 1) / 2);
+        const int64_t m = rows / width, q = g / m;
+        return m * (q * (q + 1) / 2) + (g % m) * (q + 1);
+    }
+    __host__ __device__ int64_t count() const {
+        const int64_t last = below(groups) - below(groups - 1);
+        return below(groups - 1) + (last < rb ? last : rb);
+    }
+    // item t's row block and column group
+    __device__ void at(int64_t t, int& r, int& g) const {
+        g = (int)sqrtf(2.0f * (float)rows / (float)width * (float)t);
+        while (g > 0 && below(g) > t) --g;
+        while (below(g + 1) <= t) ++g;
+        r = (int)(t - below(g));
+    }
+};
+
+__host__ __device__ __forceinline__ ItemList item_list(int rows, int rb, int cc) {
+    return ItemList{rows, kMedCols, rb, cc};
+}
+
 // ---- single-problem kernels -----------------------------------------------------
 struct OneMed {
     int N, d;
@@ -1053,20 +1073,51 @@ __global__ __launch_bounds__(kSelThreads) void k_sample_select(OneMed a, int exa
 
 template <int DP, int ROWS>
 __global__ __launch_bounds__(256) void k_med_items(OneMed a, const float* theta) {
-    med_item<DP, ROWS>(med_view(a.N, a.d, a.fixed_h, a.L, a.ws), theta, blockIdx.y, blockIdx.x);
+    const MedView v = med_view(a.N, a.d, a.fixed_h, a.L, a.ws);
+    if (v.sel->mode != kModePass0) return;
+    int rb, g;
+    item_list(ROWS, v.rb, v.cc).at(blockIdx.x, rb, g);
+    med_item<DP, ROWS, kPass0>(v, theta, rb, g, v.sel->lo, v.sel->hi, 0, nullptr);
 }
 
 template <int KS, int ROWS>
-__global__ __launch_bounds__(256) void k_med_items_gram(OneMed a) {
-    med_item_gram<KS, ROWS>(med_view(a.N, a.d, a.fixed_h, a.L, a.ws), blockIdx.y, blockIdx.x * kGramGroup);
+__device__ __forceinline__ void gram_pass0(const MedView& v, int blk, int nblk) {
+    if (v.sel->mode != kModePass0) return;
+    med_gram<KS, ROWS, kPass0>(v, blk, nblk, v.sel->lo, v.sel->hi, 0, nullptr);
 }
 
-__global__ __launch_bounds__(256) void k_med_cand(OneMed a) {
-    med_cand_body(med_view(a.N, a.d, a.fixed_h, a.L, a.ws), blockIdx.x / kCandParts, blockIdx.x % kCandParts);
+template <int KS, int ROWS>
+__global__ __launch_bounds__(256, 4) void k_med_items_gram(OneMed a) {
+    const MedView v = med_view(a.N, a.d, a.fixed_h, a.L, a.ws);
+    gram_pass0<KS, ROWS>(v, blockIdx.x, gridDim.x);
 }
 
-__global__ __launch_bounds__(256) void k_med_select(OneMed a, float* h_out) {
-    med_select_body(med_view(a.N, a.d, a.fixed_h, a.L, a.ws), h_out);
+// passes 1..3 (grid: a multiple of kCandSegs workgroups)
+template <int DP, int ROWS>
+__global__ __launch_bounds__(256) void k_med_pass(OneMed a, const float* theta, int pass, float* h_out) {
+    const MedView v = med_view(a.N, a.d, a.fixed_h, a.L, a.ws);
+    med_pass(v, pass, blockIdx.x, gridDim.x, h_out,
+             [&](uint32_t lo, uint32_t hi, uint32_t s, uint32_t* lh) {
+                 const ItemList l = item_list(ROWS, v.rb, v.cc);
+                 const int64_t n = l.count();
+                 for (int64_t it = blockIdx.x; it < n; it += gridDim.x) {
+                     int rb, g;
+                     l.at(it, rb, g);
+                     med_item<DP, ROWS, kPassHist>(v, theta, rb, g, lo, hi, s, lh);
+                 }
+             });
+}
+
+template <int KS, int ROWS>
+__device__ __forceinline__ void gram_pass(const MedView& v, int pass, int blk, int nblk, float* h_out) {
+    med_pass(v, pass, blk, nblk, h_out, [&](uint32_t lo, uint32_t hi, uint32_t s, uint32_t* lh) {
+        med_gram<KS, ROWS, kPassHist>(v, blk, nblk, lo, hi, s, lh);
+    });
+}
+
+template <int KS, int ROWS>
+__global__ __launch_bounds__(256) void k_med_pass_gram(OneMed a, int pass, float* h_out) {
+    gram_pass<KS, ROWS>(med_view(a.N, a.d, a.fixed_h, a.L, a.ws), pass, blockIdx.x, gridDim.x, h_out);
 }
 
 __global__ __launch_bounds__(kFinishThreads) void k_med_finish(OneMed a, const float* theta, float* h_out) {
@@ -1126,28 +1177,25 @@ __global__ __launch_bounds__(256) void k_med_items_batched(const ProblemDesc* __
                                                             char* ws) {
     const int4 w = work[blockIdx.x];
     const ProblemDesc& D = descs[w.x];
-    med_item<DP, ROWS>(med_of(D, ws), theta + D.theta_off, w.y, w.z);
+    const MedView v = med_of(D, ws);
+    if (v.sel->mode != kModePass0) return;
+    med_item<DP, ROWS, kPass0>(v, theta + D.theta_off, w.y, w.z, v.sel->lo, v.sel->hi, 0, nullptr);
 }
 
+// entry = (problem, row block, first column chunk of the item, -)
 template <int KS, int ROWS>
-__global__ __launch_bounds__(256) void k_med_items_gram_batched(const ProblemDesc* __restrict__ descs,
+__global__ __launch_bounds__(256, 4) void k_med_items_gram_batched(const ProblemDesc* __restrict__ descs,
                                                                  const int4* __restrict__ work, char* ws) {
     const int4 w = work[blockIdx.x];
-    const ProblemDesc& D = descs[w.x];
-    // the entry that starts a group of kGramGroup column chunks runs them all
-    if (w.z % kGramGroup != 0) return;
-    med_item_gram<KS, ROWS>(med_of(D, ws), w.y, w.z);
+    gram_pass0<KS, ROWS>(med_of(descs[w.x], ws), w.y, w.z);
 }
 
-// entry = (problem, segment, part, -)
-__global__ __launch_bounds__(256) void k_med_cand_batched(const ProblemDesc* __restrict__ descs,
-                                                          const int4* __restrict__ work, char* ws) {
+// entry = (problem, workgroup, workgroups, -)
+template <int KS, int ROWS>
+__global__ __launch_bounds__(256) void k_med_pass_gram_batched(const ProblemDesc* __restrict__ descs,
+                                                                const int4* __restrict__ work, char* ws, int pass) {
     const int4 w = work[blockIdx.x];
-    med_cand_body(med_of(descs[w.x], ws), w.y, w.z);
-}
-
-__global__ __launch_bounds__(256) void k_med_select_batched(const ProblemDesc* __restrict__ descs, char* ws) {
-    med_select_body(med_of(descs[blockIdx.x], ws), nullptr);
+    gram_pass<KS, ROWS>(med_of(descs[w.x], ws), pass, w.y, w.z, nullptr);
 }
 
 // entry = (problem, -, -, -) of a problem of 2^20 pairs at most: the select
@@ -1159,82 +1207,67 @@ __global__ __launch_bounds__(kFinishThreads) void k_med_finish_batched(const Pro
     med_finish_body(med_of(D, ws), theta + D.theta_off, nullptr);
 }
 
-template <int ROWS>
-void launch_items_rows(const OneMed& a, const float* theta, hipStream_t st) {
-    const dim3 grid(a.L.med_cc, a.L.med_rb);
-    const int dp = med_dp(a.d);
-    if (dp == 16) hipLaunchKernelGGL((k_med_items<16, ROWS>), grid, dim3(256), 0, st, a, theta);
-    else if (dp == 32) hipLaunchKernelGGL((k_med_items<32, ROWS>), grid, dim3(256), 0, st, a, theta);
-    else hipLaunchKernelGGL((k_med_items<64, ROWS>), grid, dim3(256), 0, st, a, theta);
+// f(padded dimension, rows) as constants
+template <class F>
+void by_item_shape(int d, int rows, F&& f) {
+    auto dp = [&](auto r) {
+        switch (med_dp(d)) {
+            case 16: f(std::integral_constant<int, 16>{}, r); break;
+            case 32: f(std::integral_constant<int, 32>{}, r); break;
+            default: f(std::integral_constant<int, 64>{}, r); break;
+        }
+    };
+    if (rows == 64) dp(std::integral_constant<int, 64>{});
+    else dp(std::integral_constant<int, 256>{});
 }
 
-void launch_items(const OneMed& a, const float* theta, hipStream_t st) {
-    if (a.L.med_rows == 64) launch_items_rows<64>(a, theta, st);
-    else launch_items_rows<256>(a, theta, st);
+// f(Gram k-steps (0: split form), rows) as constants, by med_gram_ks
+template <class F>
+void by_gram_shape(int ks, int rows, F&& f) {
+    auto k = [&](auto r) {
+        switch (ks) {
+            case 0: f(std::integral_constant<int, 0>{}, r); break;
+            case 8: f(std::integral_constant<int, 8>{}, r); break;
+            case 10: f(std::integral_constant<int, 10>{}, r); break;
+            case 12: f(std::integral_constant<int, 12>{}, r); break;
+            case 14: f(std::integral_constant<int, 14>{}, r); break;
+            default: f(std::integral_constant<int, 16>{}, r); break;
+        }
+    };
+    if (rows == 64) k(std::integral_constant<int, 64>{});
+    else k(std::integral_constant<int, 256>{});
 }
 
-template <int KS>
-void launch_items_gram_ks(const OneMed& a, hipStream_t st) {
-    const dim3 grid((a.L.med_cc + kGramGroup - 1) / kGramGroup, a.L.med_rb);
-    if (a.L.med_rows == 64) hipLaunchKernelGGL((k_med_items_gram<KS, 64>), grid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((k_med_items_gram<KS, 256>), grid, dim3(256), 0, st, a);
-}
-
-void launch_items_gram(const OneMed& a, hipStream_t st) {
-    if (a.L.split3) {
-        launch_items_gram_ks<0>(a, st);
-        return;
-    }
-    switch (a.L.ks32) {
-        case 2: launch_items_gram_ks<2>(a, st); break;
-        case 4: launch_items_gram_ks<4>(a, st); break;
-        case 6: launch_items_gram_ks<6>(a, st); break;
-        case 8: launch_items_gram_ks<8>(a, st); break;
-        case 10: launch_items_gram_ks<10>(a, st); break;
-        case 12: launch_items_gram_ks<12>(a, st); break;
-        case 14: launch_items_gram_ks<14>(a, st); break;
-        default: launch_items_gram_ks<16>(a, st); break;
-    }
-}
-
-// each item shape's work list, in its own launch
-template <int DP, int ROWS>
-void launch_direct_list(const BatchPlan& P, const ProblemDesc* descs, const float* theta, char* ws, hipStream_t st) {
-    const int c = med_class(DP, ROWS);
-    if (P.dist_n[c])
-        hipLaunchKernelGGL((k_med_items_batched<DP, ROWS>), dim3(P.dist_n[c]), dim3(256), 0, st, descs,
-                           P.dist_work + P.dist_start[c], theta, ws);
-}
-
-template <int KS>
-void launch_gram_lists(const BatchPlan& P, const ProblemDesc* descs, char* ws, hipStream_t st) {
-    const int c64 = med_gram_list(KS, 64), c256 = med_gram_list(KS, 256);
-    if (P.dist_n[c64])
-        hipLaunchKernelGGL((k_med_items_gram_batched<KS, 64>), dim3(P.dist_n[c64]), dim3(256), 0, st, descs,
-                           P.dist_work + P.dist_start[c64], ws);
-    if (P.dist_n[c256])
-        hipLaunchKernelGGL((k_med_items_gram_batched<KS, 256>), dim3(P.dist_n[c256]), dim3(256), 0, st, descs,
-                           P.dist_work + P.dist_start[c256], ws);
-}
-
+// pass 0 over the items of every shape present, each from its own work list
 void launch_items_batched(const BatchPlan& P, const ProblemDesc* descs, const float* theta, char* ws,
                           hipStream_t st) {
-    if (!P.n_dist) return;
-    launch_direct_list<16, 64>(P, descs, theta, ws, st);
-    launch_direct_list<32, 64>(P, descs, theta, ws, st);
-    launch_direct_list<64, 64>(P, descs, theta, ws, st);
-    launch_direct_list<16, 256>(P, descs, theta, ws, st);
-    launch_direct_list<32, 256>(P, descs, theta, ws, st);
-    launch_direct_list<64, 256>(P, descs, theta, ws, st);
-    launch_gram_lists<0>(P, descs, ws, st);
-    launch_gram_lists<2>(P, descs, ws, st);
-    launch_gram_lists<4>(P, descs, ws, st);
-    launch_gram_lists<6>(P, descs, ws, st);
-    launch_gram_lists<8>(P, descs, ws, st);
-    launch_gram_lists<10>(P, descs, ws, st);
-    launch_gram_lists<12>(P, descs, ws, st);
-    launch_gram_lists<14>(P, descs, ws, st);
-    launch_gram_lists<16>(P, descs, ws, st);
+    for (int rows : {64, 256}) {
+        for (int d : {16, 32, 64})
+            by_item_shape(d, rows, [&](auto dp, auto r) {
+                const int c = med_class(dp.value, r.value);
+                if (P.dist_n[c])
+                    hipLaunchKernelGGL((k_med_items_batched<dp.value, r.value>), dim3(P.dist_n[c]), dim3(256), 0, st,
+                                       descs, P.dist_work + P.dist_start[c], theta, ws);
+            });
+        for (int ks : {0, 8, 10, 12, 14, 16})
+            by_gram_shape(ks, rows, [&](auto k, auto r) {
+                const int c = med_gram_list(k.value, r.value);
+                if (P.dist_n[c])
+                    hipLaunchKernelGGL((k_med_items_gram_batched<k.value, r.value>), dim3(P.dist_n[c]), dim3(256), 0,
+                                       st, descs, P.dist_work + P.dist_start[c], ws);
+            });
+    }
+}
+
+void launch_pass_batched(const BatchPlan& P, const ProblemDesc* descs, char* ws, int pass, hipStream_t st) {
+    for (int rows : {64, 256})
+        for (int ks : {0, 8, 10, 12, 14, 16})
+            by_gram_shape(ks, rows, [&](auto k, auto r) {
+                const int c = med_gram_list(k.value, r.value) - kMedDirect;
+                if (P.pass_n[c])
+                    hipLaunchKernelGGL((k_med_pass_gram_batched<k.value, r.value>), dim3(P.pass_n[c]), dim3(256), 0, st,
+                                       descs, P.pass_work + P.pass_start[c], ws, pass);
+            });
 }
 
 }  // namespace
@@ -1250,20 +1283,26 @@ hipError_t launch_median(int N, int d, const float* theta, float bandwidth, int 
     if (exact && N >= 2 && !(bandwidth > 0.0f) && pair_count(N) > (uint64_t)kMedSample) {
         // pass 0; small problems keep direct differences, whose every-pair
         // fallback lives in the finishing workgroup
-        const bool small = !med_gram(N);
-        if (gram && !small) launch_items_gram(a, st);
-        else launch_items(a, theta, st);
-        if (small) {  // one workgroup finishes
-            hipLaunchKernelGGL(k_med_finish, dim3(1), dim3(kFinishThreads), 0, st, a, theta, h_out);
-            return hipGetLastError();
-        }
-        hipLaunchKernelGGL(k_med_select, dim3(1), dim3(256), 0, st, a, h_out);
-        for (int pass = 0; pass < 3; ++pass) {
-            hipLaunchKernelGGL(k_med_cand, dim3(kCandSegs * kCandParts), dim3(256), 0, st, a);
-            if (gram) launch_items_gram(a, st);
-            else launch_items(a, theta, st);
-            hipLaunchKernelGGL(k_med_select, dim3(1), dim3(256), 0, st, a, h_out);
-        }
+        const bool small = !med_takes_gram(N);
+        if (gram && !small)
+            by_gram_shape(med_gram_ks(L), L.med_rows, [&](auto k, auto r) {
+                hipLaunchKernelGGL((k_med_items_gram<k.value, r.value>), dim3(med_gram_groups(N)), dim3(256), 0, st, a);
+                for (int pass = 1; pass <= 3; ++pass)
+                    hipLaunchKernelGGL((k_med_pass_gram<k.value, r.value>), dim3(med_pass_groups(N)), dim3(256), 0, st,
+                                       a, pass, h_out);
+            });
+        else
+            by_item_shape(d, L.med_rows, [&](auto dp, auto r) {
+                const int64_t items = item_list(r.value, L.med_rb, L.med_cc).count();
+                hipLaunchKernelGGL((k_med_items<dp.value, r.value>), dim3((uint32_t)items), dim3(256), 0, st, a, theta);
+                if (small) {  // one workgroup finishes
+                    hipLaunchKernelGGL(k_med_finish, dim3(1), dim3(kFinishThreads), 0, st, a, theta, h_out);
+                    return;
+                }
+                for (int pass = 1; pass <= 3; ++pass)
+                    hipLaunchKernelGGL((k_med_pass<dp.value, r.value>), dim3(med_pass_groups(N)), dim3(256), 0, st, a,
+                                       theta, pass, h_out);
+            });
     }
     return hipGetLastError();
 }
@@ -1283,22 +1322,13 @@ hipError_t launch_median_batched(const BatchPlan& P, const ProblemDesc* descs, c
     hipLaunchKernelGGL(k_med_dist_batched, dim3(kMedSample / 64, np), dim3(256), 0, st, descs, theta, ws);
     hipLaunchKernelGGL(k_sample_select_batched, dim3(np), dim3(kSelThreads), 0, st, descs, ws, exact);
     if (exact && P.n_dist) {
-        auto items = [&]() { launch_items_batched(P, descs, theta, ws, st); };
-        items();
-        // problems of 2^20 pairs at most end in one workgroup each; the larger
-        // ones take the select and the candidate passes (which skip the
-        // problems already done)
+        launch_items_batched(P, descs, theta, ws, st);
+        // problems of 2^20 pairs at most end in one workgroup each, the larger
+        // ones in the passes
         if (P.n_fin)
             hipLaunchKernelGGL(k_med_finish_batched, dim3(P.n_fin), dim3(kFinishThreads), 0, st, descs, P.fin_work,
                                theta, ws);
-        if (P.n_cand) {
-            hipLaunchKernelGGL(k_med_select_batched, dim3(np), dim3(256), 0, st, descs, ws);
-            for (int pass = 0; pass < 3; ++pass) {
-                hipLaunchKernelGGL(k_med_cand_batched, dim3(P.n_cand), dim3(256), 0, st, descs, P.cand_work, ws);
-                items();
-                hipLaunchKernelGGL(k_med_select_batched, dim3(np), dim3(256), 0, st, descs, ws);
-            }
-        }
+        for (int pass = 1; pass <= 3; ++pass) launch_pass_batched(P, descs, ws, pass, st);
     }
     return hipGetLastError();
 }

@@ -256,12 +256,13 @@ constexpr int kMaxSvgdN = 65536;
 struct SolvePlan {
     std::vector<stamp::ProblemDesc> descs;
     std::vector<int2> roll_tiles, adj_tiles;  // forward and adjoint rollout tiles (their layouts may differ)
-    std::vector<int4> dist_work, cand_work, fin_work, red_work;
+    std::vector<int4> dist_work, pass_work, fin_work, red_work;
     std::vector<int4> phi_work[kPhi32Classes];
     std::vector<int4> ctr_work, row16_work, phi16_work[2];  // BF16 form
     int phi_rows = 256;
     int dist_start[kMedLists] = {}, dist_n[kMedLists] = {};  // dist_work sorted by item shape
-    size_t clk_off = 0, desc_off = 0, roll_off = 0, adj_tiles_off = 0, dist_off = 0, cand_off = 0, fin_off = 0,
+    int pass_start[kMedGram] = {}, pass_n[kMedGram] = {};    // pass_work by Gram shape
+    size_t clk_off = 0, desc_off = 0, roll_off = 0, adj_tiles_off = 0, dist_off = 0, pass_off = 0, fin_off = 0,
            red_off = 0;
     size_t ctr16_off = 0, row16_off = 0, phi16_off[2] = {};
     size_t phi_off[kPhi32Classes] = {};
@@ -286,7 +287,7 @@ void build_plan(int n, const stamp_scene* scenes, const int32_t* N, int K, float
     size_t sv = 0;
     char buf[64];
     P.key.clear();
-    std::vector<int4> dist_lists[kMedLists];
+    std::vector<int4> dist_lists[kMedLists], pass_lists[kMedGram];
     for (int p = 0; p < n; ++p) {
         ProblemDesc& D = P.descs[p];
         memset(&D, 0, sizeof D);
@@ -310,19 +311,22 @@ void build_plan(int n, const stamp_scene* scenes, const int32_t* N, int K, float
         snprintf(buf, sizeof buf, "%d/%d/%d/%d;", N[p], s->H, s->B, s->T);
         P.key += buf;
         // median passes over all pairs, for problems whose pairs exceed the sample:
-        // every (row block, column chunk) item (items without a pair i < j write
-        // zero counts), and (segment, part) of the candidate passes
+        // (row block, column chunk) items, and the workgroups of the later passes
         if (D.N >= 2 && !(bandwidth > 0.0f) && (uint64_t)D.N * (uint64_t)(D.N - 1) / 2 > (uint64_t)kMedSample) {
             // problems above 2^20 pairs take the Gram form (median.hip)
             const bool gram = (uint64_t)D.N * (uint64_t)(D.N - 1) / 2 > (1ull << 20);
-            const int c = gram ? med_gram_list(D.sv.split3 ? 0 : D.sv.ks32, D.sv.med_rows)
+            const int c = gram ? med_gram_list(med_gram_ks(D.sv), D.sv.med_rows)
                                : med_class(med_dp(D.d), D.sv.med_rows);
-            for (int rb = 0; rb < D.sv.med_rb; ++rb)
-                for (int cc = 0; cc < D.sv.med_cc; ++cc) dist_lists[c].push_back(make_int4(p, rb, cc, 0));
             if (gram) {
-                for (int g = 0; g < kCandSegs; ++g)
-                    for (int q = 0; q < kCandParts; ++q) P.cand_work.push_back(make_int4(p, g, q, 0));
+                const int ni = med_gram_groups(D.N);
+                for (int q = 0; q < ni; ++q) dist_lists[c].push_back(make_int4(p, q, ni, 0));
+                const int nb = med_pass_groups(D.N);
+                for (int q = 0; q < nb; ++q) pass_lists[c - kMedDirect].push_back(make_int4(p, q, nb, 0));
             } else {
+                for (int rb = 0; rb < D.sv.med_rb; ++rb)  // items with a pair i < j only
+                    for (int cc = 0; cc < D.sv.med_cc; ++cc)
+                        if ((cc + 1) * kMedCols > rb * D.sv.med_rows + 1)
+                            dist_lists[c].push_back(make_int4(p, rb, cc, 0));
                 P.fin_work.push_back(make_int4(p, 0, 0, 0));
             }
         }
@@ -366,6 +370,11 @@ void build_plan(int n, const stamp_scene* scenes, const int32_t* N, int K, float
         P.dist_n[c] = (int)dist_lists[c].size();
         P.dist_work.insert(P.dist_work.end(), dist_lists[c].begin(), dist_lists[c].end());
     }
+    for (int c = 0; c < kMedGram; ++c) {
+        P.pass_start[c] = (int)P.pass_work.size();
+        P.pass_n[c] = (int)pass_lists[c].size();
+        P.pass_work.insert(P.pass_work.end(), pass_lists[c].begin(), pass_lists[c].end());
+    }
     // The contraction lists get the room of their longest form (64-row
     // blocks), so that no region of the workspace moves when the row block
     // changes: pointers into it stay valid across every launch shape.
@@ -386,7 +395,7 @@ void build_plan(int n, const stamp_scene* scenes, const int32_t* N, int K, float
     P.roll_off = take(P.roll_tiles.size() * sizeof(int2));
     P.adj_tiles_off = take(P.adj_tiles.size() * sizeof(int2));
     P.dist_off = take(P.dist_work.size() * sizeof(int4));
-    P.cand_off = take(P.cand_work.size() * sizeof(int4));
+    P.pass_off = take(P.pass_work.size() * sizeof(int4));
     P.fin_off = take(P.fin_work.size() * sizeof(int4));
     P.red_off = take(P.red_work.size() * sizeof(int4));
     for (int c = 0; c < kPhi32Classes; ++c) P.phi_off[c] = take(phi_cap[c] * sizeof(int4));
@@ -509,7 +518,7 @@ bool class_plan(int n, const stamp_scene* scenes, const int32_t* N, const stamp_
 bool same_layout(const SolvePlan& a, const SolvePlan& b) {
     bool ok = a.total == b.total && a.clk_off == b.clk_off && a.desc_off == b.desc_off && a.roll_off == b.roll_off &&
               a.adj_tiles_off == b.adj_tiles_off &&
-              a.dist_off == b.dist_off && a.cand_off == b.cand_off && a.fin_off == b.fin_off &&
+              a.dist_off == b.dist_off && a.pass_off == b.pass_off && a.fin_off == b.fin_off &&
               a.red_off == b.red_off &&
               a.ctr_off == b.ctr_off && a.err_off == b.err_off && a.tape_off == b.tape_off && a.seg_off == b.seg_off &&
               a.grad_off == b.grad_off && a.phi_vec_off == b.phi_vec_off && a.cost_off == b.cost_off &&
@@ -1018,7 +1027,7 @@ static int32_t solve_impl(stamp_ctx* ctx, int32_t n_problems, const stamp_scene*
         if ((r = upload(P.adj_tiles_off, P.adj_tiles.data(), P.adj_tiles.size() * sizeof(int2))) != hipSuccess)
             return r;
         if ((r = upload(P.dist_off, P.dist_work.data(), P.dist_work.size() * sizeof(int4))) != hipSuccess) return r;
-        if ((r = upload(P.cand_off, P.cand_work.data(), P.cand_work.size() * sizeof(int4))) != hipSuccess) return r;
+        if ((r = upload(P.pass_off, P.pass_work.data(), P.pass_work.size() * sizeof(int4))) != hipSuccess) return r;
         if ((r = upload(P.fin_off, P.fin_work.data(), P.fin_work.size() * sizeof(int4))) != hipSuccess) return r;
         if ((r = upload(P.red_off, P.red_work.data(), P.red_work.size() * sizeof(int4))) != hipSuccess) return r;
         for (int c = 0; c < kPhi32Classes; ++c)
@@ -1043,10 +1052,13 @@ static int32_t solve_impl(stamp_ctx* ctx, int32_t n_problems, const stamp_scene*
             B.dist_start[c] = P.dist_start[c];
             B.dist_n[c] = P.dist_n[c];
         }
-        B.cand_work = (const int4*)(ws + P.cand_off);
+        B.pass_work = (const int4*)(ws + P.pass_off);
+        for (int c = 0; c < kMedGram; ++c) {
+            B.pass_start[c] = P.pass_start[c];
+            B.pass_n[c] = P.pass_n[c];
+        }
         B.fin_work = (const int4*)(ws + P.fin_off);
         B.n_fin = (int)P.fin_work.size();
-        B.n_cand = (int)P.cand_work.size();
         for (int c = 0; c < kPhi32Classes; ++c) {
             B.phi_work[c] = (const int4*)(ws + P.phi_off[c]);
             B.n_phi[c] = (int)P.phi_work[c].size();

@@ -211,9 +211,7 @@ SvgdLayout svgd_workspace_layout(int N, int d) {
     L.cand_off = off;
     off = align256(off + (N >= 2 ? (size_t)L.cand_cap * 4 : 0));
     L.hist_off = off;
-    off = align256(off + kMedBins * 4);
-    L.cnt_off = off;
-    off = align256(off + (size_t)L.med_rb * L.med_cc * 2 * 4);
+    off = align256(off + 3 * kMedBins * 4);
     L.sel_off = off;
     off = align256(off + sizeof(SelState));
     L.part_off = off;
