@@ -218,29 +218,37 @@ struct BatchPlan {
     const int4* red_work;   int n_red;    // (p, first elem, end elem, -)
 };
 
-// Mean of coordinate l over N particles ([d][N] layout), one workgroup of
-// kMeanThreads: four independent partial sums per thread keep four loads in
-// flight; a fixed tree adds the threads' sums (same order on every launch).
+// Mean of coordinate l over N particles ([d][N] layout), one workgroup of BLOCK
+// threads: NT partial sums of four independent accumulators each (NT / BLOCK
+// of them a thread, so that many loads are in flight); a fixed tree adds the
+// partial sums (same order on every launch and for every BLOCK).
 constexpr int kMeanThreads = 1024;
-template <int NT = kMeanThreads>
+template <int NT = kMeanThreads, int BLOCK = NT>
 __device__ __forceinline__ void particle_mean_body(int N, int l, const float* __restrict__ theta,
                                                    float* __restrict__ ctr) {
-    constexpr int kMeanThreads = NT;
-    __shared__ float red[kMeanThreads];
+    constexpr int PER = NT / BLOCK;
+    static_assert(PER * BLOCK == NT, "whole partial sums per thread");
+    __shared__ float red[NT];
     const float* t = theta + (int64_t)l * N;
-    float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
-    int i = threadIdx.x;
-    for (; i + 3 * kMeanThreads < N; i += 4 * kMeanThreads) {
-        s0 += t[i];
-        s1 += t[i + kMeanThreads];
-        s2 += t[i + 2 * kMeanThreads];
-        s3 += t[i + 3 * kMeanThreads];
+    float s[PER][4] = {};
+    int i = threadIdx.x;  // the thread's first partial sum's next element
+    for (; i + (PER - 1) * BLOCK + 3 * NT < N; i += 4 * NT)
+#pragma unroll
+        for (int p = 0; p < PER; ++p)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) s[p][u] += t[i + p * BLOCK + u * NT];
+#pragma unroll
+    for (int p = 0; p < PER; ++p) {
+        int j = i + p * BLOCK;
+        for (; j + 3 * NT < N; j += 4 * NT)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) s[p][u] += t[j + u * NT];
+        for (; j < N; j += NT) s[p][0] += t[j];
+        red[threadIdx.x + p * BLOCK] = (s[p][0] + s[p][1]) + (s[p][2] + s[p][3]);
     }
-    for (; i < N; i += kMeanThreads) s0 += t[i];
-    red[threadIdx.x] = (s0 + s1) + (s2 + s3);
     __syncthreads();
-    for (int w = kMeanThreads / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+    for (int w = NT / 2; w > 0; w >>= 1) {
+        for (int q = threadIdx.x; q < w; q += BLOCK) red[q] += red[q + w];
         __syncthreads();
     }
     if (threadIdx.x == 0) ctr[l] = red[0] / (float)N;

@@ -48,10 +48,6 @@ hipError_t launch_svgd_bandwidth(int N, int d, const float* theta, float bandwid
 // P.n_ctr > 0: some problem has N >= 2)
 hipError_t launch_svgd_bandwidth_batched(const BatchPlan& P, const ProblemDesc* descs, const float* theta, int exact,
                                          char* ws, hipStream_t st, int* step = nullptr);
-// particle mean, centred rows and norms (before the median)
-hipError_t launch_operands32(int N, int d, const float* theta, void* ws, const SvgdLayout& L, hipStream_t st);
-hipError_t launch_operands32_batched(const BatchPlan& P, const ProblemDesc* descs, const float* theta, char* ws,
-                                     hipStream_t st, int* step = nullptr);
 // The step's second half: V = w [g - (2/h) x | 1] packed from theta, the
 // gradient and the weights, then phi from the bandwidth, centre and rows the
 // workspace holds (FP32 matrix cores, phi32.hip).
@@ -88,25 +84,26 @@ hipError_t launch_dsvgd_weights_batched(int n_problems, const ProblemDesc* descs
 
 // Median-heuristic bandwidth into the problem's SelState (median.hip): exact = 1
 // the exact lower median of all pairs, 0 the lower median of a fixed sample.
-// gram = 1: problems above 2^20 pairs take, in their passes over every pair,
-// the Gram-form distances of the FP32 contraction's operands (which the
-// workspace must already hold for this theta: launch_operands32); smaller ones
-// keep direct differences.  The batched median always does so: its work lists
-// fix each problem's form (exact = 1 needs the operands of the large ones).
+// operands: the theta-only operands built on the way (kOperands32: the particle
+// mean, the centred rows and their norms; kOperands16: the particle mean).  With
+// kOperands32 problems above 2^20 pairs take, in their passes over every pair,
+// the Gram-form distances of those rows; smaller ones and the others keep
+// direct differences.  The batched median builds kOperands32 and its work lists
+// fix each problem's form; step (nullable) is advanced once by its first launch
+// when P.n_ctr > 0.
+constexpr int kOperandsNone = 0, kOperands32 = 1, kOperands16 = 2;
 hipError_t launch_median(int N, int d, const float* theta, float bandwidth, int exact, void* ws, const SvgdLayout& L,
-                         float* h_out, hipStream_t st, int gram = 0);
-hipError_t launch_median_batched(const BatchPlan& P, const ProblemDesc* descs, const float* theta, int exact,
-                                 char* ws, hipStream_t st);
+                         float* h_out, hipStream_t st, int operands = kOperandsNone);
+hipError_t launch_median_batched(const BatchPlan& P, const ProblemDesc* descs, const float* theta, char* ws,
+                                 hipStream_t st, int* step);
 
 // The same step on the BF16 matrix cores with a sampled median (phi16.hip).
 hipError_t launch_svgd16(int N, int d, const float* theta, const float* grad, float bandwidth, float* phi,
                          float* h_out, void* ws, const SvgdLayout& L, uint32_t* status, hipStream_t st);
 hipError_t launch_svgd16_batched(const BatchPlan& P, const ProblemDesc* descs, const float* theta, const float* grad,
                                  float* phi, char* ws, uint32_t* status, hipStream_t st);
-// its theta-only operand (the particle mean), built with the sampled median,
-// and its second half (the scaled BF16 rows and V, which need h, the
+// its second half (the scaled BF16 rows and V, which need h, the
 // contraction, the reduce; upd as for the FP32 form)
-hipError_t launch_operands16(int N, int d, const float* theta, void* ws, const SvgdLayout& L, hipStream_t st);
 // the sampled median and the centres for a batch, in two launches (sample
 // distances with the centres, then the sample select); a non-null step
 // counter is advanced by one on the way

@@ -45,6 +45,7 @@
 #include "bf16_operands.h"
 #include "common.h"
 #include "internal.h"
+#include "operands32.h"
 
 namespace stamp {
 
@@ -1059,16 +1060,35 @@ struct OneMed {
     char* ws;
 };
 
-// four lanes per sample slot
-__global__ __launch_bounds__(256) void k_med_dist(OneMed a, const float* theta) {
-    if (a.N < 2 || a.fixed_h > 0.0f) return;
-    const int t = blockIdx.x * 64 + (threadIdx.x >> 2), q = threadIdx.x & 3;
+// The step's first two launches, each of two stages that do not depend on each
+// other: the sample distances (four lanes a slot, 64 slots a workgroup) beside
+// the coordinates' means, then the select (the first workgroup, of 1024)
+// beside the packing of the centred rows (256 a workgroup).  All four are
+// latency: with a launch for each the step took 45.6 us at N = 1024, d = 18 and
+// 33.9 at N = 32, in pairs 40.2 and 23.4.  n_dist = 0 or no centre workgroups
+// leave a stage out.
+template <int NT>
+__global__ __launch_bounds__(256) void k_med_gather(OneMed a, const float* theta, int n_dist) {
+    const int b = blockIdx.x;
+    if (b >= n_dist) {
+        particle_mean_body<NT, 256>(a.N, b - n_dist, theta, reinterpret_cast<float*>(a.ws + a.L.ctr_off));
+        return;
+    }
+    const int t = b * 64 + (threadIdx.x >> 2), q = threadIdx.x & 3;
     const float v = sample_dist4(a.N, a.d, t, q, theta);
     if (q == 0) med_view(a.N, a.d, a.fixed_h, a.L, a.ws).smp[t] = v;
 }
 
 __global__ __launch_bounds__(kSelThreads) void k_sample_select(OneMed a, int exact, float* h_out) {
     sample_select_body(med_view(a.N, a.d, a.fixed_h, a.L, a.ws), exact, h_out);
+}
+
+constexpr int kPackRows = 256;  // rows of a packing workgroup of kSelThreads
+__global__ __launch_bounds__(kSelThreads) void k_select_pack(OneMed a, const float* theta, float* h_out) {
+    if (blockIdx.x == 0) sample_select_body(med_view(a.N, a.d, a.fixed_h, a.L, a.ws), 1, h_out);
+    else
+        pack32_x_rows<kSelThreads / 256>(a.N, a.d, a.L.ks32, (blockIdx.x - 1) * kPackRows, theta, view32(a.L, a.ws),
+                                         a.L.split3);
 }
 
 template <int DP, int ROWS>
@@ -1129,29 +1149,34 @@ __device__ __forceinline__ MedView med_of(const ProblemDesc& D, char* ws) {
     return med_view(D.N, D.d, D.fixed_h, D.sv, ws + D.svgd_off);
 }
 
-// grid (kMedSample / 64, problems): four lanes per sample slot
-__global__ __launch_bounds__(256) void k_med_dist_batched(const ProblemDesc* __restrict__ descs, const float* theta,
-                                                          char* ws) {
-    const ProblemDesc& D = descs[blockIdx.y];
-    if (D.N < 2 || D.fixed_h > 0.0f) return;
-    const int t = blockIdx.x * 64 + (threadIdx.x >> 2), q = threadIdx.x & 3;
-    const float v = sample_dist4(D.N, D.d, t, q, theta + D.theta_off);
-    if (q == 0) med_of(D, ws).smp[t] = v;
-}
-
 __global__ __launch_bounds__(kSelThreads) void k_sample_select_batched(const ProblemDesc* __restrict__ descs, char* ws,
                                                                 int exact) {
     sample_select_body(med_of(descs[blockIdx.x], ws), exact, nullptr);
 }
 
-// The BF16 form's bandwidth stage in two launches.  First: blocks below
-// nd = (kMedSample / 64) x problems gather the sample distances (four lanes a
+// np problems' selects, then the packing: entry = (problem, first row of a
+// 256-row chunk, -, -)
+__global__ __launch_bounds__(kSelThreads) void k_select_pack_batched(const ProblemDesc* __restrict__ descs, int np,
+                                                                     const int4* __restrict__ work, const float* theta,
+                                                                     char* ws) {
+    if ((int)blockIdx.x < np) {
+        sample_select_body(med_of(descs[blockIdx.x], ws), 1, nullptr);
+        return;
+    }
+    const int4 e = work[blockIdx.x - np];
+    const ProblemDesc& D = descs[e.x];
+    if (D.N < 2) return;
+    pack32_x_rows<kSelThreads / 256>(D.N, D.d, D.sv.ks32, e.y, theta + D.theta_off, view32(D.sv, ws + D.svgd_off),
+                                     D.sv.split3);
+}
+
+// A batch's first launch, and with the select the BF16 form's whole bandwidth
+// stage: blocks below nd = (kMedSample / 64) x problems gather the sample distances (four lanes a
 // slot), the rest take one entry (problem, coordinate) of the centre list
-// each.  Second: one workgroup per problem selects the sample median (the
-// scaled rows, which need it, are packed with V).  A non-null step counter is
-// advanced once by the first launch (a solve's iteration counter, read by
-// the update at the iteration's end).
-__global__ __launch_bounds__(256) void k_bw16_gather_batched(const ProblemDesc* __restrict__ descs,
+// each (NT partial sums).  A non-null step counter is advanced once (a solve's
+// iteration counter, read by the update at the iteration's end).
+template <int NT>
+__global__ __launch_bounds__(256) void k_gather_batched(const ProblemDesc* __restrict__ descs,
                                                              const int4* __restrict__ ctr_work, int nd,
                                                              const float* theta, char* ws, int* step) {
     constexpr int per = kMedSample / 64;
@@ -1166,8 +1191,8 @@ __global__ __launch_bounds__(256) void k_bw16_gather_batched(const ProblemDesc* 
     }
     const int4 e = ctr_work[blockIdx.x - nd];
     const ProblemDesc& D = descs[e.x];
-    particle_mean_body<kCentreThreads>(D.N, e.y, theta + D.theta_off,
-                                       reinterpret_cast<float*>(ws + D.svgd_off + D.sv.ctr_off));
+    particle_mean_body<NT, 256>(D.N, e.y, theta + D.theta_off,
+                                reinterpret_cast<float*>(ws + D.svgd_off + D.sv.ctr_off));
 }
 
 // entry = (problem, row block, column chunk, -) of this item shape's work list
@@ -1273,18 +1298,27 @@ void launch_pass_batched(const BatchPlan& P, const ProblemDesc* descs, char* ws,
 }  // namespace
 
 hipError_t launch_median(int N, int d, const float* theta, float bandwidth, int exact, void* ws, const SvgdLayout& L,
-                         float* h_out, hipStream_t st, int gram) {
+                         float* h_out, hipStream_t st, int operands) {
     OneMed a{N, d, bandwidth > 0.0f ? bandwidth : 0.0f, L, static_cast<char*>(ws)};
     // the sample distances only when a median is wanted: with a given
     // bandwidth (or one particle) the select just records h
-    if (N >= 2 && !(bandwidth > 0.0f))
-        hipLaunchKernelGGL(k_med_dist, dim3(kMedSample / 64), dim3(256), 0, st, a, theta);
-    hipLaunchKernelGGL(k_sample_select, dim3(1), dim3(kSelThreads), 0, st, a, exact, h_out);
+    const int n_dist = N >= 2 && !(bandwidth > 0.0f) ? kMedSample / 64 : 0, n_ctr = operands && N >= 2 ? d : 0;
+    if (n_dist + n_ctr) {
+        const dim3 grid(n_dist + n_ctr);
+        if (operands == kOperands16)
+            hipLaunchKernelGGL(k_med_gather<kCentreThreads>, grid, dim3(256), 0, st, a, theta, n_dist);
+        else
+            hipLaunchKernelGGL(k_med_gather<kMeanThreads>, grid, dim3(256), 0, st, a, theta, n_dist);
+    }
+    if (n_ctr && operands == kOperands32)
+        hipLaunchKernelGGL(k_select_pack, dim3(1 + L.npad / kPackRows), dim3(kSelThreads), 0, st, a, theta, h_out);
+    else
+        hipLaunchKernelGGL(k_sample_select, dim3(1), dim3(kSelThreads), 0, st, a, exact, h_out);
     if (exact && N >= 2 && !(bandwidth > 0.0f) && pair_count(N) > (uint64_t)kMedSample) {
         // pass 0; small problems keep direct differences, whose every-pair
         // fallback lives in the finishing workgroup
         const bool small = !med_takes_gram(N);
-        if (gram && !small)
+        if (operands == kOperands32 && !small)
             by_gram_shape(med_gram_ks(L), L.med_rows, [&](auto k, auto r) {
                 hipLaunchKernelGGL((k_med_items_gram<k.value, r.value>), dim3(med_gram_groups(N)), dim3(256), 0, st, a);
                 for (int pass = 1; pass <= 3; ++pass)
@@ -1310,18 +1344,20 @@ hipError_t launch_median(int N, int d, const float* theta, float bandwidth, int 
 hipError_t launch_bandwidth16_batched(const BatchPlan& P, const ProblemDesc* descs, const float* theta, char* ws,
                                       hipStream_t st, int* step) {
     const int np = P.n_problems, nd = (kMedSample / 64) * np;
-    hipLaunchKernelGGL(k_bw16_gather_batched, dim3(nd + P.n_ctr), dim3(256), 0, st, descs, P.ctr_work, nd, theta, ws,
-                       step);
+    hipLaunchKernelGGL(k_gather_batched<kCentreThreads>, dim3(nd + P.n_ctr), dim3(256), 0, st, descs, P.ctr_work, nd,
+                       theta, ws, step);
     hipLaunchKernelGGL(k_sample_select_batched, dim3(np), dim3(kSelThreads), 0, st, descs, ws, 0);
     return hipGetLastError();
 }
 
-hipError_t launch_median_batched(const BatchPlan& P, const ProblemDesc* descs, const float* theta, int exact,
-                                 char* ws, hipStream_t st) {
-    const int np = P.n_problems;
-    hipLaunchKernelGGL(k_med_dist_batched, dim3(kMedSample / 64, np), dim3(256), 0, st, descs, theta, ws);
-    hipLaunchKernelGGL(k_sample_select_batched, dim3(np), dim3(kSelThreads), 0, st, descs, ws, exact);
-    if (exact && P.n_dist) {
+hipError_t launch_median_batched(const BatchPlan& P, const ProblemDesc* descs, const float* theta, char* ws,
+                                 hipStream_t st, int* step) {
+    const int np = P.n_problems, nd = (kMedSample / 64) * np;
+    hipLaunchKernelGGL(k_gather_batched<kMeanThreads>, dim3(nd + P.n_ctr), dim3(256), 0, st, descs, P.ctr_work, nd,
+                       theta, ws, P.n_ctr ? step : nullptr);
+    hipLaunchKernelGGL(k_select_pack_batched, dim3(np + P.n_row16), dim3(kSelThreads), 0, st, descs, np, P.row16_work,
+                       theta, ws);
+    if (P.n_dist) {
         launch_items_batched(P, descs, theta, ws, st);
         // problems of 2^20 pairs at most end in one workgroup each, the larger
         // ones in the passes

@@ -281,10 +281,6 @@ struct One16 {
     float fixed_h;
 };
 
-__global__ __launch_bounds__(kCentreThreads) void k_center(One16 a, const float* theta, char* ws) {
-    particle_mean_body<kCentreThreads>(a.N, blockIdx.x, theta, view16(a.L, ws).ctr);
-}
-
 __global__ __launch_bounds__(256) void k_pack16_v(One16 a, const float* theta, const float* g, char* ws) {
     pack16_v_rows(a.N, a.d, a.L.kd, a.L.vc, blockIdx.x * 256, theta, g, view16(a.L, ws));
 }
@@ -362,14 +358,6 @@ __global__ __launch_bounds__(256) void k_reduce16_batched(const ProblemDesc* __r
 
 }  // namespace
 
-hipError_t launch_operands16(int N, int d, const float* theta, void* ws, const SvgdLayout& L, hipStream_t st) {
-    if (N < 2) return hipSuccess;
-    One16 a{N, d, L, 0.0f};
-    char* b = static_cast<char*>(ws);
-    hipLaunchKernelGGL(k_center, dim3(d), dim3(kCentreThreads), 0, st, a, theta, b);
-    return hipGetLastError();
-}
-
 hipError_t launch_svgd16_direction(int N, int d, const float* theta, const float* grad, float* phi, void* ws,
                                    const SvgdLayout& L, uint32_t* status, hipStream_t st, const UpdateArgs* upd) {
     One16 a{N, d, L, 0.0f};
@@ -392,9 +380,8 @@ hipError_t launch_svgd16_direction(int N, int d, const float* theta, const float
 
 hipError_t launch_svgd16(int N, int d, const float* theta, const float* grad, float bandwidth, float* phi,
                          float* h_out, void* ws, const SvgdLayout& L, uint32_t* status, hipStream_t st) {
-    hipError_t e = launch_median(N, d, theta, bandwidth, 0, ws, L, h_out, st);
+    hipError_t e = launch_median(N, d, theta, bandwidth, 0, ws, L, h_out, st, kOperands16);
     if (e != hipSuccess) return e;
-    if ((e = launch_operands16(N, d, theta, ws, L, st)) != hipSuccess) return e;
     return launch_svgd16_direction(N, d, theta, grad, phi, ws, L, status, st, nullptr);
 }
 

@@ -275,9 +275,7 @@ hipError_t launch_svgd(int N, int d, const float* theta, const float* grad_logp,
 
 hipError_t launch_svgd_bandwidth(int N, int d, const float* theta, float bandwidth, float* h_out, void* ws,
                                  const SvgdLayout& L, hipStream_t st) {
-    hipError_t e = launch_operands32(N, d, theta, ws, L, st);
-    if (e != hipSuccess) return e;
-    return launch_median(N, d, theta, bandwidth, 1, ws, L, h_out, st, 1);
+    return launch_median(N, d, theta, bandwidth, 1, ws, L, h_out, st, kOperands32);
 }
 
 hipError_t launch_svgd_batched(const BatchPlan& P, const ProblemDesc* descs, const float* theta, const float* grad,
@@ -292,9 +290,7 @@ hipError_t launch_svgd_bandwidth_batched(const BatchPlan& P, const ProblemDesc* 
     // the theta-only operands of the FP32 form (exact median, whose all-pairs
     // passes read them) or of the BF16 form (sampled median)
     if (!exact) return launch_bandwidth16_batched(P, descs, theta, ws, st, step);
-    hipError_t e;
-    if ((e = launch_operands32_batched(P, descs, theta, ws, st, step)) != hipSuccess) return e;
-    return launch_median_batched(P, descs, theta, 1, ws, st);
+    return launch_median_batched(P, descs, theta, ws, st, step);
 }
 
 hipError_t launch_phi_reduce(int N, int d, int splits, const float* partial, float* phi, uint32_t* status,
