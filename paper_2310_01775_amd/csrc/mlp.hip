@@ -23,6 +23,8 @@
 // a refresh of the BF16 copies.
 #include <math.h>
 
+#include <type_traits>
+
 #include "common.h"
 #include "internal.h"
 
@@ -498,11 +500,21 @@ constexpr int kInfRows = 16 * kInfBlocks;
 // sample i is dataset row src = idx ? idx[i] : i of X [n_rows][n_in], its
 // target log(1 + cost[src]).  An index outside [0, n_rows) reads row 0 and
 // sets STAMP_STATUS_BAD_INDEX.
+typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
+// Place of sample s of feature f among nf in a training activation: 32 samples
+// (a weight-gradient MFMA's) of every feature together, so that the fragments
+// of 16 features are one contiguous kilobyte.  Feature rows of all M samples
+// put them M apart, for M = 8192 all in the same cache channel (the weight
+// gradients 14.6 -> 9.6 us; the training kernel's stores are hidden either way).
+__device__ __forceinline__ int64_t act_at(int nf, int f, int s) {
+    return (int64_t)(s >> 5) * (32 * nf) + 32 * f + (s & 31);
+}
+
 // A workgroup of four waves takes kTrainRows = 16 samples and each wave 64 of
 // every layer's 256 neurons (four 16-neuron blocks), the activations passing
 // between the waves through LDS; every block's weight fragments load while
 // the previous block computes.
-// Writes feature-major BF16 activations for the weight gradients and per-tile
+// Writes BF16 activations (act_at) for the weight gradients and per-tile
 // partial sums: part[tile][0..255] = sum delta1, [256..511] = sum delta2,
 // [512..767] = sum delta3 * h2, [768] = sum delta3, [769] = sum (y - t)^2 / M.
 __global__ __launch_bounds__(256) void k_mlp_train_fb(const float* __restrict__ P, const __bf16* __restrict__ Wb,
@@ -540,7 +552,7 @@ __global__ __launch_bounds__(256) void k_mlp_train_fb(const float* __restrict__ 
     // U^T for dW1
     for (int e = threadIdx.x; e < kIn * 16; e += 256) {
         const int f = e >> 4, r = e & 15;
-        UT[(int64_t)f * M + row0 + r] = sU[r * kLdU + f];
+        UT[act_at(kIn, f, row0 + r)] = sU[r * kLdU + f];
     }
     // layer 1 on the wave's neurons: z1 kept for delta1, h1 to LDS
     f4 z1[NB];
@@ -558,11 +570,14 @@ __global__ __launch_bounds__(256) void k_mlp_train_fb(const float* __restrict__ 
             }
             z1[a] = mma_rows_w<kIn>(sU, kLdU, w0, f4{0.f, 0.f, 0.f, 0.f});
             const int c = cb * 16 + col;
+            bf16x4 h4;
+#pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const __bf16 h = (__bf16)gelu(z1[a][j] + b1v[a]);
                 sH[(4 * kq + j) * kLdH + c] = h;
-                H1T[(int64_t)c * M + row0 + 4 * kq + j] = h;
+                h4[j] = h;
             }
+            *reinterpret_cast<bf16x4*>(H1T + act_at(kW, c, row0 + 4 * kq)) = h4;
 #pragma unroll
             for (int k = 0; k < kIn / 32; ++k) w0[k] = w1[k];
         }
@@ -617,14 +632,17 @@ __global__ __launch_bounds__(256) void k_mlp_train_fb(const float* __restrict__ 
     for (int a = 0; a < NB; ++a) {
         const int c = (nb0 + a) * 16 + col;
         float s2 = 0.0f, s3 = 0.0f;
+        bf16x4 d4;
+#pragma unroll
         for (int j = 0; j < 4; ++j) {
             const float dz = d3[j] * w3v[a] * gelu_grad(z2[a][j]);
             const __bf16 db = (__bf16)dz;
             sD[(4 * kq + j) * kLdH + c] = db;
-            D2T[(int64_t)c * M + row0 + 4 * kq + j] = db;
+            d4[j] = db;
             s2 += dz;
             s3 += d3[j] * gelu(z2[a][j]);
         }
+        *reinterpret_cast<bf16x4*>(D2T + act_at(kW, c, row0 + 4 * kq)) = d4;
         s2 = sum_groups(s2);
         s3 = sum_groups(s3);
         if (kq == 0) {
@@ -653,11 +671,14 @@ __global__ __launch_bounds__(256) void k_mlp_train_fb(const float* __restrict__ 
             const f4 t = mma_rows_w<kW>(sD, kLdH, t0, f4{0.f, 0.f, 0.f, 0.f});
             const int k = kb * 16 + col;
             float s1 = 0.0f;
+            bf16x4 d4;
+#pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const float dz = t[j] * gelu_grad(z1[a][j] + b1v[a]);
-                D1T[(int64_t)k * M + row0 + 4 * kq + j] = (__bf16)dz;
+                d4[j] = (__bf16)dz;
                 s1 += dz;
             }
+            *reinterpret_cast<bf16x4*>(D1T + act_at(kW, k, row0 + 4 * kq)) = d4;
             s1 = sum_groups(s1);
             if (kq == 0) sRed[k] = s1;
 #pragma unroll
@@ -669,40 +690,61 @@ __global__ __launch_bounds__(256) void k_mlp_train_fb(const float* __restrict__ 
         part[(int64_t)blockIdx.x * kMlpPartStride + e] = e < 770 ? sRed[e] : 0.0f;
 }
 
-// Weight-gradient partials of a minibatch split in `splits` sample ranges:
+// Weight-gradient partials of a minibatch split in sample ranges of `per`:
 // part[q][c][k] = sum over the samples s of range q of AT[c][s] BT[k][s]
-// (AT [nc][M], BT [nk][M], BF16 feature-major; nc, nk multiples of 64).  A
+// (AT of kW features, BT of nk, a multiple of 64, BF16 laid out by act_at).  A
 // workgroup of four waves takes a 64 x 64 output tile of one range, each wave
-// a 32 x 32 quarter as 2 x 2 MFMA tiles; Adam adds the ranges in order.
-__global__ __launch_bounds__(256) void k_mlp_wgrad(const __bf16* __restrict__ AT, const __bf16* __restrict__ BT,
-                                                   int M, int nc, int nk, int per, float* __restrict__ part) {
-    const int tk = nk / 64;
-    const int c0 = (int)(blockIdx.x / tk) * 64, k0 = (int)(blockIdx.x % tk) * 64;
+// a 32 x 32 quarter as 2 x 2 MFMA tiles; Adam adds the ranges in order.  Both
+// layers share the launch, the first kW / 64 x kW / 64 workgroups of a range
+// layer 2, and the loads of four MFMA steps are in flight: the loads bound it
+// (M = 8192: 12.1 + 5.5 us in two launches over feature rows of all samples, 14.6
+// in one, 9.6 with the samples in blocks).
+__global__ __launch_bounds__(256) void k_mlp_wgrad(const __bf16* __restrict__ D2T, const __bf16* __restrict__ H1T,
+                                                   float* __restrict__ dW2, const __bf16* __restrict__ D1T,
+                                                   const __bf16* __restrict__ UT, float* __restrict__ dW1, int M,
+                                                   int per) {
+    constexpr int kTiles2 = (kW / 64) * (kW / 64);
+    const bool second = (int)blockIdx.x < kTiles2;
+    const int nk = second ? kW : kIn, tk = nk / 64, tile = second ? blockIdx.x : blockIdx.x - kTiles2;
+    const __bf16* AT = second ? D2T : D1T;
+    const __bf16* BT = second ? H1T : UT;
+    float* part = second ? dW2 : dW1;
+    const int c0 = tile / tk * 64, k0 = tile % tk * 64;
     const int q = blockIdx.y;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
     const int r = l & 15, kq = l >> 4;
     const int cw = c0 + 32 * (wave >> 1), kw = k0 + 32 * (wave & 1);
     const int s0 = q * per;
-    const __bf16* a0 = AT + (int64_t)(cw + r) * M + 8 * kq;
-    const __bf16* b0 = BT + (int64_t)(kw + r) * M + 8 * kq;
+    const __bf16* a0 = AT + 32 * (cw + r) + 8 * kq;
+    const __bf16* b0 = BT + 32 * (kw + r) + 8 * kq;
     f4 acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-    for (int s = s0; s < s0 + per; s += 32) {
-        bf16x8 av[2], bv[2];
+    auto steps = [&](auto count, int s) __attribute__((always_inline)) {  // their loads in flight at once
+        constexpr int C = decltype(count)::value;
+        bf16x8 av[C][2], bv[C][2];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) av[i] = *reinterpret_cast<const bf16x8*>(a0 + (int64_t)16 * i * M + s);
+        for (int u = 0; u < C; ++u)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) bv[j] = *reinterpret_cast<const bf16x8*>(b0 + (int64_t)16 * j * M + s);
+            for (int i = 0; i < 2; ++i) {
+                av[u][i] = *reinterpret_cast<const bf16x8*>(a0 + (int64_t)(s + 32 * u) * kW + 512 * i);
+                bv[u][i] = *reinterpret_cast<const bf16x8*>(b0 + (int64_t)(s + 32 * u) * nk + 512 * i);
+            }
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int u = 0; u < C; ++u)
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[i], bv[j], acc[i][j], 0, 0, 0);
-    }
-    float* out = part + (int64_t)q * nc * nk;
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[u][i], bv[u][j], acc[i][j], 0, 0, 0);
+    };
+    int s = s0;
+    for (; s + 128 <= s0 + per; s += 128) steps(std::integral_constant<int, 4>{}, s);
+    for (; s < s0 + per; s += 32) steps(std::integral_constant<int, 1>{}, s);
+    float* out = part + (int64_t)q * kW * nk;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -719,71 +761,103 @@ __host__ __device__ __forceinline__ int wgrad_splits(int M) {
     return q;
 }
 
-// Adam on the trained tensors (FP32 master weights): the weight gradients add
-// their sample ranges in range order, the bias and output-weight gradients
-// the training workgroups' partial sums in workgroup order (32 loads in
-// flight).  Element 0 (mu, not trained) writes the loss instead when asked.
-__global__ __launch_bounds__(256) void k_mlp_adam(float* __restrict__ P, float* __restrict__ mom,
-                                                  float* __restrict__ vel, const float* __restrict__ dW1,
-                                                  const float* __restrict__ dW2, int splits,
-                                                  const float* __restrict__ part, int tiles, int n_in, int t,
-                                                  float lr, float b1, float b2, float eps, float* loss) {
-    const int e = blockIdx.x * 256 + threadIdx.x;
-    if (e >= kMlpParams) return;
-    // the range sum (stride bytes between ranges) or the workgroup sum
-    auto sum = [&](const float* base, int64_t stride, int n) {
-        constexpr int F = 32;  // loads in flight (the 16-row tiles of a large batch are many)
-        float g = 0.0f;
-        for (int q0 = 0; q0 < n; q0 += F) {
-            float u[F];
-#pragma unroll
-            for (int k = 0; k < F; ++k) u[k] = base[(int64_t)min(q0 + k, n - 1) * stride];
-#pragma unroll
-            for (int k = 0; k < F; ++k)
-                if (q0 + k < n) g += u[k];
-        }
-        return g;
+// Element e of a [kW][cols] weight matrix into its BF16 copy at `at` and the
+// copy of its transpose at `at_t`.
+__device__ __forceinline__ void write_copies(__bf16* __restrict__ Wb, float x, int e, int cols, int at, int at_t) {
+    const __bf16 w = (__bf16)x;
+    Wb[at + e] = w;
+    Wb[at_t + (e % cols) * kW + e / cols] = w;
+}
+
+// Adam on the trained tensors (FP32 master weights) and the BF16 working copies
+// of the updated weights (as k_mlp_prepare writes them).  The first
+// kAdamWeightBlocks workgroups take the weight matrices, an element a thread:
+// its gradient adds the sample ranges in range order, 32 loads in flight.  The
+// others take kAdamSums sums over the training workgroups each (bias and
+// output-weight gradients, the loss): all threads stage 512 workgroups' values
+// through LDS and one thread a sum adds them in workgroup order.  Latency: at
+// M = 8192 a thread that loads its 512 values itself, 32 at a time, took 16.0 us
+// and the copies a launch of 4.7 more; now 8.3 us for both.
+constexpr int kAdamWeightBlocks = (kW * kIn + kW * kW) / 256;
+constexpr int kAdamSums = 16, kAdamStage = 512;
+constexpr int kAdamSumBlocks = (770 + kAdamSums - 1) / kAdamSums;
+__global__ __launch_bounds__(256) void k_mlp_adam(float* __restrict__ P, __bf16* __restrict__ Wb,
+                                                  float* __restrict__ mom, float* __restrict__ vel,
+                                                  const float* __restrict__ dW1, const float* __restrict__ dW2,
+                                                  int splits, const float* __restrict__ part, int tiles, int n_in,
+                                                  int t, float lr, float b1, float b2, float eps, float* loss) {
+    static_assert(kW * kIn % 256 == 0 && kW * kW % 256 == 0, "whole workgroups per matrix");
+    __shared__ float stage[kAdamStage * kAdamSums];
+    auto update = [&](int e, float g) {
+        const float mm = b1 * mom[e] + (1.0f - b1) * g;
+        const float vv = b2 * vel[e] + (1.0f - b2) * g * g;
+        mom[e] = mm;
+        vel[e] = vv;
+        const float mhat = mm / (1.0f - powf(b1, (float)t));
+        const float vhat = vv / (1.0f - powf(b2, (float)t));
+        const float w = P[e] - lr * mhat / (sqrtf(vhat) + eps);
+        P[e] = w;
+        return w;
     };
-    if (e == 0 && loss) *loss = sum(part + 769, kMlpPartStride, tiles);
-    float g;
-    if (e >= kMlpOffW1 && e < kMlpOffB1) {
-        const int k = (e - kMlpOffW1) / kIn, f = (e - kMlpOffW1) % kIn;
-        g = f < n_in ? sum(dW1 + k * kIn + f, (int64_t)kW * kIn, splits) : 0.0f;
-    } else if (e >= kMlpOffW2 && e < kMlpOffB2) {
-        g = sum(dW2 + (e - kMlpOffW2), (int64_t)kW * kW, splits);
-    } else {
-        int idx;
-        if (e >= kMlpOffB1 && e < kMlpOffW2) idx = e - kMlpOffB1;              // sum delta1
-        else if (e >= kMlpOffB2 && e < kMlpOffW3) idx = 256 + (e - kMlpOffB2);  // sum delta2
-        else if (e >= kMlpOffW3 && e < kMlpOffB3) idx = 512 + (e - kMlpOffW3);  // sum delta3 h2
-        else if (e == kMlpOffB3) idx = 768;                                     // sum delta3
-        else return;  // mu, inv_sigma and padding are not trained
-        g = sum(part + idx, kMlpPartStride, tiles);
+    const int tid = threadIdx.x;
+    if ((int)blockIdx.x < kAdamWeightBlocks) {
+        const bool first = (int)blockIdx.x < kW * kIn / 256;
+        const int e = (first ? blockIdx.x : blockIdx.x - kW * kIn / 256) * 256 + tid;
+        const int64_t stride = first ? kW * kIn : kW * kW;
+        const float* base = (first ? dW1 : dW2) + e;
+        float g = 0.0f;
+        if (!first || e % kIn < n_in) {
+            float u[32];  // at most 32 ranges
+#pragma unroll
+            for (int k = 0; k < 32; ++k) u[k] = base[min(k, splits - 1) * stride];
+#pragma unroll
+            for (int k = 0; k < 32; ++k)
+                if (k < splits) g += u[k];
+        }
+        const float w = update((first ? kMlpOffW1 : kMlpOffW2) + e, g);
+        if (first) write_copies(Wb, w, e, kIn, kMlpBfW1, kMlpBfW1T);
+        else write_copies(Wb, w, e, kW, kMlpBfW2, kMlpBfW2T);
+        return;
     }
-    const float mm = b1 * mom[e] + (1.0f - b1) * g;
-    const float vv = b2 * vel[e] + (1.0f - b2) * g * g;
-    mom[e] = mm;
-    vel[e] = vv;
-    const float mhat = mm / (1.0f - powf(b1, (float)t));
-    const float vhat = vv / (1.0f - powf(b2, (float)t));
-    P[e] = P[e] - lr * mhat / (sqrtf(vhat) + eps);
+    // the sums 0..255 delta1, 256..511 delta2, 512..767 delta3 h2, 768 delta3, 769 the loss
+    const int i0 = ((int)blockIdx.x - kAdamWeightBlocks) * kAdamSums, i = i0 + tid % kAdamSums;
+    float g = 0.0f;
+    for (int q0 = 0; q0 < tiles; q0 += kAdamStage) {
+        constexpr int R = 256 / kAdamSums;  // workgroups staged side by side
+        float u[kAdamStage / R];
+#pragma unroll
+        for (int k = 0; k < kAdamStage / R; ++k)
+            u[k] = part[(int64_t)min(q0 + tid / kAdamSums + R * k, tiles - 1) * kMlpPartStride + min(i, 769)];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kAdamStage / R; ++k) stage[tid + 256 * k] = u[k];
+        __syncthreads();
+        if (tid < kAdamSums) {
+            const int n = min(tiles - q0, kAdamStage);
+            int q = 0;
+            for (; q + 16 <= n; q += 16) {
+                float x[16];
+#pragma unroll
+                for (int k = 0; k < 16; ++k) x[k] = stage[(q + k) * kAdamSums + tid];
+#pragma unroll
+                for (int k = 0; k < 16; ++k) g += x[k];
+            }
+            for (; q < n; ++q) g += stage[q * kAdamSums + tid];
+        }
+    }
+    if (tid >= kAdamSums || i > 769) return;
+    if (i == 769) {
+        if (loss) *loss = g;
+        return;
+    }
+    update(i < 256 ? kMlpOffB1 + i : i < 512 ? kMlpOffB2 + i - 256 : i < 768 ? kMlpOffW3 + i - 512 : kMlpOffB3, g);
 }
 
 // BF16 working copies of W1, W1^T, W2, W2^T from the FP32 parameters.
 __global__ __launch_bounds__(256) void k_mlp_prepare(const float* __restrict__ P, __bf16* __restrict__ Wb) {
     const int e = blockIdx.x * 256 + threadIdx.x;
-    if (e < kW * kIn) {
-        const int k = e / kIn, f = e % kIn;
-        const __bf16 w = (__bf16)P[kMlpOffW1 + e];
-        Wb[kMlpBfW1 + e] = w;
-        Wb[kMlpBfW1T + f * kW + k] = w;
-    }
-    if (e < kW * kW) {
-        const int c = e / kW, k = e % kW;
-        const __bf16 w = (__bf16)P[kMlpOffW2 + e];
-        Wb[kMlpBfW2 + e] = w;
-        Wb[kMlpBfW2T + k * kW + c] = w;
-    }
+    if (e < kW * kIn) write_copies(Wb, P[kMlpOffW1 + e], e, kIn, kMlpBfW1, kMlpBfW1T);
+    if (e < kW * kW) write_copies(Wb, P[kMlpOffW2 + e], e, kW, kMlpBfW2, kMlpBfW2T);
 }
 
 // mu and inv_sigma from the data: mean and population standard deviation of
@@ -938,13 +1012,10 @@ hipError_t launch_mlp_train_step(float* P, __bf16* Wb, float* mom, float* vel, i
     const int splits = wgrad_splits(M), per = M / splits;
     hipLaunchKernelGGL(k_mlp_train_fb, dim3(tiles), dim3(256), 0, st, P, Wb, X, cost, idx, n_rows, M, n_in, status,
                        UT, H1T, D2T, D1T, part);
-    hipLaunchKernelGGL(k_mlp_wgrad, dim3((kW / 64) * (kW / 64), splits), dim3(256), 0, st, D2T, H1T, M, kW, kW, per,
-                       dW2);
-    hipLaunchKernelGGL(k_mlp_wgrad, dim3((kW / 64) * (kIn / 64), splits), dim3(256), 0, st, D1T, UT, M, kW, kIn, per,
-                       dW1);
-    hipLaunchKernelGGL(k_mlp_adam, dim3((kMlpParams + 255) / 256), dim3(256), 0, st, P, mom, vel, dW1, dW2, splits,
-                       part, tiles, n_in, t, lr, b1, b2, eps, loss_out);
-    hipLaunchKernelGGL(k_mlp_prepare, dim3((kW * kW + 255) / 256), dim3(256), 0, st, P, Wb);
+    hipLaunchKernelGGL(k_mlp_wgrad, dim3((kW / 64) * (kW / 64) + (kW / 64) * (kIn / 64), splits), dim3(256), 0, st, D2T,
+                       H1T, dW2, D1T, UT, dW1, M, per);
+    hipLaunchKernelGGL(k_mlp_adam, dim3(kAdamWeightBlocks + kAdamSumBlocks), dim3(256), 0, st, P, Wb, mom, vel, dW1, dW2,
+                       splits, part, tiles, n_in, t, lr, b1, b2, eps, loss_out);
     return hipGetLastError();
 }
 
