@@ -922,22 +922,41 @@ __global__ void k_mlp_pack_rows(const float* __restrict__ theta, int N, int d, c
 }
 
 // Surrogate check: out[p] = mean_i |log(1 + c_sur_i) - log(1 + c_true_i)| over
-// problem p's particles (one workgroup per problem, fixed-order tree sum).
-__global__ __launch_bounds__(256) void k_log_err(const ProblemDesc* __restrict__ descs, const float* __restrict__ c_true,
-                                                 const float* __restrict__ c_sur, float* __restrict__ out) {
+// problem p's particles (one workgroup per problem, fixed-order sums: thread t <
+// 256 the particles t, t + 256, ... in order, then a tree).  The logarithms
+// bound it: all 1024 threads take them, 4096 at a time through LDS (with the
+// 256 summing threads alone N = 16384 took 48 us, now 23).
+__global__ __launch_bounds__(1024) void k_log_err(const ProblemDesc* __restrict__ descs,
+                                                  const float* __restrict__ c_true, const float* __restrict__ c_sur,
+                                                  float* __restrict__ out) {
+    __shared__ float err[4096];
     __shared__ float red[256];
-    const int p = blockIdx.x;
+    const int p = blockIdx.x, tid = threadIdx.x;
     const int N = descs[p].N;
     const int64_t off = descs[p].cost_off;
     float s = 0.0f;
-    for (int i = threadIdx.x; i < N; i += 256) s += fabsf(log1pf(c_sur[off + i]) - log1pf(c_true[off + i]));
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+    for (int i0 = 0; i0 < N; i0 += 4096) {
+        float x[4], y[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = min(i0 + tid + 1024 * u, N - 1);
+            x[u] = c_sur[off + i];
+            y[u] = c_true[off + i];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) err[tid + 1024 * u] = fabsf(log1pf(x[u]) - log1pf(y[u]));
+        __syncthreads();
+        if (tid < 256)
+            for (int i = tid; i < min(4096, N - i0); i += 256) s += err[i];
         __syncthreads();
     }
-    if (threadIdx.x == 0) out[p] = red[0] / (float)N;
+    if (tid < 256) red[tid] = s;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if (tid < w) red[tid] += red[tid + w];
+        __syncthreads();
+    }
+    if (tid == 0) out[p] = red[0] / (float)N;
 }
 
 
@@ -960,7 +979,7 @@ hipError_t launch_mlp_infer(const float* P, const __bf16* Wb, const float* X, in
 
 hipError_t launch_log_err(const ProblemDesc* descs, int n_problems, const float* c_true, const float* c_sur,
                           float* out, hipStream_t st) {
-    hipLaunchKernelGGL(k_log_err, dim3(n_problems), dim3(256), 0, st, descs, c_true, c_sur, out);
+    hipLaunchKernelGGL(k_log_err, dim3(n_problems), dim3(1024), 0, st, descs, c_true, c_sur, out);
     return hipGetLastError();
 }
 
