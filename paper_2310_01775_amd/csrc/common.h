@@ -77,7 +77,7 @@ constexpr uint32_t kCandSegMin = 16384;  // candidate slots per segment at least
 struct SelState {
     uint32_t lo, hi;      // bracket, inclusive, of FP32 bit patterns
     uint32_t rank;        // 1-based rank of the median among all pairs
-    uint32_t mode;        // 0 done, 1 the passes are wanted
+    uint32_t mode;        // 1 the passes are wanted, 0 not; written by the sample select alone
     // pass 0, per candidate segment: pairs below the bracket << 32 | candidates;
     // a counter per cache line: the workgroups' atomics on a line run one by one
     unsigned long long seg[kCandSegs][16];

@@ -173,12 +173,14 @@ __device__ float sample_dist4(int N, int d, int t, int q, const float* __restric
     return ok ? s : __int_as_float(0x7f800000);
 }
 
+// Leaves sel->mode alone: the passes' workgroups branch on it at their start,
+// and in the last pass one of them may end here before another one starts.
+// Only the sample select writes it.
 __device__ __forceinline__ void set_bandwidth(SelState* sel, int N, uint32_t m2_bits, float* h_out) {
     const float m2 = __uint_as_float(m2_bits);
     const float h = fmaxf(m2 / logf((float)N), 1e-12f);
     sel->m2 = m2;
     sel->h = h;
-    sel->mode = kModeDone;
     if (h_out) *h_out = h;
 }
 
@@ -409,6 +411,7 @@ __device__ void sample_select_body(const MedView& v, int exact, float* h_out) {
     if (tid != 0) return;
     if (!exact || all) {
         set_bandwidth(sel, N, m, h_out);
+        sel->mode = kModeDone;
         return;
     }
     sel->lo = lo0;
