@@ -997,7 +997,10 @@ static int32_t solve_impl(stamp_ctx* ctx, int32_t n_problems, const stamp_scene*
         build_plan(n_problems, scenes, N, K, cfg->bandwidth, rows, &consts, P, packed, packed_adj);
         return same_layout(P, layout0);
     };
-    const std::string tkey = P.key + "K" + std::to_string(K) + (cfg->bandwidth > 0 ? "fixed" : "median");
+    // the batch's sizes and layout: they fix the work lists and their places in
+    // the workspace, which the captured graphs hold
+    const std::string tkey = P.key + "K" + std::to_string(K) + (cfg->bandwidth > 0 ? "fixed" : "median") +
+                             (packed ? "packed" : "blocks");
     StampTune tune;
     auto it_t = ctx->tune.find(tkey);
     const bool have_tune = ctx->is_pinned || it_t != ctx->tune.end();

@@ -73,3 +73,34 @@ def test_layout_argument_is_checked(layout_ctx):
     with pytest.raises(S.StampError) as e:
         layout_ctx.set_rollout_layout(3)
     assert e.value.code == S.EINVAL
+
+
+def test_a_solve_after_a_layout_change_takes_the_new_layout(layout_ctx):
+    """The same buffers and a launch grid both layouts share: nothing but the
+    layout tells the second solve's captured iterations from the first's."""
+    import paper_2310_01775_amd as S
+    ctx = layout_ctx
+    probs = [(W.make_scene(8, pid, B, H, 60, 0.005), W.cost_weights(), W.make_particles(8, pid, N, H))
+             for pid, (N, B, H) in enumerate([(90, 3, 3), (33, 4, 2), (50, 2, 4), (17, 1, 3)])]
+    scenes, ws_, Ns = ([S.make_scene(s) for s, _, _ in probs], [S.make_cost(w) for _, w, _ in probs],
+                       [th.shape[0] for _, _, th in probs])
+    cfg = S.make_cfg(5, lr=1e-3, ckpt_every=5)  # an unrolled graph and a graph of one iteration
+    flat0 = torch.cat([S.soa(th).reshape(-1) for _, _, th in probs]).contiguous()
+    flat, m, v = (torch.empty_like(flat0) for _ in range(3))
+    work = torch.empty(S.Context.solve_workspace_bytes(scenes, Ns, cfg), dtype=torch.uint8, device="cuda")
+    status = ctx.status_word()
+    outs = []
+    ctx.set_launch_shape(64, 2, 64)
+    try:
+        for layout in (S.LAYOUT_BLOCKS, S.LAYOUT_PACKED, S.LAYOUT_BLOCKS):
+            print("layout", layout, flush=True)
+            ctx.set_rollout_layout(layout)
+            flat.copy_(flat0), m.zero_(), v.zero_()
+            cost = ctx.solve(scenes, ws_, Ns, cfg, flat, m, v, workspace=work, status=status)
+            torch.cuda.synchronize()
+            outs.append((flat.clone(), cost.clone()))
+    finally:
+        ctx.set_launch_shape()
+    for o in outs[1:]:
+        assert torch.equal(o[0], outs[0][0]) and torch.equal(o[1], outs[0][1])
+    assert status.item() == 0
