@@ -94,7 +94,7 @@ struct SvgdLayout {
     uint32_t cand_cap;              // their capacity: kCandSegs segments of cand_cap / kCandSegs
     int med_rows;                   // rows (one per thread) of an all-pairs item: 64 or 256
     int med_rb, med_cc;             // all-pairs items: row blocks x column chunks
-    size_t hist_off;                // [3][kMedBins] histograms of the median select
+    size_t hist_off;                // [3][kMedBins] histograms of the median select (at part_off)
     size_t sel_off;                 // SelState
     size_t part_off, part_floats;   // phi partial sums [splits][d][N]
     int splits;                     // column chunks of the phi contraction

@@ -205,17 +205,17 @@ SvgdLayout svgd_workspace_layout(int N, int d) {
     }
     // the partial sums of both contractions share one region: the FP32
     // matrix-core form's [splits32][16 ot][npad] and the structured kernel's
-    // [splits][d][N]
+    // [splits][d][N].  Before a direction writes them, its first bytes hold the
+    // median's histograms (so that the select's region is no larger than the
+    // no-alloc step's scratch has room for)
     L.part_floats = std::max((size_t)splits * d * N, (size_t)L.splits32 * 16 * L.ot32 * L.npad);
     size_t off = 0;
     L.cand_off = off;
     off = align256(off + (N >= 2 ? (size_t)L.cand_cap * 4 : 0));
-    L.hist_off = off;
-    off = align256(off + 3 * kMedBins * 4);
     L.sel_off = off;
     off = align256(off + sizeof(SelState));
-    L.part_off = off;
-    off = align256(off + L.part_floats * 4);
+    L.part_off = L.hist_off = off;
+    off = align256(off + std::max(L.part_floats, (size_t)3 * kMedBins) * 4);
     L.x32_off = off;
     off = align256(off + (size_t)L.npad * 4 * L.ks32 * 4);
     L.n32_off = off;

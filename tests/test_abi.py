@@ -72,6 +72,13 @@ def test_tape_and_workspace_sizes(B, H, T, N, K):
     assert S.Context.svgd_workspace_bytes(N, 6 * H) > 0
 
 
+# the largest particle sets of some dimensions that the no-alloc step has taken
+@pytest.mark.parametrize("N,d", [(7219, 20), (6564, 24), (5641, 30), (4728, 36), (3464, 55), (3101, 63)])
+def test_the_no_alloc_scratch_still_holds_the_largest_steps(N, d):
+    import paper_2310_01775_amd as S
+    assert S.Context.svgd_workspace_bytes(N, d) <= 64 << 20
+
+
 def test_sizing_rejects_bad_arguments():
     import paper_2310_01775_amd as S
     sc = S.make_scene(W.make_scene(2, 0, 1, 2, 50, 0.01))
