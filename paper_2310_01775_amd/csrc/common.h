@@ -88,6 +88,14 @@ struct SelState {
     float m2;             // the median
 };
 
+// The select state at `off` (a multiple of 8) of a workspace.  Its 64-bit counters
+// are added to atomically, which needs 8-byte addresses, while a caller's
+// workspace is only 4-byte aligned: its place moves up by the base's remainder.
+constexpr size_t kSelBytes = sizeof(SelState) + 4;
+__host__ __device__ inline SelState* sel_state(char* base, size_t off) {
+    return reinterpret_cast<SelState*>(base + off + (reinterpret_cast<uintptr_t>(base) & 4));
+}
+
 // Byte offsets inside one problem's SVGD workspace.
 struct SvgdLayout {
     size_t cand_off;                // bracket values of the median select (uint32 bit patterns)

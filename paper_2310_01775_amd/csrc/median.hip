@@ -103,7 +103,7 @@ __device__ __forceinline__ MedView med_view(int N, int d, float fixed_h, const S
     v.cc = L.med_cc;
     v.seg_cap = L.cand_cap / kCandSegs & ~3u;
     v.smp = reinterpret_cast<float*>(b + L.smp_off);
-    v.sel = reinterpret_cast<SelState*>(b + L.sel_off);
+    v.sel = sel_state(b, L.sel_off);
     v.hist = reinterpret_cast<uint32_t*>(b + L.hist_off);
     v.cand = reinterpret_cast<uint32_t*>(b + L.cand_off);
     v.xr = reinterpret_cast<const float*>(b + L.x32_off);

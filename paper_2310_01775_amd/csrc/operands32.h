@@ -31,7 +31,7 @@ __device__ __forceinline__ View32 view32(const SvgdLayout& L, char* base) {
     v.part = reinterpret_cast<float*>(base + L.part_off);
     v.xs3 = reinterpret_cast<__bf16*>(base + L.xs3_off);
     v.vs3 = reinterpret_cast<__bf16*>(base + L.vs3_off);
-    v.sel = reinterpret_cast<const SelState*>(base + L.sel_off);
+    v.sel = sel_state(base, L.sel_off);
     return v;
 }
 

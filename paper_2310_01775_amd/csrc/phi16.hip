@@ -66,7 +66,7 @@ __device__ __forceinline__ View16 view16(const SvgdLayout& L, char* base) {
     v.xc = reinterpret_cast<__bf16*>(base + L.xc_off);
     v.vt = reinterpret_cast<__bf16*>(base + L.vt_off);
     v.p16 = reinterpret_cast<float*>(base + L.p16_off);
-    v.sel = reinterpret_cast<SelState*>(base + L.sel_off);
+    v.sel = sel_state(base, L.sel_off);
     return v;
 }
 

@@ -234,8 +234,8 @@ StructView struct_view(void* ws, const SvgdLayout& L, const StructKernel& sk) {
     v.feat = reinterpret_cast<float*>(base + L.sfeat_off);
     v.Lg = L;
     v.Lg.sel_off = L.sh_off;
-    v.bw.sel[0] = reinterpret_cast<const SelState*>(base + v.Lg.sel_off);
-    v.bw.sel[1] = reinterpret_cast<const SelState*>(base + L.sel_off);
+    v.bw.sel[0] = sel_state(base, v.Lg.sel_off);
+    v.bw.sel[1] = sel_state(base, L.sel_off);
     v.bw.fixed[0] = sk.h_g;
     v.bw.fixed[1] = sk.h_z;
     v.bw.K = sk.K;

@@ -213,7 +213,7 @@ SvgdLayout svgd_workspace_layout(int N, int d) {
     L.cand_off = off;
     off = align256(off + (N >= 2 ? (size_t)L.cand_cap * 4 : 0));
     L.sel_off = off;
-    off = align256(off + sizeof(SelState));
+    off = align256(off + kSelBytes);
     L.part_off = L.hist_off = off;
     off = align256(off + std::max(L.part_floats, (size_t)3 * kMedBins) * 4);
     L.x32_off = off;
@@ -260,7 +260,7 @@ SvgdLayout svgd_workspace_layout(int N, int d) {
     L.sfeat_off = off;
     off = align256(off + (size_t)2 * d * N * 4);
     L.sh_off = off;
-    off = align256(off + sizeof(SelState));
+    off = align256(off + kSelBytes);
     L.total = off;
     return L;
 }

@@ -1,8 +1,10 @@
 """The median's passes after pass 0: their workgroups agree on whether to run,
-whichever of them ends first."""
+whichever of them ends first; and where the select's state may lie."""
 import numpy as np
 import pytest
 import torch
+
+import workloads as W
 
 pytestmark = pytest.mark.gpu
 
@@ -27,3 +29,53 @@ def test_the_last_pass_leaves_the_word_its_workgroups_branch_on(ctx, N, d):
     at = (words == (N * (N - 1) // 2 + 1) // 2).nonzero().flatten()
     assert at.numel() == 1
     assert words[at + 1].item() == 1  # the passes were wanted, and nothing in them took that back
+
+
+# the finishing workgroup, the passes over the matrix cores' distances and over
+# direct ones (structured); every array argument is 4-byte aligned, no more
+@pytest.mark.parametrize("N", [700, 1500])
+def test_a_workspace_may_start_at_any_four_bytes(ctx, N):
+    import paper_2310_01775_amd as S
+    d = 18
+    rng = np.random.default_rng(N)
+    th, g = S.soa(rng.standard_normal((N, d))), S.soa(rng.standard_normal((N, d)))
+    need = S.Context.svgd_workspace_bytes(N, d)
+    kern = S.struct_kernel(S.KERNEL_PUSH, 3)
+
+    def steps(ws):
+        h, h2 = torch.zeros(1, device="cuda"), torch.zeros(2, device="cuda")
+        out = [ctx.svgd_step(th, g, h_out=h, workspace=ws), h,
+               ctx.svgd_step_structured(th, g, kern, h_out=h2, workspace=ws), h2,
+               ctx.svgd_step_bf16(th, g, workspace=ws)]
+        torch.cuda.synchronize()
+        return out
+
+    ref = steps(torch.zeros(need, dtype=torch.uint8, device="cuda"))
+    for shift in (4, 8, 12):
+        print("case", N, shift, flush=True)
+        buf = torch.zeros(need + 16, dtype=torch.uint8, device="cuda")
+        buf[need + shift:] = 77
+        for a, b in zip(steps(buf[shift:shift + need]), ref):
+            assert torch.equal(a, b)
+        assert (buf[:shift] == 0).all() and (buf[need + shift:] == 77).all()
+
+
+def test_a_solve_workspace_may_start_at_any_four_bytes(ctx):
+    import paper_2310_01775_amd as S
+    probs = [(W.make_scene(8, p, 2, 3, 40, 0.005), W.cost_weights(), W.make_particles(8, p, N, 3))
+             for p, N in enumerate([200, 1500])]
+    scenes, w, Ns = ([S.make_scene(s) for s, _, _ in probs], [S.make_cost(c) for _, c, _ in probs], [200, 1500])
+    cfg = S.make_cfg(3, lr=1e-3)
+    need = S.Context.solve_workspace_bytes(scenes, Ns, cfg)
+    outs = []
+    for shift in (0, 4):
+        print("case", shift, flush=True)
+        flat = torch.cat([S.soa(th).reshape(-1) for _, _, th in probs]).contiguous()
+        m, v, us = torch.zeros_like(flat), torch.zeros_like(flat), torch.zeros(2, device="cuda")
+        buf = torch.zeros(need + 16, dtype=torch.uint8, device="cuda")
+        cost = ctx.solve(scenes, w, Ns, cfg, flat, m, v, solve_time_us=us, workspace=buf[shift:shift + need])
+        torch.cuda.synchronize()
+        assert (us > 0).all()
+        outs.append((flat, m, v, cost))
+    for a, b in zip(*outs):
+        assert torch.equal(a, b)
