@@ -163,10 +163,11 @@ int32_t stamp_set_launch_shape(stamp_ctx* ctx, int32_t roll_block, int32_t roll_
  * own lane (more waves: faster while the rollout is latency-bound on a small
  * particle set), STAMP_LAYOUT_PACKED one lane per sub-rollout holding all its
  * blocks (about half the instructions per particle), for the forward and the
- * adjoint alike.  STAMP_LAYOUT_AUTO (default): packed from 9216 particles of
- * one problem, or for a batch once the block-per-lane form would need 2^17
- * lanes (two waves per SIMD).  Applies to every rollout
- * of the context's later calls.  STAMP_EINVAL for another value. */
+ * adjoint alike.  STAMP_LAYOUT_AUTO (default): for one problem by what
+ * each rollout keeps and its particles and blocks (packed from some 4000 to
+ * 10000 particles; the adjoint of checkpoints block per lane), for a batch packed
+ * once the block-per-lane form would need 2^17 lanes (two waves per SIMD).
+ * Applies to every rollout of the context's later calls.  STAMP_EINVAL for another value. */
 #define STAMP_LAYOUT_AUTO 0
 #define STAMP_LAYOUT_BLOCKS 1
 #define STAMP_LAYOUT_PACKED 2

@@ -24,8 +24,8 @@ hipError_t launch_rollout_fwd_batched(const ProblemDesc* descs, const int2* tile
                                       hipStream_t st, bool packed, int max_H, int max_B);
 hipError_t launch_rollout_adj_batched(const ProblemDesc* descs, const int2* tiles, int ntiles, int block,
                                       int grid, const float* theta, const float* tape, float cb_scalar,
-                                      float* grad, float* seg, uint32_t* status, hipStream_t st, bool packed, int max_H,
-                                      int max_B);
+                                      float* grad, float* seg, uint32_t* status, hipStream_t st, bool packed,
+                                      int max_H);
 
 // SVGD step of one problem.  h: when bandwidth > 0 it is used as is; otherwise
 // the median heuristic runs and writes h into the workspace (and h_out if

@@ -1905,7 +1905,8 @@ hipError_t launch_rollout_fwd_batched(const ProblemDesc* descs, const int2* tile
 
 hipError_t launch_rollout_adj_batched(const ProblemDesc* descs, const int2* tiles, int ntiles, int block,
                                       int grid, const float* theta, const float* tape, float cb_scalar,
-                                      float* grad, float* seg, uint32_t* status, hipStream_t st, bool packed, int max_H, int max_B) {
+                                      float* grad, float* seg, uint32_t* status, hipStream_t st, bool packed,
+                                      int max_H) {
     const int wf = adj_table_floats(max_H);
     if (packed)
         hipLaunchKernelGGL(k_rollout_adj_batched<true>, dim3(grid), dim3(block), (size_t)(block / 64) * wf * 4, st,

@@ -227,24 +227,50 @@ int64_t block_lanes(int N, int B) { return (int64_t)4 * (B == 1 ? 1 : (B == 2 ? 
 // Automatic layout.  The block-per-lane form keeps more waves in flight,
 // which pays while a rollout is latency-bound (few waves per SIMD); once its
 // waves fill the chip, one lane per sub-rollout issues about half the
-// instructions per particle and wins.  A packed rollout of one problem takes
-// about the same time up to some 12 000 particles (its waves do not fill the
-// chip before), so its line is a particle count, the same for every block
-// count: T = 200, H = 5, block per lane against packed, forward / adjoint in us,
-//   B = 2: 8 192 particles 68 / 87 against 93 / 99, 12 288 108 / 120 against 94 / 103;
-//   B = 3: 8 192 114 / 146 against 132 / 141, 12 288 161 / 207 against 138 / 143;
-//   B = 4: 8 192 135 / 180 against 170 / 199, 12 288 197 / 255 against 176 / 206.
-// A batch of problems goes by its lanes: the 64-problem batch takes 1.88 ms per
-// iteration packed, 2.12 ms block per lane.  The tape layout is the same, and
-// so are the results, bit for bit.
+// instructions per particle and wins.  The tape layout is the same, and so are
+// the results, bit for bit, so each rollout of one problem takes its own line
+// (us, T = 200, H = 5, block per lane against packed):
+// - A forward that keeps no full tape: once the block-per-lane lanes pass one
+//   wave per SIMD (8 192 particles of 2 blocks, 4 096 of 3 or 4).  B = 2: 8 192 48
+//   against 51, 8 700 68 / 49; B = 3: 4 001 54 / 70, 5 000 86 / 71; B = 4: 4 001 61 /
+//   97, 5 001 102 / 99, 8 700 146 / 98.
+// - A forward that writes the full tape is nearer the memory's rate, where the
+//   lanes' count matters less.  B = 2: 9 216 89 / 94, 9 999 98 / 94; B = 3: 8 192 111 /
+//   132, 9 216 139 / 134; B = 4: 8 192 129 / 170, 9 216 172 / 175, 9 700 179 / 176.
+// - The adjoint of a full tape: B = 2: 9 700 102 / 104, 10 240 105 / 103; B = 3, block
+//   per lane split over waves while a round of that fits the chip: 5 001 114 / 138,
+//   6 000 142 / 139, 8 192 146 / 141; B = 4: 8 192 180 / 199, 8 700 250 / 204.
+// - The adjoint of checkpoints replays each segment through memory, which the
+//   packed form does with half the waves: block per lane throughout (every 32
+//   steps; B = 2: 8 192 170 / 224, 65 536 1 019 / 1 190; B = 3: 8 192 258 / 343, 65 536
+//   1 775 / 2 032; B = 4: 16 384 581 / 621, 65 536 2 172 / 2 528).
+enum RolloutKind { kForward, kForwardTape, kAdjointTape, kAdjointCkpt };
+constexpr int64_t kOneWaveLanes = (int64_t)64 * 1024;
+bool packed_pays(int N, int B, RolloutKind kind) {
+    if (kind == kAdjointCkpt) return false;
+    if (kind == kForward) return block_lanes(N, B) > kOneWaveLanes;
+    if (B <= 2) return N > 9728;
+    return N > (B == 3 && kind == kAdjointTape ? 5120 : 8192);
+}
+
+// A batch goes by its lanes as a whole (its kernels compile every block count
+// into one body).  Solves of 8 iterations, T = 200, ms, block per lane against
+// packed: 4, 8, 16 problems of 1 024 particles and 3 blocks (65 536, 131 072, 262 144
+// lanes) 1.87 / 2.54, 2.77 / 2.80, 4.85 / 4.35; 16, 32 of 512 particles and 1 to 4
+// blocks (90 112, 180 224 lanes) 2.50 / 3.59, 4.20 / 4.45; the 64-problem batch 15.1
+// / 13.8.
 constexpr int64_t kPackedAutoLanes = (int64_t)2 * 64 * 1024;
-constexpr int kPackedAutoParticles = 9216;
 bool packed_for(const stamp_ctx* ctx, bool automatic) {
     if (ctx->rollout_layout == STAMP_LAYOUT_BLOCKS) return false;
     if (ctx->rollout_layout == STAMP_LAYOUT_PACKED) return true;
     return automatic;
 }
-bool packed_one(const stamp_ctx* ctx, int N) { return packed_for(ctx, N >= kPackedAutoParticles); }
+bool packed_fwd(const stamp_ctx* ctx, int N, int B, bool full_tape) {
+    return packed_for(ctx, packed_pays(N, B, full_tape ? kForwardTape : kForward));
+}
+bool packed_adj(const stamp_ctx* ctx, int N, int B, int ckpt) {
+    return packed_for(ctx, packed_pays(N, B, ckpt > 0 ? kAdjointCkpt : kAdjointTape));
+}
 
 constexpr int kGraphUnroll = 4;  // iterations per unrolled graph
 constexpr int kMaxSvgdDim = 64;
@@ -255,14 +281,14 @@ constexpr int kMaxSvgdN = 65536;
 //   tapes | segment buffers | grad | phi | cost scratch | per-problem SVGD regions
 struct SolvePlan {
     std::vector<stamp::ProblemDesc> descs;
-    std::vector<int2> roll_tiles, adj_tiles;  // forward and adjoint rollout tiles (their layouts may differ)
+    std::vector<int2> roll_tiles;  // rollout tiles of either direction
     std::vector<int4> dist_work, pass_work, fin_work, red_work;
     std::vector<int4> phi_work[kPhi32Classes];
     std::vector<int4> ctr_work, row16_work, phi16_work[2];  // BF16 form
     int phi_rows = 256;
     int dist_start[kMedLists] = {}, dist_n[kMedLists] = {};  // dist_work sorted by item shape
     int pass_start[kMedGram] = {}, pass_n[kMedGram] = {};    // pass_work by Gram shape
-    size_t clk_off = 0, desc_off = 0, roll_off = 0, adj_tiles_off = 0, dist_off = 0, pass_off = 0, fin_off = 0,
+    size_t clk_off = 0, desc_off = 0, roll_off = 0, dist_off = 0, pass_off = 0, fin_off = 0,
            red_off = 0;
     size_t ctr16_off = 0, row16_off = 0, phi16_off[2] = {};
     size_t phi_off[kPhi32Classes] = {};
@@ -278,8 +304,7 @@ constexpr int kRedChunk = 256;    // elements per workgroup of the phi reduction
 // Lay out the workspace and build the work lists.  phi_rows fixes the row
 // blocks of the contraction work list.
 void build_plan(int n, const stamp_scene* scenes, const int32_t* N, int K, float bandwidth, int phi_rows,
-                const std::vector<stamp::SimConst>* consts, SolvePlan& P, bool packed_fwd = false,
-                bool packed_adj = false) {
+                const std::vector<stamp::SimConst>* consts, SolvePlan& P, bool packed = false) {
     P = SolvePlan{};  // rebuilt from scratch: appending twice would repeat work items
     P.phi_rows = phi_rows;
     P.descs.resize(n);
@@ -351,18 +376,15 @@ void build_plan(int n, const stamp_scene* scenes, const int32_t* N, int K, float
     }
     // rollout tiles, those that take longest first (a tile's time grows with
     // its blocks and steps): the launch's last workgroups are then its
-    // cheapest.  The 64-problem batch (4 192 tiles, 1 to 4 blocks): forward 760
-    // -> 690 us, adjoint 815 -> 710 us by the kernel trace.
+    // cheapest.
     std::vector<int> longest(n);
     for (int p = 0; p < n; ++p) longest[p] = p;
     std::stable_sort(longest.begin(), longest.end(), [&](int x, int y) {
         return (int64_t)scenes[x].B * scenes[x].T > (int64_t)scenes[y].B * scenes[y].T;
     });
     for (int p : longest) {
-        const int step_f = rollout_tile_particles(scenes[p].B, packed_fwd);
-        const int step_a = rollout_tile_particles(scenes[p].B, packed_adj);
-        for (int i0 = 0; i0 < N[p]; i0 += step_f) P.roll_tiles.push_back(make_int2(p, i0));
-        for (int i0 = 0; i0 < N[p]; i0 += step_a) P.adj_tiles.push_back(make_int2(p, i0));
+        const int step = rollout_tile_particles(scenes[p].B, packed);
+        for (int i0 = 0; i0 < N[p]; i0 += step) P.roll_tiles.push_back(make_int2(p, i0));
     }
     P.n_theta = th;
     for (int c = 0; c < kMedLists; ++c) {
@@ -393,7 +415,6 @@ void build_plan(int n, const stamp_scene* scenes, const int32_t* N, int K, float
     P.clk_off = take((size_t)n * 2 * sizeof(uint64_t));
     P.desc_off = take(P.descs.size() * sizeof(ProblemDesc));
     P.roll_off = take(P.roll_tiles.size() * sizeof(int2));
-    P.adj_tiles_off = take(P.adj_tiles.size() * sizeof(int2));
     P.dist_off = take(P.dist_work.size() * sizeof(int4));
     P.pass_off = take(P.pass_work.size() * sizeof(int4));
     P.fin_off = take(P.fin_work.size() * sizeof(int4));
@@ -517,7 +538,6 @@ bool class_plan(int n, const stamp_scene* scenes, const int32_t* N, const stamp_
 // True when two plans place every workspace region at the same offset.
 bool same_layout(const SolvePlan& a, const SolvePlan& b) {
     bool ok = a.total == b.total && a.clk_off == b.clk_off && a.desc_off == b.desc_off && a.roll_off == b.roll_off &&
-              a.adj_tiles_off == b.adj_tiles_off &&
               a.dist_off == b.dist_off && a.pass_off == b.pass_off && a.fin_off == b.fin_off &&
               a.red_off == b.red_off &&
               a.ctr_off == b.ctr_off && a.err_off == b.err_off && a.tape_off == b.tape_off && a.seg_off == b.seg_off &&
@@ -670,7 +690,7 @@ int32_t stamp_rollout_fwd(stamp_ctx* ctx, const stamp_scene* scene, const stamp_
         return fail(ctx, STAMP_ENOSPACE, "tape %zu < %zu floats", tape_len, tape_floats(scene, N, ckpt_every));
     const TapeGeom g = tape_geom(scene, N, ckpt_every);
     hipError_t e = launch_rollout_fwd(c, N, theta, cost, tape, g, status, (hipStream_t)stream,
-                                      packed_one(ctx, N));
+                                      packed_fwd(ctx, N, c.B, tape && ckpt_every == 0));
     return e == hipSuccess ? STAMP_OK : hip_fail(ctx, e, "rollout_fwd");
 }
 
@@ -705,7 +725,7 @@ int32_t stamp_plan_readout(stamp_ctx* ctx, const stamp_scene* scene, const stamp
     if (e == hipSuccess) e = launch_onehot(N, scene->H, theta, plan, st);
     if (e == hipSuccess)
         e = launch_rollout_fwd(c, N, plan, cost, nullptr, tape_geom(scene, N, 0), status, st,
-                               packed_one(ctx, N));
+                               packed_fwd(ctx, N, c.B, false));
     return e == hipSuccess ? STAMP_OK : hip_fail(ctx, e, "plan_readout");
 }
 
@@ -728,7 +748,7 @@ static int32_t rollout_adj_impl(stamp_ctx* ctx, const stamp_scene* scene, const 
     const TapeGeom g = tape_geom(scene, N, ckpt_every);
     c.per_phase = per_phase;
     hipError_t e = launch_rollout_adj(c, N, theta, tape, g, cost_bar, 1.0f, grad, (float*)workspace, status,
-                                      (hipStream_t)stream, packed_one(ctx, N));
+                                      (hipStream_t)stream, packed_adj(ctx, N, c.B, ckpt_every));
     return e == hipSuccess ? STAMP_OK : hip_fail(ctx, e, "rollout_adj");
 }
 
@@ -986,21 +1006,20 @@ static int32_t solve_impl(stamp_ctx* ctx, int32_t n_problems, const stamp_scene*
         max_H = std::max(max_H, scenes[p].H);
         max_B = std::max(max_B, scenes[p].B);
     }
-    const bool packed = n_problems == 1 ? packed_one(ctx, N[0]) : packed_for(ctx, all_lanes >= kPackedAutoLanes);
-    const bool packed_adj = packed;
+    const bool packed = packed_for(ctx, all_lanes >= kPackedAutoLanes);
     SolvePlan P;
-    build_plan(n_problems, scenes, N, K, cfg->bandwidth, 256, &consts, P, packed, packed_adj);
+    build_plan(n_problems, scenes, N, K, cfg->bandwidth, 256, &consts, P, packed);
     // Every rebuild below (another row block) must keep the regions where the
     // pointers derived next point: the layout reserves the longest lists.
     const SolvePlan layout0 = P;
     auto rebuild = [&](int rows) -> bool {
-        build_plan(n_problems, scenes, N, K, cfg->bandwidth, rows, &consts, P, packed, packed_adj);
+        build_plan(n_problems, scenes, N, K, cfg->bandwidth, rows, &consts, P, packed);
         return same_layout(P, layout0);
     };
-    // the batch's sizes and layout: they fix the work lists and their places in
-    // the workspace, which the captured graphs hold
+    // the batch's sizes and the layout asked for: they fix the rollout kernels, the
+    // work lists and their places in the workspace, which the captured graphs hold
     const std::string tkey = P.key + "K" + std::to_string(K) + (cfg->bandwidth > 0 ? "fixed" : "median") +
-                             (packed ? "packed" : "blocks");
+                             "L" + std::to_string(ctx->rollout_layout);
     StampTune tune;
     auto it_t = ctx->tune.find(tkey);
     const bool have_tune = ctx->is_pinned || it_t != ctx->tune.end();
@@ -1012,7 +1031,6 @@ static int32_t solve_impl(stamp_ctx* ctx, int32_t n_problems, const stamp_scene*
     char* ws = (char*)workspace;
     ProblemDesc* d_desc = (ProblemDesc*)(ws + P.desc_off);
     int2* d_roll = (int2*)(ws + P.roll_off);
-    int2* d_adj_tiles = (int2*)(ws + P.adj_tiles_off);
     int* d_ctr = (int*)(ws + P.ctr_off);
     uint64_t* d_clk = (uint64_t*)(ws + P.clk_off);
     float* d_tape = (float*)(ws + P.tape_off);
@@ -1027,8 +1045,6 @@ static int32_t solve_impl(stamp_ctx* ctx, int32_t n_problems, const stamp_scene*
         hipError_t r;
         if ((r = upload(P.desc_off, P.descs.data(), P.descs.size() * sizeof(ProblemDesc))) != hipSuccess) return r;
         if ((r = upload(P.roll_off, P.roll_tiles.data(), P.roll_tiles.size() * sizeof(int2))) != hipSuccess) return r;
-        if ((r = upload(P.adj_tiles_off, P.adj_tiles.data(), P.adj_tiles.size() * sizeof(int2))) != hipSuccess)
-            return r;
         if ((r = upload(P.dist_off, P.dist_work.data(), P.dist_work.size() * sizeof(int4))) != hipSuccess) return r;
         if ((r = upload(P.pass_off, P.pass_work.data(), P.pass_work.size() * sizeof(int4))) != hipSuccess) return r;
         if ((r = upload(P.fin_off, P.fin_work.data(), P.fin_work.size() * sizeof(int4))) != hipSuccess) return r;
@@ -1045,7 +1061,7 @@ static int32_t solve_impl(stamp_ctx* ctx, int32_t n_problems, const stamp_scene*
         return hipStreamSynchronize(st);  // host lists may go out of scope after this
     };
     STAMP_TRY(upload_lists(), "upload work lists");
-    const int ntiles = (int)P.roll_tiles.size(), nadj = (int)P.adj_tiles.size();
+    const int ntiles = (int)P.roll_tiles.size();
     auto batch_plan = [&]() {
         BatchPlan B{};
         B.n_problems = n_problems;
@@ -1112,8 +1128,8 @@ static int32_t solve_impl(stamp_ctx* ctx, int32_t n_problems, const stamp_scene*
                     const float ms = timed([&] {
                         (void)launch_rollout_fwd_batched(d_desc, d_roll, ntiles, block, roll_grid(cand, ntiles), theta,
                                                          d_phi, d_tape, nullptr, st, packed, max_H, max_B);
-                        (void)launch_rollout_adj_batched(d_desc, d_adj_tiles, nadj, block, roll_grid(cand, nadj), theta,
-                                                         d_tape, -1.0f, d_grad, d_seg, nullptr, st, packed_adj, max_H, max_B);
+                        (void)launch_rollout_adj_batched(d_desc, d_roll, ntiles, block, roll_grid(cand, ntiles), theta,
+                                                         d_tape, -1.0f, d_grad, d_seg, nullptr, st, packed, max_H);
                     });
                     if (ms < best) {
                         best = ms;
@@ -1155,7 +1171,7 @@ static int32_t solve_impl(stamp_ctx* ctx, int32_t n_problems, const stamp_scene*
         if (single) {
             const ProblemDesc& D = P.descs[0];
             return launch_rollout_fwd(D.c, D.N, th + D.theta_off, cost + D.cost_off, tape ? tape + D.tape_off : nullptr,
-                                      D.g, stat, st, packed);
+                                      D.g, stat, st, packed_fwd(ctx, D.N, D.c.B, tape && K == 0));
         }
         return launch_rollout_fwd_batched(d_desc, d_roll, ntiles, tune.roll_block, rgrid, th, cost, tape, stat, st,
                                           packed, max_H, max_B);
@@ -1164,10 +1180,11 @@ static int32_t solve_impl(stamp_ctx* ctx, int32_t n_problems, const stamp_scene*
         if (single) {
             const ProblemDesc& D = P.descs[0];
             return launch_rollout_adj(D.c, D.N, theta + D.theta_off, d_tape + D.tape_off, D.g, nullptr, -1.0f,
-                                      d_grad + D.theta_off, d_seg + D.seg_off, stat, st, packed_adj);
+                                      d_grad + D.theta_off, d_seg + D.seg_off, stat, st,
+                                      packed_adj(ctx, D.N, D.c.B, K));
         }
-        return launch_rollout_adj_batched(d_desc, d_adj_tiles, nadj, tune.roll_block, roll_grid(tune, nadj), theta,
-                                          d_tape, -1.0f, d_grad, d_seg, stat, st, packed_adj, max_H, max_B);
+        return launch_rollout_adj_batched(d_desc, d_roll, ntiles, tune.roll_block, rgrid, theta, d_tape, -1.0f,
+                                          d_grad, d_seg, stat, st, packed, max_H);
     };
 
     // one SVGD iteration over every problem, captured once and replayed; with
@@ -1610,7 +1627,7 @@ int32_t stamp_mlp_label(stamp_ctx* ctx, const stamp_scene* scene, const stamp_co
     if (n_in > d && !enc) return fail(ctx, STAMP_EINVAL, "null scene encoding");
     const TapeGeom g = tape_geom(scene, N, 0);
     hipError_t e = launch_rollout_fwd(c, N, theta, cost, nullptr, g, status, (hipStream_t)stream,
-                                      packed_one(ctx, N));
+                                      packed_fwd(ctx, N, c.B, false));
     if (e == hipSuccess) e = launch_mlp_pack_rows(theta, N, d, enc, n_in, x, (hipStream_t)stream);
     return e == hipSuccess ? STAMP_OK : hip_fail(ctx, e, "mlp_label");
 }

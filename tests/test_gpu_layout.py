@@ -68,6 +68,26 @@ def test_layouts_give_the_same_solves(layout_ctx):
     assert torch.equal(outs[1][0], outs[3][0]) and torch.equal(outs[1][1], outs[3][1])
 
 
+# either side of the automatic layout's lines: two, three and four blocks, with
+# the full tape, with checkpoints and without a tape
+@pytest.mark.parametrize("B,N", [(2, 8192), (2, 8193), (2, 9728), (2, 9729), (3, 4096), (3, 4097), (3, 5121), (3, 8193),
+                                 (4, 4097), (4, 8193)])
+def test_automatic_layout_agrees_with_both(layout_ctx, B, N):
+    import paper_2310_01775_amd as S
+    ctx = layout_ctx
+    print("case", B, N, flush=True)
+    sc, cw = S.make_scene(W.make_scene(6, B, B, 2, 9, 0.005)), S.make_cost(W.cost_weights(rot=1.0))
+    theta = S.soa(W.make_particles(6, B, N, 2))
+    for ckpt in (0, 3):
+        ref = None
+        for layout in (S.LAYOUT_AUTO, S.LAYOUT_BLOCKS, S.LAYOUT_PACKED):
+            out = _run(ctx, S, layout, sc, cw, theta, N, ckpt, False) + (ctx.rollout_fwd(sc, cw, theta),)
+            torch.cuda.synchronize()
+            ref = ref or out
+            for a, b in zip(out, ref):
+                assert torch.equal(a, b)
+
+
 def test_layout_argument_is_checked(layout_ctx):
     import paper_2310_01775_amd as S
     with pytest.raises(S.StampError) as e:
