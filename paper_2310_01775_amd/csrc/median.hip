@@ -184,6 +184,15 @@ __device__ __forceinline__ void set_bandwidth(SelState* sel, int N, uint32_t m2_
     if (h_out) *h_out = h;
 }
 
+// The bandwidth when no median is wanted: the caller's, or 1 for a lone particle.
+__device__ __forceinline__ void given_bandwidth(const MedView& v, float* h_out) {
+    const float h = v.N < 2 ? 1.0f : v.fixed_h;
+    v.sel->h = h;
+    v.sel->m2 = -1.0f;
+    v.sel->mode = kModeDone;
+    if (h_out) *h_out = h;
+}
+
 // ---- select inside one workgroup of NT threads -----------------------------------
 // Sum over the workgroup (every thread gets the total); wt: NT/64 words of LDS.
 template <int NT>
@@ -339,13 +348,7 @@ __device__ void sample_select_body(const MedView& v, int exact, float* h_out) {
     SelState* sel = v.sel;
     const int N = v.N;
     if (N < 2 || v.fixed_h > 0.0f) {
-        if (tid == 0) {
-            const float h = N < 2 ? 1.0f : v.fixed_h;
-            sel->h = h;
-            sel->m2 = -1.0f;
-            sel->mode = kModeDone;
-            if (h_out) *h_out = h;
-        }
+        if (tid == 0) given_bandwidth(v, h_out);
         return;
     }
     const uint64_t P = pair_count(N);
@@ -1100,6 +1103,20 @@ __global__ __launch_bounds__(kSelThreads) void k_select_pack(OneMed a, const flo
                                          a.L.split3);
 }
 
+// The FP32 operands at a given bandwidth, in two launches: the means, then the
+// packing, whose first thread records h.  With nothing beside them to hide in, the
+// two stages take their own shapes, 1024 threads a mean and 64 rows a workgroup
+// (by the launches above: a step of 8192 particles, d = 30, 72.6 us, now 67.8; 3001, d = 48
+// 71.3, now 61.4).
+__global__ __launch_bounds__(kMeanThreads) void k_mean(OneMed a, const float* theta) {
+    particle_mean_body(a.N, blockIdx.x, theta, reinterpret_cast<float*>(a.ws + a.L.ctr_off));
+}
+
+__global__ __launch_bounds__(256) void k_pack_given(OneMed a, const float* theta, float* h_out) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) given_bandwidth(med_view(a.N, a.d, a.fixed_h, a.L, a.ws), h_out);
+    pack32_x_rows(a.N, a.d, a.L.ks32, blockIdx.x * 64, theta, view32(a.L, a.ws), a.L.split3);
+}
+
 template <int DP, int ROWS>
 __global__ __launch_bounds__(256) void k_med_items(OneMed a, const float* theta) {
     const MedView v = med_view(a.N, a.d, a.fixed_h, a.L, a.ws);
@@ -1309,6 +1326,11 @@ void launch_pass_batched(const BatchPlan& P, const ProblemDesc* descs, char* ws,
 hipError_t launch_median(int N, int d, const float* theta, float bandwidth, int exact, void* ws, const SvgdLayout& L,
                          float* h_out, hipStream_t st, int operands) {
     OneMed a{N, d, bandwidth > 0.0f ? bandwidth : 0.0f, L, static_cast<char*>(ws)};
+    if (operands == kOperands32 && N >= 2 && bandwidth > 0.0f) {
+        hipLaunchKernelGGL(k_mean, dim3(d), dim3(kMeanThreads), 0, st, a, theta);
+        hipLaunchKernelGGL(k_pack_given, dim3(L.npad / 64), dim3(256), 0, st, a, theta, h_out);
+        return hipGetLastError();
+    }
     // the sample distances only when a median is wanted: with a given
     // bandwidth (or one particle) the select just records h
     const int n_dist = N >= 2 && !(bandwidth > 0.0f) ? kMedSample / 64 : 0, n_ctr = operands && N >= 2 ? d : 0;
