@@ -226,7 +226,8 @@ inline int med_pass_grid(int N, int64_t items, int share = 1) {
 
 struct BatchPlan {
     int n_problems;
-    const int4* dist_work;  int n_dist;   // (p, row block, column chunk, -) of pass 0,
+    const int4* dist_work;  int n_dist;   // pass 0: (p, row block, column chunk, -) of direct items,
+                                          //   (p, workgroup, workgroups, -) of the Gram form,
     int dist_start[kMedLists];            // sorted by item shape: list c = entries
     int dist_n[kMedLists];                //   [dist_start[c], dist_start[c] + dist_n[c])
     const int4* pass_work;                // (p, workgroup, workgroups, -) of the median's later passes

@@ -194,23 +194,6 @@ __device__ __forceinline__ void given_bandwidth(const MedView& v, float* h_out) 
 }
 
 // ---- select inside one workgroup of NT threads -----------------------------------
-// Sum over the workgroup (every thread gets the total); wt: NT/64 words of LDS.
-template <int NT>
-__device__ __forceinline__ uint32_t wg_sum(uint32_t c, uint32_t* wt) {
-    static_assert(NT % 256 == 0, "wave totals are read four at a time");
-    for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
-    if ((threadIdx.x & 63) == 0) wt[threadIdx.x >> 6] = c;
-    __syncthreads();
-    uint32_t t = 0;
-#pragma unroll
-    for (int w = 0; w < NT / 64; w += 4) {
-        const uint4 v = *reinterpret_cast<const uint4*>(&wt[w]);
-        t += (v.x + v.y) + (v.z + v.w);
-    }
-    __syncthreads();
-    return t;
-}
-
 // Inclusive prefix sum over the workgroup in thread order.
 template <int NT>
 __device__ __forceinline__ uint32_t wg_scan(uint32_t x, uint32_t* wt) {
@@ -1096,8 +1079,8 @@ __global__ __launch_bounds__(kSelThreads) void k_sample_select(OneMed a, int exa
 }
 
 constexpr int kPackRows = 256;  // rows of a packing workgroup of kSelThreads
-__global__ __launch_bounds__(kSelThreads) void k_select_pack(OneMed a, const float* theta, float* h_out) {
-    if (blockIdx.x == 0) sample_select_body(med_view(a.N, a.d, a.fixed_h, a.L, a.ws), 1, h_out);
+__global__ __launch_bounds__(kSelThreads) void k_select_pack(OneMed a, const float* theta, int exact, float* h_out) {
+    if (blockIdx.x == 0) sample_select_body(med_view(a.N, a.d, a.fixed_h, a.L, a.ws), exact, h_out);
     else
         pack32_x_rows<kSelThreads / 256>(a.N, a.d, a.L.ks32, (blockIdx.x - 1) * kPackRows, theta, view32(a.L, a.ws),
                                          a.L.split3);
@@ -1233,7 +1216,7 @@ __global__ __launch_bounds__(256) void k_med_items_batched(const ProblemDesc* __
     med_item<DP, ROWS, kPass0>(v, theta + D.theta_off, w.y, w.z, v.sel->lo, v.sel->hi, 0, nullptr);
 }
 
-// entry = (problem, row block, first column chunk of the item, -)
+// entry = (problem, workgroup, workgroups, -) of the problem's equal runs of steps
 template <int KS, int ROWS>
 __global__ __launch_bounds__(256, 4) void k_med_items_gram_batched(const ProblemDesc* __restrict__ descs,
                                                                  const int4* __restrict__ work, char* ws) {
@@ -1342,7 +1325,8 @@ hipError_t launch_median(int N, int d, const float* theta, float bandwidth, int 
             hipLaunchKernelGGL(k_med_gather<kMeanThreads>, grid, dim3(256), 0, st, a, theta, n_dist);
     }
     if (n_ctr && operands == kOperands32)
-        hipLaunchKernelGGL(k_select_pack, dim3(1 + L.npad / kPackRows), dim3(kSelThreads), 0, st, a, theta, h_out);
+        hipLaunchKernelGGL(k_select_pack, dim3(1 + L.npad / kPackRows), dim3(kSelThreads), 0, st, a, theta,
+                           exact, h_out);
     else
         hipLaunchKernelGGL(k_sample_select, dim3(1), dim3(kSelThreads), 0, st, a, exact, h_out);
     if (exact && N >= 2 && !(bandwidth > 0.0f) && pair_count(N) > (uint64_t)kMedSample) {
