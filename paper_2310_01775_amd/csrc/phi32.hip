@@ -412,9 +412,8 @@ __global__ __launch_bounds__(256) void k_reduce32(One32 a, const float* theta, c
 // ---- batched kernels (work-list entries as in svgd.hip) ------------------------------
 __device__ __forceinline__ char* base32(const ProblemDesc& D, char* ws) { return ws + D.svgd_off; }
 
-// entry = (problem, coordinate, -, -)
-// a non-null step counter is advanced once (a solve's iteration counter, read
-// by the update at the iteration's end)
+// entry = (problem, first row of a 256-row chunk, -, -); four workgroups per
+// entry, 64 rows each
 __global__ __launch_bounds__(256) void k_pack32_v_batched(const ProblemDesc* __restrict__ descs,
                                                           const int4* __restrict__ work, const float* theta,
                                                           const float* grad, const float* wts, char* ws) {

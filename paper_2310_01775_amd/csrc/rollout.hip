@@ -96,19 +96,8 @@ __device__ __forceinline__ void phase_push(const SimConst& c, float Ax, float Ay
 // Tape entries hold, per (particle, side) sub-rollout, its blocks' states one
 // after another: block b of sub-rollout 4i+s is slot (4i+s)B+b, 6 floats
 // (x, y, phi, vx, vy, omega).
-__device__ __forceinline__ void load_blk(Blk& X, const float* __restrict__ entry, int64_t slot) {
-    const float2* p = reinterpret_cast<const float2*>(entry + slot * 6);
-    const float2 a = p[0], c = p[1], e = p[2];
-    X.x = a.x;
-    X.y = a.y;
-    X.ph = c.x;
-    X.vx = c.y;
-    X.vy = e.x;
-    X.om = e.y;
-}
-
-// The same at a 32-bit float offset from a wave-uniform entry pointer (a
-// scalar base plus a vector offset in the memory instruction).
+// They are read and written at a 32-bit float offset from a wave-uniform entry
+// pointer (a scalar base plus a vector offset in the memory instruction).
 __device__ __forceinline__ void load_blk_at(Blk& X, const float* __restrict__ entry, uint32_t off) {
     const float2* p = reinterpret_cast<const float2*>(entry + off);
     const float2 a = p[0], c = p[1], e = p[2];
@@ -118,13 +107,6 @@ __device__ __forceinline__ void load_blk_at(Blk& X, const float* __restrict__ en
     X.vx = c.y;
     X.vy = e.x;
     X.om = e.y;
-}
-
-__device__ __forceinline__ void store_blk(const Blk& X, float* __restrict__ entry, int64_t slot) {
-    float2* p = reinterpret_cast<float2*>(entry + slot * 6);
-    p[0] = make_float2(X.x, X.y);
-    p[1] = make_float2(X.ph, X.vx);
-    p[2] = make_float2(X.vy, X.om);
 }
 
 __device__ __forceinline__ void store_blk_at(const Blk& X, float* __restrict__ entry, uint32_t off) {
@@ -691,7 +673,7 @@ __device__ __forceinline__ int phase_entry(const TapeGeom& g, int k, int T, int 
 template <int B>
 struct AdjLane {
     int i, s, b, lw;
-    bool live;  // lanes past the last particle repeat particle N-1, write nothing
+    bool live;  // lanes past the last particle repeat particle N-1: the same scratch values, no results
     bool blk;   // a block slot (an idle one duplicates block B - 1)
     int64_t slot0, stride;
     uint32_t off;
@@ -1920,19 +1902,20 @@ hipError_t launch_rollout_adj_batched(const ProblemDesc* descs, const int2* tile
 }
 
 // ---------------------------------------------------------------------------
+static unsigned rollout_groups(int64_t lanes) { return (unsigned)((lanes + kRolloutBlock - 1) / kRolloutBlock); }
+
 template <int B>
 static hipError_t launch_fwd_b(const SimConst& c, int N, const float* theta, float* cost, float* tape,
                                const TapeGeom& g, uint32_t* status, hipStream_t st, bool packed) {
     // one block: both layouts are the same lanes; the block-per-lane kernel runs it
-    const bool pk = packed && B > 1;
-    const int64_t lanes = (int64_t)(pk ? 4 : Slots<B>::LANES) * N;
-    const unsigned grid = (unsigned)((lanes + kRolloutBlock - 1) / kRolloutBlock);
-    if (pk)
-        hipLaunchKernelGGL(k_rollout_fwd_packed<B>, dim3(grid), dim3(kRolloutBlock), rollout_lds_floats(c.H, B) * 4, st, c, N, theta, cost, tape,
-                           g, status);
-    else
-        hipLaunchKernelGGL(k_rollout_fwd<B>, dim3(grid), dim3(kRolloutBlock), rollout_lds_floats(c.H, 0) * 4, st, c, N, theta, cost, tape, g,
-                           status);
+    if constexpr (B > 1)
+        if (packed) {
+            hipLaunchKernelGGL(k_rollout_fwd_packed<B>, dim3(rollout_groups((int64_t)4 * N)), dim3(kRolloutBlock),
+                               rollout_lds_floats(c.H, B) * 4, st, c, N, theta, cost, tape, g, status);
+            return hipGetLastError();
+        }
+    hipLaunchKernelGGL(k_rollout_fwd<B>, dim3(rollout_groups((int64_t)Slots<B>::LANES * N)), dim3(kRolloutBlock),
+                       rollout_lds_floats(c.H, 0) * 4, st, c, N, theta, cost, tape, g, status);
     return hipGetLastError();
 }
 
@@ -1940,7 +1923,11 @@ static hipError_t launch_fwd_b(const SimConst& c, int N, const float* theta, flo
 // are on the chip at once.  A second round of them costs as long as the first,
 // while the waves of the whole-step sweep all fit: N = 4096, B = 3, H = 5 (1024
 // workgroups, 54 KB with chunks of four steps) took 131 us in two rounds, 99
-// whole-step, 93 with chunks of two steps (31 KB, one round).
+// whole-step, 93 with chunks of two steps (31 KB, one round).  That is the full
+// tape's line; the checkpointed kernels take it too, where two rounds have not been
+// measured (T = 400, K = 32, B = 1: one round at N = 4096 92 us, whole-step at 4097
+// 223).  Where the states leave no room for the four-wave kernel (B = 3, K = 36..50)
+// the two-wave one takes 178..211 us up to N = 1024, whole steps (K = 64) 292.
 constexpr int64_t kLdsBytes = 160 * 1024;
 static bool split_adjoint_pays(unsigned grid, int64_t lds) {
     return lds <= kLdsBytes && grid <= 256 * (kLdsBytes / lds);
@@ -1950,17 +1937,19 @@ template <int B>
 static hipError_t launch_adj_b(const SimConst& c, int N, const float* theta, const float* tape,
                                const TapeGeom& g, const float* cost_bar, float cb_scalar, float* grad,
                                float* seg, uint32_t* status, hipStream_t st, bool packed) {
-    const bool pk = packed && B > 1;
-    const int64_t lanes = (int64_t)(pk ? 4 : Slots<B>::LANES) * N;
-    const unsigned grid = (unsigned)((lanes + kRolloutBlock - 1) / kRolloutBlock);
+    if constexpr (B > 1)
+        if (packed) {
+            hipLaunchKernelGGL(k_rollout_adj_packed<B>, dim3(rollout_groups((int64_t)4 * N)), dim3(kRolloutBlock),
+                               adj_table_floats(c.H) * 4, st, c, N, theta, tape, g, cost_bar, cb_scalar, grad, seg,
+                               status);
+            return hipGetLastError();
+        }
+    const unsigned grid = rollout_groups((int64_t)Slots<B>::LANES * N);
     // LDS of the split sweeps: the table, two chunk buffers of 4 or 2 steps,
     // two buffers of a replayed segment's states
     const int64_t table = adj_table_floats(c.H) * 4, states = (int64_t)2 * g.ckpt * 6 * 64 * 4;
     const int64_t lds4 = table + 2 * pipe_buffer_floats<B, 4>() * 4, lds2 = table + 2 * pipe_buffer_floats<B, 2>() * 4;
-    if (pk)
-        hipLaunchKernelGGL(k_rollout_adj_packed<B>, dim3(grid), dim3(kRolloutBlock), adj_table_floats(c.H) * 4, st, c, N, theta, tape, g,
-                           cost_bar, cb_scalar, grad, seg, status);
-    else if (g.ckpt == 0 && split_adjoint_pays(grid, lds4))
+    if (g.ckpt == 0 && split_adjoint_pays(grid, lds4))
         hipLaunchKernelGGL((k_rollout_adj_split<B, 4>), dim3(grid), dim3(64 * (1 + kPipeHelpers)), lds4, st, c, N,
                            theta, tape, g, cost_bar, cb_scalar, grad, status);
     else if (g.ckpt == 0 && split_adjoint_pays(grid, lds2))
