@@ -1,5 +1,8 @@
 """The median's passes after pass 0: their workgroups agree on whether to run,
-whichever of them ends first; and where the select's state may lie."""
+whichever of them ends first; the widest particles; and where the select's
+state may lie."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -29,6 +32,24 @@ def test_the_last_pass_leaves_the_word_its_workgroups_branch_on(ctx, N, d):
     at = (words == (N * (N - 1) // 2 + 1) // 2).nonzero().flatten()
     assert at.numel() == 1
     assert words[at + 1].item() == 1  # the passes were wanted, and nothing in them took that back
+
+
+# FP32 products of 14 and 16 steps, in blocks of 64 and of 256 rows
+@pytest.mark.parametrize("N,d", [(1449, 49), (1500, 56), (2003, 57), (4097, 55), (4200, 64)])
+def test_bandwidth_of_wide_particles_is_the_order_statistic(ctx, N, d):
+    import paper_2310_01775_amd as S
+    print("case", N, d, flush=True)
+    th = np.random.default_rng(N + d).standard_normal((N, d)).astype(np.float32).astype(np.float64)
+    h = torch.zeros(1, device="cuda")
+    ctx.svgd_bandwidth(S.soa(th), h_out=h)
+    torch.cuda.synchronize()
+    m2 = float(h.item()) * math.log(N)
+    q = (th * th).sum(1)
+    D = (q[:, None] + q[None, :] - 2.0 * (th @ th.T))[np.triu_indices(N, 1)]
+    k = (D.size + 1) // 2
+    # 64 FP32 products and sums over terms of up to |xi|^2 + |xj|^2 <= 4 D or so
+    tol = 256 * 2.0 ** -24
+    assert (D < m2 * (1 - tol)).sum() < k <= (D <= m2 * (1 + tol)).sum()
 
 
 # the finishing workgroup, the passes over the matrix cores' distances and over
