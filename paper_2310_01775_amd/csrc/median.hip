@@ -1002,14 +1002,22 @@ __device__ void med_finish_body(const MedView& v, const float* __restrict__ thet
     while (lo < hi) {  // histogram passes over every pair (rare)
         const uint32_t s = shift_for((uint64_t)hi - lo + 1);
         for (int i = tid; i < N; i += NT)
-            for (int j = i + 1; j < N; ++j) {
-                float acc = 0.0f;
+            for (int j = i + 1; j < N; j += 4) {  // four at once share the row's loads
+                float acc[4] = {};
                 for (int l = 0; l < d; ++l) {
-                    const float df = theta[(int64_t)l * N + i] - theta[(int64_t)l * N + j];
-                    acc = fmaf(df, df, acc);
+                    const float* t = theta + (int64_t)l * N;
+                    const float ti = t[i];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const float df = ti - t[min(j + q, N - 1)];
+                        acc[q] = fmaf(df, df, acc[q]);
+                    }
                 }
-                const uint32_t x = __float_as_uint(acc);
-                if (x >= lo && x <= hi) atomicAdd(&lh[(x - lo) >> s], 1u);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const uint32_t x = __float_as_uint(acc[q]);
+                    if (j + q < N && x >= lo && x <= hi) atomicAdd(&lh[(x - lo) >> s], 1u);
+                }
             }
         wg_narrow<NT>(lh, wt, part, s, lo, hi, r);
     }
