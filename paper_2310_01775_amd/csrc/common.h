@@ -202,28 +202,6 @@ __host__ __device__ inline int med_pass_groups(int N) {
     return kCandSegs * (int)(p < 1 ? 1 : p > 4 ? 4 : p);
 }
 
-// Workgroups a pass is launched with: those of the candidates, or more for when it
-// has to go over every pair (the Gram form's, or `items` items of direct
-// differences; `share` problems side by side in a batch).  Each then adds its
-// histogram's bins to the global one, so a workgroup takes some 40 000 pairs until
-// a resident round of them has more: the bandwidth after a missed bracket with 64 /
-// 256 / 512 / 1024 workgroups, d = 30, N = 4096 184 / 99 / 110 / 150 us, 6000 338 / 140 /
-// 137 / 167, 12 000 (from 256) 370 / 295 / 295; the structured step, N = 8192, 3197 (128
-// workgroups) / 1256 / 960 / 878, N = 3 001 625 (64) / 310 / 293 / 336.
-inline int med_pass_grid(int N, int64_t items, int share = 1) {
-    const int64_t pairs = (int64_t)N * (N - 1) / 2, least = items ? 512 : 256;
-    int64_t g = pairs / 40000;
-    g = g < least ? least : g > 1024 ? 1024 : g;
-    if (items) {  // whole rounds of items
-        const int64_t rounds = (items + g - 1) / g;
-        g = (items + rounds - 1) / rounds;
-    } else if (g > med_gram_groups(N)) {
-        g = med_gram_groups(N);
-    }
-    g /= share;
-    return (int)(g > med_pass_groups(N) ? g : med_pass_groups(N));
-}
-
 struct BatchPlan {
     int n_problems;
     const int4* dist_work;  int n_dist;   // pass 0: (p, row block, column chunk, -) of direct items,

@@ -796,12 +796,8 @@ __device__ void med_gram(const MedView& v, int blk, int nblk, uint32_t lo, uint3
 }
 
 // ---- the passes after pass 0 -------------------------------------------------------
-// blk of nblk workgroups of 256, the first ncand of which take the candidates
-// (med_pass_groups); going over every pair again takes all of them, and
-// items(lo, hi, s, lh) histograms this workgroup's share.  With ncand workgroups
-// for either, a rank outside the bracket (or an overflow) cost the structured
-// step 3.2 ms at N = 8192 (now 0.88) and the bandwidth 184 us at N = 4096, d = 30 (now
-// 98); those that leave at once cost the usual select nothing measurable.
+// blk of nblk workgroups of 256; items(lo, hi, s, lh) histograms this
+// workgroup's share of all pairs.
 //   1: where rank k lies (the bracket's candidates, or, when it lies outside
 //      or a segment overflowed, every pair), and the histogram of that interval;
 //   2: the bin with rank k, and its histogram;
@@ -815,13 +811,13 @@ struct Interval {
 };
 
 template <class Items>
-__device__ __forceinline__ void pass_values(const MedView& v, int blk, int ncand, bool all, const Interval& I,
-                                            uint32_t s, uint32_t* lh, Items&& items) {
+__device__ __forceinline__ void pass_values(const MedView& v, int blk, int nblk, bool all, const Interval& I, uint32_t s,
+                                            uint32_t* lh, Items&& items) {
     if (all) {
         items(I.lo, I.hi, s, lh);
         return;
     }
-    const int parts = ncand / kCandSegs, g = blk / parts, part = blk % parts;
+    const int parts = nblk / kCandSegs, g = blk / parts, part = blk % parts;
     const uint32_t got = (uint32_t)v.sel->seg[g][0];
     const uint32_t n = got < v.seg_cap ? got : v.seg_cap;
     const uint32_t per = ((n + parts - 1) / parts + 3) & ~3u, b0 = (uint32_t)part * per;
@@ -838,8 +834,7 @@ __device__ __forceinline__ uint32_t narrow_from(const uint32_t* __restrict__ h, 
 }
 
 template <class Items>
-__device__ __forceinline__ void med_pass(const MedView& v, int pass, int blk, int nblk, int ncand, float* h_out,
-                                         Items&& items) {
+__device__ __forceinline__ void med_pass(const MedView& v, int pass, int blk, int nblk, float* h_out, Items&& items) {
     __shared__ uint32_t lh[kMedBins];
     __shared__ __align__(16) uint32_t wt[4];
     __shared__ uint32_t part[4];
@@ -876,15 +871,14 @@ __device__ __forceinline__ void med_pass(const MedView& v, int pass, int blk, in
             sel->rank1 = I.rank;
             sel->all = all;
         }
-        if (I.lo == I.hi || (!all && blk >= ncand)) return;
+        if (I.lo == I.hi) return;
         for (int b = tid; b < kMedBins; b += 256) lh[b] = 0;
         __syncthreads();
-        pass_values(v, blk, ncand, all, I, shift_for((uint64_t)I.hi - I.lo + 1), lh, items);
+        pass_values(v, blk, nblk, all, I, shift_for((uint64_t)I.hi - I.lo + 1), lh, items);
         flush(v.hist);
         return;
     }
     const bool all = sel->all != 0;
-    if (!all && blk >= ncand) return;
     Interval I{sel->lo1, sel->hi1, sel->rank1};
     if (pass == 2) {
         if (I.lo == I.hi) return;
@@ -895,7 +889,7 @@ __device__ __forceinline__ void med_pass(const MedView& v, int pass, int blk, in
             sel->rank2 = I.rank;
         }
         if (I.lo == I.hi) return;
-        pass_values(v, blk, ncand, all, I, shift_for((uint64_t)I.hi - I.lo + 1), lh, items);
+        pass_values(v, blk, nblk, all, I, shift_for((uint64_t)I.hi - I.lo + 1), lh, items);
         flush(v.hist + kMedBins);
         return;
     }
@@ -906,13 +900,13 @@ __device__ __forceinline__ void med_pass(const MedView& v, int pass, int blk, in
         return;
     }
     const uint32_t s = shift_for((uint64_t)I.hi - I.lo + 1);
-    pass_values(v, blk, ncand, all, I, s, lh, items);
+    pass_values(v, blk, nblk, all, I, s, lh, items);
     flush(v.hist + 2 * kMedBins);
     __threadfence();  // this workgroup's counts before its arrival
     __syncthreads();
     if (tid == 0) part[3] = atomicAdd(&sel->arrived, 1u);
     __syncthreads();
-    if (part[3] != (uint32_t)(all ? nblk : ncand) - 1) return;
+    if (part[3] != (uint32_t)nblk - 1) return;
     __threadfence();
     for (int b = tid; b < kMedBins; b += 256) lh[b] = __hip_atomic_load(&v.hist[2 * kMedBins + b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     wg_narrow<256>(lh, wt, part, s, I.lo, I.hi, I.rank);
@@ -1129,11 +1123,11 @@ __global__ __launch_bounds__(256, 4) void k_med_items_gram(OneMed a) {
     gram_pass0<KS, ROWS>(v, blockIdx.x, gridDim.x);
 }
 
-// passes 1..3
+// passes 1..3 (grid: a multiple of kCandSegs workgroups)
 template <int DP, int ROWS>
 __global__ __launch_bounds__(256) void k_med_pass(OneMed a, const float* theta, int pass, float* h_out) {
     const MedView v = med_view(a.N, a.d, a.fixed_h, a.L, a.ws);
-    med_pass(v, pass, blockIdx.x, gridDim.x, med_pass_groups(a.N), h_out,
+    med_pass(v, pass, blockIdx.x, gridDim.x, h_out,
              [&](uint32_t lo, uint32_t hi, uint32_t s, uint32_t* lh) {
                  const ItemList l = item_list(ROWS, v.rb, v.cc);
                  const int64_t n = l.count();
@@ -1147,7 +1141,7 @@ __global__ __launch_bounds__(256) void k_med_pass(OneMed a, const float* theta, 
 
 template <int KS, int ROWS>
 __device__ __forceinline__ void gram_pass(const MedView& v, int pass, int blk, int nblk, float* h_out) {
-    med_pass(v, pass, blk, nblk, med_pass_groups(v.N), h_out, [&](uint32_t lo, uint32_t hi, uint32_t s, uint32_t* lh) {
+    med_pass(v, pass, blk, nblk, h_out, [&](uint32_t lo, uint32_t hi, uint32_t s, uint32_t* lh) {
         med_gram<KS, ROWS, kPassHist>(v, blk, nblk, lo, hi, s, lh);
     });
 }
@@ -1345,7 +1339,7 @@ hipError_t launch_median(int N, int d, const float* theta, float bandwidth, int 
             by_gram_shape(med_gram_ks(L), L.med_rows, [&](auto k, auto r) {
                 hipLaunchKernelGGL((k_med_items_gram<k.value, r.value>), dim3(med_gram_groups(N)), dim3(256), 0, st, a);
                 for (int pass = 1; pass <= 3; ++pass)
-                    hipLaunchKernelGGL((k_med_pass_gram<k.value, r.value>), dim3(med_pass_grid(N, 0)), dim3(256), 0, st,
+                    hipLaunchKernelGGL((k_med_pass_gram<k.value, r.value>), dim3(med_pass_groups(N)), dim3(256), 0, st,
                                        a, pass, h_out);
             });
         else
@@ -1357,8 +1351,8 @@ hipError_t launch_median(int N, int d, const float* theta, float bandwidth, int 
                     return;
                 }
                 for (int pass = 1; pass <= 3; ++pass)
-                    hipLaunchKernelGGL((k_med_pass<dp.value, r.value>), dim3(med_pass_grid(N, items)), dim3(256), 0, st,
-                                       a, theta, pass, h_out);
+                    hipLaunchKernelGGL((k_med_pass<dp.value, r.value>), dim3(med_pass_groups(N)), dim3(256), 0, st, a,
+                                       theta, pass, h_out);
             });
     }
     return hipGetLastError();

@@ -313,9 +313,6 @@ void build_plan(int n, const stamp_scene* scenes, const int32_t* N, int K, float
     char buf[64];
     P.key.clear();
     std::vector<int4> dist_lists[kMedLists], pass_lists[kMedGram];
-    auto gram_form = [](int64_t N) { return N * (N - 1) / 2 > (1ll << 20); };  // median.hip
-    int n_gram = 0;
-    for (int p = 0; p < n; ++p) n_gram += gram_form(N[p]);
     for (int p = 0; p < n; ++p) {
         ProblemDesc& D = P.descs[p];
         memset(&D, 0, sizeof D);
@@ -341,13 +338,14 @@ void build_plan(int n, const stamp_scene* scenes, const int32_t* N, int K, float
         // median passes over all pairs, for problems whose pairs exceed the sample:
         // (row block, column chunk) items, and the workgroups of the later passes
         if (D.N >= 2 && !(bandwidth > 0.0f) && (uint64_t)D.N * (uint64_t)(D.N - 1) / 2 > (uint64_t)kMedSample) {
-            const bool gram = gram_form(D.N);
+            // problems above 2^20 pairs take the Gram form (median.hip)
+            const bool gram = (uint64_t)D.N * (uint64_t)(D.N - 1) / 2 > (1ull << 20);
             const int c = gram ? med_gram_list(med_gram_ks(D.sv), D.sv.med_rows)
                                : med_class(med_dp(D.d), D.sv.med_rows);
             if (gram) {
                 const int ni = med_gram_groups(D.N);
                 for (int q = 0; q < ni; ++q) dist_lists[c].push_back(make_int4(p, q, ni, 0));
-                const int nb = med_pass_grid(D.N, 0, n_gram);
+                const int nb = med_pass_groups(D.N);
                 for (int q = 0; q < nb; ++q) pass_lists[c - kMedDirect].push_back(make_int4(p, q, nb, 0));
             } else {
                 for (int rb = 0; rb < D.sv.med_rb; ++rb)  // items with a pair i < j only
