@@ -342,16 +342,18 @@ __device__ void sample_select_body(const MedView& v, int exact, float* h_out) {
     const float half = kBracketSigmas * 0.5f / sqrtf((float)S);  // four sigmas of the sample median's rank
     rank[0] = (uint32_t)fmaxf(1.0f, floorf((float)S * (0.5f - half)));
     rank[2] = (uint32_t)fminf((float)S, ceilf((float)S * (0.5f + half)));
-    uint32_t mn = 0xffffffffu, mx = 0u;  // range of the sample's (non-NaN) values
-    {  // the sample into LDS, all loads in flight
+    uint32_t mn = 0xffffffffu, mx = 0u;  // range of the sample's values
+    {  // the sample into LDS, all loads in flight; a NaN ranks as +inf, so that every
+       // rank is found
         const uint32_t* g = reinterpret_cast<const uint32_t*>(v.smp);
         uint32_t x[kMedSample / NT];
 #pragma unroll
         for (int u = 0; u < kMedSample / NT; ++u) x[u] = g[tid + NT * u];
 #pragma unroll
         for (int u = 0; u < kMedSample / NT; ++u) {
+            x[u] = min(x[u], 0x7f800000u);
             xs[tid + NT * u] = x[u];
-            if ((uint32_t)(tid + NT * u) < S && x[u] <= 0x7f800000u) {
+            if ((uint32_t)(tid + NT * u) < S) {
                 mn = min(mn, x[u]);
                 mx = max(mx, x[u]);
             }
@@ -373,7 +375,6 @@ __device__ void sample_select_body(const MedView& v, int exact, float* h_out) {
     __syncthreads();
     for (int b = tid; b < kMedBins; b += NT) lh[b] = 0;
     __syncthreads();
-    if (mn > mx) mn = mx = 0x7f800000u;  // every sample value is NaN
     uint32_t lo0 = 0u, hi2 = 0u, m = 0u;
     if (!exact || all) {
         m = wg_select_array<NT>(xs, kMedSample, mn, mx, rank[1], lh, wt, part);

@@ -155,3 +155,23 @@ def test_a_batch_outside_the_bracket_equals_its_loop(ctx, kind):
         torch.cuda.synchronize()
         assert torch.equal(flat[off:off + theta.numel()].view_as(theta), theta)
         off += theta.numel()
+
+
+# a lost particle's distances rank last; with half of the particles lost the
+# sample's median (or a small problem's, of all its pairs) is no number's
+@pytest.mark.parametrize("N,lost", [(300, 0), (300, 50), (300, 160), (100, 10), (100, 60), (300, 300)])
+def test_sampled_median_with_lost_particles(ctx, N, lost):
+    import paper_2310_01775_amd as S
+    print("case", N, lost, flush=True)
+    th = np.random.default_rng(N + lost).standard_normal((N, 6)).astype(np.float32).astype(np.float64)
+    th[np.random.default_rng(1).permutation(N)[:lost], 2] = np.nan
+    h = torch.zeros(1, device="cuda")
+    ctx.svgd_step_bf16(S.soa(th), S.soa(np.ones_like(th)), h_out=h)
+    torch.cuda.synchronize()
+    i, j = _sample(N) if N > 128 else np.triu_indices(N, 1)
+    D = ((th[i] - th[j]) ** 2).sum(1)
+    m2 = np.sort(np.where(np.isnan(D), np.inf, D))[(D.size + 1) // 2 - 1]
+    if np.isinf(m2):
+        assert math.isinf(h.item())
+    else:
+        assert abs(h.item() * math.log(N) / m2 - 1.0) < 16 * 2.0 ** -24
