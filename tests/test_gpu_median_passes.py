@@ -100,3 +100,24 @@ def test_a_solve_workspace_may_start_at_any_four_bytes(ctx):
         outs.append((flat, m, v, cost))
     for a, b in zip(*outs):
         assert torch.equal(a, b)
+
+
+# two tight clusters: half of all distances within a thousandth of each other,
+# far more than the candidate buffer takes from a bracket one histogram wide
+@pytest.mark.parametrize("jitter", [1e-4, 1e-3])
+@pytest.mark.parametrize("N,d", [(200, 6), (1000, 18), (1500, 30), (4097, 40)])
+def test_bandwidth_of_tight_clusters_is_the_order_statistic(ctx, N, d, jitter):
+    import paper_2310_01775_amd as S
+    print("case", N, d, jitter, flush=True)
+    th = jitter * np.random.default_rng(N + d).standard_normal((N, d))
+    th[:, 0] += np.where(np.arange(N) % 2, 1.0, -1.0)
+    th = th.astype(np.float32).astype(np.float64)
+    h = torch.zeros(1, device="cuda")
+    ctx.svgd_bandwidth(S.soa(th), h_out=h)
+    torch.cuda.synchronize()
+    m2 = float(h.item()) * math.log(N)
+    D = np.concatenate([((th[i] - th[i + 1:]) ** 2).sum(1) for i in range(N - 1)])
+    k = (D.size + 1) // 2
+    # 64 FP32 products and sums over terms of up to |xi|^2 + |xj|^2 = D / 2
+    tol = 64 * 2.0 ** -24
+    assert (D < m2 * (1 - tol)).sum() < k <= (D <= m2 * (1 + tol)).sum()
