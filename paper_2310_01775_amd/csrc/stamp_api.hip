@@ -1255,8 +1255,18 @@ static int32_t solve_impl(stamp_ctx* ctx, int32_t n_problems, const stamp_scene*
     upd_pre.t_pre = 1;
     auto iteration = [&]() -> hipError_t {
         hipError_t r;
-        if ((r = fork(1, ctr_in_mean ? d_ctr : nullptr)) != hipSuccess) return r;
+        int* const ctr = ctr_in_mean ? d_ctr : nullptr;
+        // A packed batch's rollouts fill the chip: the forward leads the graph, or
+        // the bandwidth stage's first launch (128 workgroups a problem) takes the
+        // room its waves need (solves of 4 iterations, T = 200, forward after the
+        // bandwidth / leading: 64 problems of 2 048 particles and 3 blocks 18.1 / 15.1
+        // ms, 64 of 512 and 2 2.87 / 2.76, 40 of 333 and 3 1.94 / 1.86).  Elsewhere
+        // the bandwidth stage may be the longer branch and goes first (one problem
+        // of 4 096 particles, 8 iterations, 1.85 / 1.96 ms).
+        const bool forward_leads = !single && packed;
+        if ((r = forward_leads ? fork_at() : fork(1, ctr)) != hipSuccess) return r;
         if ((r = roll_fwd(theta, (float*)(ws + P.cost_off), d_tape, status)) != hipSuccess) return r;
+        if (forward_leads && (r = branch(1, ctr)) != hipSuccess) return r;
         if ((r = roll_adj(status)) != hipSuccess) return r;
         if (cfg->dsvgd) {
             for (int p = 0; p < n_problems; ++p) {
